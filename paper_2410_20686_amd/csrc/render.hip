@@ -102,18 +102,38 @@ __device__ inline float red_finish(const float4& r0, const float4& r1) {
   return group8_sum(((r0.x + r0.y) + (r0.z + r0.w)) + ((r1.x + r1.y) + (r1.z + r1.w)));
 }
 
-__device__ inline float row_reduce9(const float (&g)[9], bool b3, bool b2, bool b1, bool b0) {
-  float a[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) a[j] = bfly<0x140>(g[j], g[4 + j], b3);  // row_mirror
-  float s8 = g[8] + dpp_read<0x140>(g[8]);
-  float c[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) c[j] = bfly<0x141>(a[j], a[2 + j], b2);  // row_half_mirror
-  s8 += dpp_read<0x141>(s8);
-  const float d = bfly<0x1B>(c[0], c[1], b1);                             // quad_perm [3,2,1,0]
-  s8 += dpp_read<0x1B>(s8);
-  return bfly<0xB1>(d, s8, b0);                                           // quad_perm [1,0,3,2]
+// The first two steps (quad_reduce9) fold pairs of values with DPP adds whose bank masks write one
+// value's sum into half of the lanes and the other value's into the other half: two 4-cycle adds
+// per pair, where a select per side and an add took about eleven (measured on the VALU: DPP add 4.1
+// cycles per wavefront, select 2.8 to 4.2, plain add 2.5).  They sit in one block in an order that
+// keeps two instructions between a write and a DPP read of it, as the hardware asks for.  They
+// leave g[0], g[1] and g[8]: bank b (lanes 4b .. 4b + 3) of a row holds four partial sums of value
+// 4 (b / 2) + 2 (b % 2) in g[0], of the next value in g[1], and of value 8 (every bank alike) in g[8].
+__device__ inline void quad_reduce9(float (&g)[9]) {
+  asm("s_nop 1\n"
+      "v_add_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf\n"
+      "v_add_f32_dpp %1, %1, %1 row_mirror row_mask:0xf bank_mask:0xf\n"
+      "v_add_f32_dpp %2, %2, %2 row_mirror row_mask:0xf bank_mask:0xf\n"
+      "v_add_f32_dpp %3, %3, %3 row_mirror row_mask:0xf bank_mask:0xf\n"
+      "v_add_f32_dpp %4, %4, %4 row_mirror row_mask:0xf bank_mask:0xf\n"
+      "v_add_f32_dpp %0, %5, %5 row_mirror row_mask:0xf bank_mask:0xc\n"
+      "v_add_f32_dpp %1, %6, %6 row_mirror row_mask:0xf bank_mask:0xc\n"
+      "v_add_f32_dpp %2, %7, %7 row_mirror row_mask:0xf bank_mask:0xc\n"
+      "v_add_f32_dpp %3, %8, %8 row_mirror row_mask:0xf bank_mask:0xc\n"
+      "v_add_f32_dpp %4, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xf\n"
+      "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n"
+      "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n"
+      "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n"
+      "v_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n"
+      : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]), "+v"(g[8])
+      : "v"(g[4]), "v"(g[5]), "v"(g[6]), "v"(g[7]));
+}
+
+__device__ inline float row_reduce9(float (&g)[9], bool b1, bool b0) {
+  quad_reduce9(g);
+  const float d = bfly<0x1B>(g[0], g[1], b1);  // quad_perm [3,2,1,0]
+  const float s8 = g[8] + dpp_read<0x1B>(g[8]);
+  return bfly<0xB1>(d, s8, b0);  // quad_perm [1,0,3,2]
 }
 
 
@@ -587,6 +607,20 @@ __global__ __launch_bounds__(kWave) void render_fwd4_kernel(
   }
 }
 
+// Flags of a staged entry in the one-wavefront compositors (above the quadrant mask).
+constexpr int kEntryWrap = 1;   // some pixel centre of the tile may need the seam wrap
+constexpr int kEntryClamp = 2;  // opacity above 0.99: alpha may be clamped
+
+// A uniform word the compiler cannot relate to its other uses, so that a test of it stays a scalar
+// test beside its branch.
+__device__ inline int opaque(int x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+
+// Keeps a rarely taken uniform branch a branch: the value is not computed on the other path.
+__device__ inline void keep_branch(float& x) { asm volatile("" : "+v"(x)); }
+
 // Reverse compositing state of one pixel (back to front from its last contributor).
 struct BwdPixel {
   float T, DS, dl0, dl1, dl2;  // DS = dL/dC . (colour of everything behind, incl. background)
@@ -611,7 +645,7 @@ __device__ inline double acc_total(const float (&acc)[NS][9][B], int q, int t) {
 }
 
 // Value q of an entry's 2D-gradient record (layout of g2d) from its per-wavefront sums; a, b: the
-// entry's staged record words (l0 = a.z, l1 = a.w, l2 = b.x).
+// entry's staged record words (l0 = a.z, l1 = a.w, l2 = b.x, opacity = b.z).
 template <int NS, int B>
 __device__ inline double g2d_flush_value(const float (&acc)[NS][9][B], int q, int t, const float4& a, const float4& b) {
   const double l0 = a.z, l1 = a.w, l2 = b.x;
@@ -624,38 +658,53 @@ __device__ inline double g2d_flush_value(const float (&acc)[NS][9][B], int q, in
       const double z11 = acc_total(acc, 2, t), z12 = acc_total(acc, 3, t), z22 = acc_total(acc, 4, t);
       return 2.0 * ((l1 * l1) * z11 + 2.0 * (l1 * l2) * z12 + (l2 * l2) * z22);
     }
+    case 5: return acc_total(acc, 5, t) / (double)b.z;
     default: return acc_total(acc, q, t);
   }
 }
 
 // One pixel's contribution of a Gaussian to the nine per-tile sums (added to gq when ADD, else
-// written; slots 0..4 in whitened coordinates as above), and the pixel's recursion step.  `ok`:
-// the Gaussian contributed to this pixel; t1 = l0 du + l1 dv, t2 = l2 dv.
+// written; slots 0..4 in whitened coordinates as above; slot 5 the sum of dpow, which is the opacity
+// gradient times the opacity, since alpha = opacity G wherever alpha depends on the inputs), and the
+// pixel's recursion step.  `ok`: the Gaussian contributed to this pixel; t1 = l0 du + l1 dv,
+// t2 = l2 dv.  `clamp` (uniform): the opacity is above 0.99, so that alpha may be clamped (else
+// G <= 1 keeps it below); two branches past an instruction or two (the whole step compiled
+// for both cases copies the pixel state between them, which costs more than the branches).
 template <bool ADD>
-__device__ inline void bwd_pixel_step(BwdPixel& P, bool ok, float power, float t1, float t2, const float4& a,
-                                      const float4& b, const float4& c, float (&gq)[9]) {
+__device__ inline void bwd_pixel_step(BwdPixel& P, bool ok, int clamp, float power, float t1, float t2, const float4& b,
+                                      const float4& c, float (&gq)[9]) {
   const float G = __expf(power);
   const float araw = b.z * G;
-  const bool live = ok && !(araw > kAlphaMax);  // contributes and unclamped: alpha depends on the inputs
-  // alpha = 0 where the Gaussian does not contribute, so its weight below is 0 without a select
-  const float alpha = ok ? fminf(araw, kAlphaMax) : 0.0f;
+  // alpha = 0 where the Gaussian does not contribute, so everything below is 0 without a select
+  float alpha = ok ? araw : 0.0f;
+  if (__builtin_expect(opaque(clamp) != 0, 0)) {
+    alpha = fminf(alpha, kAlphaMax);
+    keep_branch(alpha);
+  }
   const float inv_om = __builtin_amdgcn_rcpf(1.0f - alpha);
   // transmittance in front of this Gaussian; where it does not contribute alpha = 0 and the
   // reciprocal of 1 is exactly 1 (powers of two are exact), so T is unchanged without a select
   P.T = P.T * inv_om;
   const float wk = alpha * P.T;
   const float dc = fmaf(P.dl0, c.x, fmaf(P.dl1, c.y, P.dl2 * c.z));  // dL/dC . colour
-  const float dL_da = fmaf(dc, P.T, -P.DS * inv_om);
+  // dL/dalpha alpha = (dc T - DS / (1 - alpha)) alpha
+  float dpow = fmaf(-P.DS, alpha * inv_om, dc * wk);
+  if (__builtin_expect(opaque(clamp) != 0, 0)) {
+    dpow = araw > kAlphaMax ? 0.0f : dpow;  // a clamped alpha does not depend on the inputs
+    keep_branch(dpow);
+  }
   P.DS = fmaf(dc, wk, P.DS);
-  const float dla = live ? dL_da : 0.0f;
-  const float dpow = dla * alpha;
   const float g0 = dpow * t1, g1 = dpow * t2;
-  // values 2..8 are products x_q y_q (fused into the running sums when adding)
-  const float x[7] = {g0, g0, g1, dla, wk, wk, wk}, y[7] = {t1, t2, t2, G, P.dl0, P.dl1, P.dl2};
   gq[0] = ADD ? gq[0] + g0 : g0;
   gq[1] = ADD ? gq[1] + g1 : g1;
+  gq[5] = ADD ? gq[5] + dpow : dpow;
+  // the other values are products x_q y_q (fused into the running sums when adding)
+  const float x[6] = {g0, g0, g1, wk, wk, wk}, y[6] = {t1, t2, t2, P.dl0, P.dl1, P.dl2};
 #pragma unroll
-  for (int q = 0; q < 7; ++q) gq[2 + q] = ADD ? fmaf(x[q], y[q], gq[2 + q]) : x[q] * y[q];
+  for (int q = 0; q < 6; ++q) {
+    const int k = q < 3 ? 2 + q : 3 + q;
+    gq[k] = ADD ? fmaf(x[q], y[q], gq[k]) : x[q] * y[q];
+  }
 }
 
 // g2d layout: [items][9] = d/du, d/dv, d/dS_uu, d/dS_uv, d/dS_vv, d/dopacity, d/dr, d/dg,
@@ -756,7 +805,7 @@ __global__ __launch_bounds__(TILE* TILE) void render_bwd_kernel(ViewTable vt, co
         if (kSlots && pend) red_read(red[wq], lane, r0, r1);  // previous accepted entry's values
         const float4 c = S.s2[k];
         float gq[9];
-        bwd_pixel_step<false>(P, ok, power, t1, t2, a, b, c, gq);
+        bwd_pixel_step<false>(P, ok, 1, power, t1, t2, b, c, gq);
         if constexpr (kSlots) {
           if (pend) {
             const float sj = red_finish(r0, r1);
@@ -768,7 +817,7 @@ __global__ __launch_bounds__(TILE* TILE) void render_bwd_kernel(ViewTable vt, co
           pend = true;
           pk = k;
         } else {
-          const float rs = row_reduce9(gq, lane & 8, lane & 4, lane & 2, lane & 1);
+          const float rs = row_reduce9(gq, lane & 2, lane & 1);
           if (slot < 9) atomicAdd(&acc[0][slot][k], rs);  // 9 lanes per row, 4 rows: one LDS atomic
         }
       }
@@ -795,14 +844,31 @@ __global__ __launch_bounds__(TILE* TILE) void render_bwd_kernel(ViewTable vt, co
 // (l % 8, l / 8) of each quadrant): the four quadrants' contributions to an entry are added in
 // registers and reduced across lanes once, and a quadrant the forward's pixels did not reach
 // (its bit in the staged mask) costs nothing for that entry.
+//
+// The nine sums are reduced across lanes by two DPP steps only (quad_reduce9); the sixteen partial
+// sums that leaves of each value (four lanes in each of the four 16-lane rows) go to LDS, and a
+// group of kRingEntries entries is finished at once, one lane per (entry, value): sixteen partials
+// added per lane cost less than the selects, DPP adds and row swaps that would finish them entry by
+// entry.  The map from the whitened sums to the gradient record has no branches: value q is
+// u (x Sa + y Sb) + w Sc of three sums, with coefficients that are record words selected by q.
+//
+// Bound by VALU issue.  Measured at 500k Gaussians, 8 views of 2048x1024: 1,550 us with the sums
+// finished entry by entry, a divergent map per value and every step clamping; 1,402 us with bank-
+// masked folds, a branch-free map and the clamp only for entries that can need it; 1,350 us with the
+// last two steps of the reduction left to the group and the list words read from one register.
 template <int BATCH>
 struct Stage4 {
-  float4 s0[BATCH];
-  float4 s1[BATCH];
-  float4 s2[BATCH];
+  float4 s0[BATCH];  // u, v, l0, l1
+  float4 s1[BATCH];  // l2, p_min, opacity, unused
+  float4 s2[BATCH];  // r, g, b, 1 / opacity
   uint32_t sid[BATCH];
-  uint16_t list[BATCH];  // entry index | quadrant mask << 8
+  uint16_t list[BATCH];  // entry index | quadrant mask << 8 | flags << 12
 };
+
+// Entries per flush: seven entries of nine values take 63 of the 64 lanes.
+constexpr int kRingEntries = 7;
+constexpr int kRingRow = 36;  // per 16-lane row: 16 words of g[0], 16 of g[1], 4 of g[8]
+constexpr int kRingStride = 4 * kRingRow;
 
 template <int BIN, int BATCH>
 __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
@@ -812,13 +878,24 @@ __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
     int64_t qplane, TileSched sc) {
   constexpr int TILE = 16;
   __shared__ Stage4<BATCH> S;
-  __shared__ float acc[1][9][BATCH + 1];
+  __shared__ __attribute__((aligned(16))) float ring[kRingEntries * kRingStride];
+  __shared__ float sums[kWave];  // per (entry, value) of a group; the last word stays zero
   if (forward_is_stale(sc)) return;  // uniform
   const int nsplit = reverse_split(sc);
   __shared__ uint32_t s_claim;
   uint32_t round = 0, sel = 0;
   const int lane = threadIdx.x;
-  const int slot = (int)((kRowSlot >> (4 * (lane & 15))) & 0xF);
+  // this lane's words of an entry's ring record, and in a flush its entry fe, its value fq, the first
+  // of its value's four rows of partials and the words of the sums its value is mapped from
+  float* const out01 = ring + (lane >> 4) * kRingRow + (lane & 15);
+  float* const out8 = ring + (lane >> 4) * kRingRow + 32 + (lane & 3);
+  const int fe = lane / 9, fq = lane - 9 * fe;
+  const float4* const fin = reinterpret_cast<const float4*>(
+      ring + fe * kRingStride + (fq < 8 ? 16 * (fq & 1) + 4 * (fq >> 1) : 32));
+  const int fa = 9 * fe + (fq < 2 ? 0 : (fq < 5 ? 2 : fq));
+  const int fb = fq == 1 ? 9 * fe + 1 : (fq == 3 || fq == 4 ? 9 * fe + 3 : kWave - 1);
+  const int fc = fq == 4 ? 9 * fe + 4 : kWave - 1;
+  if (lane == kWave - 1) sums[lane] = 0.0f;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
   for (int g; (g = claim_task(sc, nsplit, round, &s_claim, sel)) >= 0;) {
     const int v = view_of_tile(vt, g);
@@ -868,11 +945,10 @@ __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
             const Rec r = rec[item];
             S.s0[e] = r.r0;
             const float reach = fabsf((float)tx0 + 0.5f * (float)TILE - r.r0.x) + 0.5f * (float)TILE + 1.0f;
-            S.s1[e] = make_float4(r.r1.x, r.r1.z, r.r1.y, reach < half ? 1.0f : 0.0f);
-            S.s2[e] = r.r2;
+            m |= (reach < half ? 0 : kEntryWrap << 4) | (r.r1.y > kAlphaMax ? kEntryClamp << 4 : 0);
+            S.s1[e] = make_float4(r.r1.x, r.r1.z, r.r1.y, 0.0f);
+            S.s2[e] = make_float4(r.r2.x, r.r2.y, r.r2.z, 1.0f / r.r1.y);
             S.sid[e] = item;
-#pragma unroll
-            for (int q = 0; q < 9; ++q) acc[0][q][e] = 0.0f;
           }
         }
         const uint64_t bl = __builtin_amdgcn_ballot_w64(m != 0u);
@@ -880,52 +956,75 @@ __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
         n += __popcll(bl);
       }
       __syncthreads();
-      uint32_t kmn = S.list[0];  // the next entry's list word, read one entry ahead
-      for (int i = 0; i < n; ++i) {
-        const uint32_t km = __builtin_amdgcn_readfirstlane(kmn);
-        kmn = S.list[min(i + 1, n - 1)];
-        const int k = (int)(km & 0xFFu);
-        const int jrel = end - 1 - k;
-        const float4 a = S.s0[k];
-        const float4 b = S.s1[k];
-        const uint32_t mq = km >> 8;
-        const bool wrap = __builtin_amdgcn_readfirstlane(__float_as_int(b.w)) == 0;  // uniform
-        float du0 = px0 - a.x, du1 = px1 - a.x;
-        if (wrap) {
-          du0 = wrap_du(du0, Wf, half);
-          du1 = wrap_du(du1, Wf, half);
-        }
-        const float4 c = S.s2[k];
-        float gq[9];
+      for (int i0 = 0; i0 < n; i0 += kRingEntries) {
+        const int m = min(kRingEntries, n - i0);
+        const uint32_t words = S.list[min(i0 + lane, n - 1)];  // the group's list words, one per lane
+        for (int i = 0; i < m; ++i) {
+          const uint32_t km = __builtin_amdgcn_readlane(words, i);
+          const int k = (int)(km & 0xFFu);
+          const int jrel = end - 1 - k;
+          const float4 a = S.s0[k];
+          const float4 b = S.s1[k];
+          const uint32_t mq = km >> 8;
+          float du0 = px0 - a.x, du1 = px1 - a.x;
+          const float4 c = S.s2[k];
+          float gq[9];
 #pragma unroll
-        for (int q = 0; q < 9; ++q) gq[q] = 0.0f;
-        bool any = false;
+          for (int q = 0; q < 9; ++q) gq[q] = 0.0f;
+          if (mq & (kEntryWrap << 4)) {  // uniform
+            du0 = wrap_du(du0, Wf, half);
+            du1 = wrap_du(du1, Wf, half);
+          }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (!((mq >> q) & 1u)) continue;  // uniform: no pixel of this quadrant reached the entry
-          const float dv = (q >> 1 ? py1 : py0) - a.y;
-          const float du = q & 1 ? du1 : du0;
-          const float t1 = fmaf(a.z, du, a.w * dv), t2 = b.x * dv;
-          const float p = -fmaf(t1, t1, t2 * t2);
-          const bool ok = jrel < P[q].last && !(p < b.y);
-          if (__builtin_amdgcn_ballot_w64(ok) == 0ull) continue;  // uniform
-          bwd_pixel_step<true>(P[q], ok, p, t1, t2, a, b, c, gq);
-          any = true;
+          for (int q = 0; q < 4; ++q) {
+            if (!((mq >> q) & 1u)) continue;  // uniform: no pixel of this quadrant reached the entry
+            const float dv = (q >> 1 ? py1 : py0) - a.y;
+            const float du = q & 1 ? du1 : du0;
+            const float t1 = fmaf(a.z, du, a.w * dv), t2 = b.x * dv;
+            const float p = -fmaf(t1, t1, t2 * t2);
+            const bool ok = jrel < P[q].last && !(p < b.y);
+            if (__builtin_amdgcn_ballot_w64(ok) == 0ull) continue;  // uniform
+            // (quadrant 0 comes first, so it writes the sums)
+            if (q == 0) bwd_pixel_step<false>(P[q], ok, (int)(mq & (kEntryClamp << 4)), p, t1, t2, b, c, gq);
+            else bwd_pixel_step<true>(P[q], ok, (int)(mq & (kEntryClamp << 4)), p, t1, t2, b, c, gq);
+          }
+          quad_reduce9(gq);
+          out01[i * kRingStride] = gq[0];
+          out01[i * kRingStride + 16] = gq[1];
+          if ((lane & 12) == 0) out8[i * kRingStride] = gq[8];
         }
-        if (!any) continue;  // uniform
-        const float rs = row_reduce9(gq, lane & 8, lane & 4, lane & 2, lane & 1);
-        const float ws = sum_rows(rs);
-        if (lane < 16 && slot < 9) acc[0][slot][k] = ws;
+        __syncthreads();
+        if (fe < m) {  // (never lane 63: fe = 7)
+          float r[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float4 p = fin[k * (kRingRow / 4)];
+            r[k] = (p.x + p.y) + (p.z + p.w);
+          }
+          sums[lane] = (r[0] + r[1]) + (r[2] + r[3]);
+        }
+        __syncthreads();
+        if (fe < m) {
+          const int t = S.list[i0 + fe] & 0xFF;
+          const float4 a = S.s0[t];
+          const float l0 = a.z, l1 = a.w, l2 = S.s1[t].x;
+          // value fq of the record, from the sums S0 .. S8:
+          //   0: 2 (l0 S0)   1: 2 (l1 S0 + l2 S1)   2: 2 l0 (l0 S2)   3: 4 l0 (l1 S2 + l2 S3)
+          //   4: 2 l1 (l1 S2 + 2 l2 S3) + 2 l2 (l2 S4)   5: S5 / opacity   6, 7, 8: Sq
+          float x = fq == 5 ? S.s2[t].w : 1.0f, u = fq < 2 ? 2.0f : 1.0f;
+          x = fq < 5 ? l1 : x;
+          x = fq == 0 || fq == 2 ? l0 : x;
+          const float y = fq == 4 ? 2.0f * l2 : l2;
+          u = fq == 2 ? 2.0f * l0 : u;
+          u = fq == 3 ? 4.0f * l0 : u;
+          u = fq == 4 ? 2.0f * l1 : u;
+          const double w = (double)l2;
+          const double d = fma((double)u, fma((double)x, (double)sums[fa], (double)y * (double)sums[fb]),
+                               (w + w) * (w * (double)sums[fc]));
+          if (d != 0.0) unsafeAtomicAdd(&g2d[(int64_t)S.sid[t] * 9 + fq], d);
+        }
+        __syncthreads();
       }
-      __syncthreads();
-      // the listed entries only (the others reached no pixel of this task)
-      for (int xq = lane; xq < 9 * n; xq += kWave) {
-        const int i = xq / 9, q = xq - 9 * i;
-        const int t = S.list[i] & 0xFF;
-        const double s = g2d_flush_value(acc, q, t, S.s0[t], S.s1[t]);
-        if (s != 0.0) unsafeAtomicAdd(&g2d[(int64_t)S.sid[t] * 9 + q], s);
-      }
-      __syncthreads();
     }
   }
 }
