@@ -138,22 +138,17 @@ __device__ inline float row_reduce9(float (&g)[9], bool b1, bool b0) {
 
 
 // Minimum over the rectangle [x0, x1] x [y0, y1] of f(x, y) = a x^2 + 2 b x y + c y^2 (positive
-// definite), with nba = -b/a and nbc = -b/c precomputed.  Float; callers add a margin that covers
-// its rounding.
+// definite), with nba = -b/a and nbc = -b/c precomputed.  f is convex with its minimum at the origin,
+// so its minimum over the rectangle lies on the vertical edge nearest to the origin or on the
+// horizontal one (a coordinate whose range holds 0 takes 0: with both, the origin itself).  Float;
+// callers add a margin that covers its rounding.
 __device__ inline float rect_min_quadratic(float a, float b, float c, float nba, float nbc, float x0, float x1,
                                            float y0, float y1) {
-  if (x0 <= 0.0f && 0.0f <= x1 && y0 <= 0.0f && 0.0f <= y1) return 0.0f;
-  float m = 3.0e38f;
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const float x = e ? x1 : x0;  // vertical edge: best y = -b x / c, clamped (median of three)
-    const float y = __builtin_amdgcn_fmed3f(nbc * x, y0, y1);
-    m = fminf(m, fmaf(a * x, x, y * fmaf(2.0f * b, x, c * y)));
-    const float yy = e ? y1 : y0;  // horizontal edge
-    const float xx = __builtin_amdgcn_fmed3f(nba * yy, x0, x1);
-    m = fminf(m, fmaf(a * xx, xx, yy * fmaf(2.0f * b, xx, c * yy)));
-  }
-  return m;
+  const float xc = __builtin_amdgcn_fmed3f(0.0f, x0, x1), yc = __builtin_amdgcn_fmed3f(0.0f, y0, y1);
+  const float y = __builtin_amdgcn_fmed3f(nbc * xc, y0, y1);  // best y on the vertical edge
+  const float x = __builtin_amdgcn_fmed3f(nba * yc, x0, x1);  // best x on the horizontal edge
+  const float b2 = 2.0f * b;
+  return fminf(fmaf(a * xc, xc, y * fmaf(b2, xc, c * y)), fmaf(a * x, x, yc * fmaf(b2, x, c * yc)));
 }
 
 // Quadrants (8x8 pixel blocks) of a tile that can hold a pixel where the Gaussian reaches
@@ -175,25 +170,30 @@ __device__ inline uint32_t quadrant_mask(const Rec& r, int tx0, int ty0, float W
   const float aa = fabsf(a), ab = fabsf(b), ac = fabsf(c);
   const float k2 = -2.0f * r.r1.z;
   const bool all_cols = eu + 3.5f >= half;
+  // Offsets of the quadrants' centres (one per column and per row of quadrants), and the margin at
+  // the farthest pixel centre of the tile, which covers every quadrant's.
+  float du[QPR], dy[QPR], xmax = 0.0f, ymax = 0.0f;
+#pragma unroll
+  for (int k = 0; k < QPR; ++k) {
+    du[k] = (float)(tx0 + 8 * k + 4) - u;
+    du[k] = du[k] >= half ? du[k] - Wf : (du[k] < -half ? du[k] + Wf : du[k]);
+    dy[k] = (float)(ty0 + 8 * k + 4) - v;
+    xmax = fmaxf(xmax, fabsf(du[k]));
+    ymax = fmaxf(ymax, fabsf(dy[k]));
+  }
+  const float X = xmax + 3.5f, Y = ymax + 3.5f;
+  const float tmax = fmaf(aa * X, X, Y * fmaf(2.0f * ab, X, ac * Y));
+  const float gmax = 2.0f * fmaf(aa + ab, X, (ab + ac) * Y);
+  const float lim = k2 + fmaf(1e-5f, tmax, fmaf(1e-2f, gmax, fmaf(1e-4f, k2, 1e-6f)));
   uint32_t mask = 0;
 #pragma unroll
   for (int q = 0; q < QPR * QPR; ++q) {
     if (!((sel >> q) & 1u)) continue;
-    const float qcx = (float)(tx0 + (q % QPR) * 8 + 4);
-    const float qcy = (float)(ty0 + (q / QPR) * 8 + 4);
-    float du = qcx - u;
-    if (du >= half) du -= Wf;
-    else if (du < -half) du += Wf;
-    const float dy = qcy - v;
-    bool hit = fabsf(dy) <= ev + 3.5f && (all_cols || fabsf(du) <= eu + 3.5f);
-    if (hit && fabsf(du) + 4.0f < half) {
-      const float X = fabsf(du) + 3.5f, Y = fabsf(dy) + 3.5f;
-      const float tmax = fmaf(aa * X, X, Y * fmaf(2.0f * ab, X, ac * Y));
-      const float gmax = 2.0f * fmaf(aa + ab, X, (ab + ac) * Y);
-      const float margin = fmaf(1e-5f, tmax, fmaf(1e-2f, gmax, fmaf(1e-4f, k2, 1e-6f)));
-      hit = rect_min_quadratic(a, b, c, nba, nbc, du - 3.5f, du + 3.5f, dy - 3.5f, dy + 3.5f) <= k2 + margin;
-    }
-    mask |= hit ? (1u << q) : 0u;
+    const float dx = du[q % QPR], dv = dy[q / QPR];
+    const bool rect = fabsf(dv) <= ev + 3.5f && (all_cols || fabsf(dx) <= eu + 3.5f);
+    const bool near = !(fabsf(dx) + 4.0f < half) ||
+                      rect_min_quadratic(a, b, c, nba, nbc, dx - 3.5f, dx + 3.5f, dv - 3.5f, dv + 3.5f) <= lim;
+    mask |= (rect & near) ? (1u << q) : 0u;
   }
   return mask;
 }
@@ -453,6 +453,11 @@ __global__ __launch_bounds__(TILE* TILE) void render_fwd_kernel(
 // entry are handed to the backward as in the one-pixel forward.  A quadrant task of a split tile
 // (see TileSched) runs the same code with its one quadrant selected, and hands its masks over in
 // the byte plane of its quadrant (plane q at byte offset q * qplane; whole tiles use plane 0).
+//
+// Bound by VALU issue; at 500k Gaussians, 8 views of 2048x1024 it went 808 -> 730 us when the stop
+// and clamp handling moved behind branches that are rarely taken (the accepted step: 58 instead of 66
+// issue cycles), the list words and the quadrants used went into registers instead of LDS, and the
+// footprint test took the two edges that face the centre instead of all four.
 // The 16x16 pixel block a task composites: its origin (bx0, by0), its quadrants (`sel`, updated)
 // and the byte plane of its culling masks.  BIN = 16: the tile, or one quadrant of a split tile
 // (plane q); BIN = 32: part p of the tile, the 16x16 block p = 2 by + bx with all four quadrants
@@ -475,12 +480,31 @@ __device__ inline void task_block(const ViewTable& vt, int v, int g, uint32_t& s
 
 template <int BATCH>
 struct FwdStage4 {
-  float4 s0[BATCH];
-  float4 s1[BATCH];
-  float4 s2[BATCH];
-  uint16_t list[BATCH];  // entry index | quadrant mask << 8
+  float4 s0[BATCH];  // u, v, l0, l1
+  float4 s1[BATCH];  // l2, p_min, opacity, unused
+  float4 s2[BATCH];  // r, g, b, unused
+  uint16_t list[BATCH];  // entry index | quadrant mask << 8 | flags << 12
   uint8_t used[BATCH];
 };
+
+// Flags of a staged entry in the one-wavefront compositors (above the quadrant mask).
+constexpr int kEntryWrap = 1;   // some pixel centre of the tile may need the seam wrap
+constexpr int kEntryClamp = 2;  // opacity above 0.99: alpha may be clamped
+
+// A uniform word the compiler cannot relate to its other uses, so that a test of it stays a scalar
+// test beside its branch.
+__device__ inline int opaque(int x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+
+// Lane `lane` (uniform) of `x` takes the uniform word `value`.
+__device__ inline void set_lane(uint32_t& x, uint32_t value, int lane) {
+  asm("s_mov_b32 m0, %2\n\tv_writelane_b32 %0, %1, m0" : "+v"(x) : "s"(value), "s"(lane));
+}
+
+// Keeps a rarely taken uniform branch a branch: the value is not computed on the other path.
+__device__ inline void keep_branch(float& x) { asm volatile("" : "+v"(x)); }
 
 template <int BIN, int BATCH>
 __global__ __launch_bounds__(kWave) void render_fwd4_kernel(
@@ -526,56 +550,73 @@ __global__ __launch_bounds__(kWave) void render_fwd4_kernel(
           const Rec r = rec[pair_items[base + e]];
           S.s0[e] = r.r0;
           const float reach = fabsf((float)tx0 + 0.5f * (float)TILE - r.r0.x) + 0.5f * (float)TILE + 1.0f;
-          S.s1[e] = make_float4(r.r1.x, r.r1.z, r.r1.y, reach < half ? 1.0f : 0.0f);
+          S.s1[e] = make_float4(r.r1.x, r.r1.z, r.r1.y, 0.0f);
           S.s2[e] = r.r2;
           S.used[e] = 0;
           m = quadrant_mask<TILE>(r, tx0, ty0, Wf, half, sel);
+          if (m != 0u) m |= (reach < half ? 0 : kEntryWrap << 4) | (r.r1.y > kAlphaMax ? kEntryClamp << 4 : 0);
         }
         const uint64_t bl = __builtin_amdgcn_ballot_w64(m != 0u);
         if (m != 0u) S.list[n + __popcll(bl & below)] = (uint16_t)(e | (m << 8));
         n += __popcll(bl);
       }
       __syncthreads();
-      uint32_t kmn = S.list[0];  // the next entry's list word, read one entry ahead
-      for (int i = 0; i < n; ++i) {
-        const uint32_t km = __builtin_amdgcn_readfirstlane(kmn);
-        kmn = S.list[min(i + 1, n - 1)];
-        const int k = (int)(km & 0xFFu);
-        const uint32_t mq = (km >> 8) & alive;
-        if (mq == 0u) continue;  // uniform
-        const float4 a = S.s0[k];
-        const float4 b = S.s1[k];
-        const bool wrap = __builtin_amdgcn_readfirstlane(__float_as_int(b.w)) == 0;  // uniform
-        float du0 = px0 - a.x, du1 = px1 - a.x;
-        if (wrap) {
-          du0 = wrap_du(du0, Wf, half);
-          du1 = wrap_du(du1, Wf, half);
-        }
-        uint32_t used = 0;
-        const float4 c = S.s2[k];  // once per entry, not per accepting quadrant: forward 0.81 -> 0.78 ms
+      for (int i0 = 0; i0 < n; i0 += kWave) {
+        // the list words of 64 entries, one per lane, and the quadrants used of each
+        const uint32_t words = S.list[min(i0 + lane, n - 1)];
+        uint32_t used_words = 0;
+        const int m = min(kWave, n - i0);
+        for (int i = 0; i < m; ++i) {
+          const uint32_t km = __builtin_amdgcn_readlane(words, i);
+          const int k = (int)(km & 0xFFu);
+          const uint32_t mq = (km >> 8) & (alive | 0xF0u);
+          if ((mq & 0xFu) == 0u) continue;  // uniform
+          const float4 a = S.s0[k];
+          const float4 b = S.s1[k];
+          float du0 = px0 - a.x, du1 = px1 - a.x;
+          if (mq & (kEntryWrap << 4)) {  // uniform
+            du0 = wrap_du(du0, Wf, half);
+            du1 = wrap_du(du1, Wf, half);
+          }
+          uint32_t used = 0;
+          const float4 c = S.s2[k];  // once per entry, not per accepting quadrant: forward 0.81 -> 0.78 ms
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (!((mq >> q) & 1u)) continue;  // uniform
-          const float dv = (q >> 1 ? py1 : py0) - a.y;
-          const float du = q & 1 ? du1 : du0;
-          const float t1 = fmaf(a.z, du, a.w * dv), t2 = b.x * dv;
-          const float power = -fmaf(t1, t1, fmaf(t2, t2, qstop[q]));
-          const bool ok = power >= b.y;  // alpha >= 1/255 (NaN once the pixel has stopped)
-          const uint64_t bok = __builtin_amdgcn_ballot_w64(ok);
-          if (bok == 0ull) continue;  // uniform
-          used |= 1u << q;
-          const float alpha = fminf(b.z * __expf(power), kAlphaMax);
-          const float Tn = T[q] * (1.0f - alpha);
-          const bool acc = ok && !(Tn < kTStop);
-          qstop[q] = ok != acc ? __builtin_nanf("") : qstop[q];  // stop: reached, but T would drop below 1e-4
-          const float w = (acc ? alpha : 0.0f) * T[q];
-          C0[q] = fmaf(w, c.x, C0[q]);
-          C1[q] = fmaf(w, c.y, C1[q]);
-          C2[q] = fmaf(w, c.z, C2[q]);
-          T[q] = acc ? Tn : T[q];
-          last[q] = acc ? (int)(base - rg.x) + k + 1 : last[q];
+          for (int q = 0; q < 4; ++q) {
+            if (!((mq >> q) & 1u)) continue;  // uniform
+            const float dv = (q >> 1 ? py1 : py0) - a.y;
+            const float du = q & 1 ? du1 : du0;
+            const float t1 = fmaf(a.z, du, a.w * dv), t2 = b.x * dv;
+            const float power = -fmaf(t1, t1, fmaf(t2, t2, qstop[q]));
+            bool ok = power >= b.y;  // alpha >= 1/255 (NaN once the pixel has stopped)
+            if (__builtin_amdgcn_ballot_w64(ok) == 0ull) continue;  // uniform
+            used |= 1u << q;
+            // alpha = 0 where the entry does not reach the pixel: T (1 - 0) = T exactly
+            float alpha = ok ? b.z * __expf(power) : 0.0f;
+            if (__builtin_expect(opaque((int)(mq & (kEntryClamp << 4))) != 0, 0)) {
+              alpha = fminf(alpha, kAlphaMax);
+              keep_branch(alpha);
+            }
+            float Tn = T[q] * (1.0f - alpha);
+            // a pixel stops at the entry that would take T below 1e-4, without it (rare: once per
+            // pixel; T itself never is below, so only reached pixels can)
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(Tn < kTStop) != 0ull, 0)) {
+              const bool stop = Tn < kTStop;
+              ok = ok && !stop;
+              alpha = stop ? 0.0f : alpha;
+              Tn = stop ? T[q] : Tn;
+              qstop[q] = stop ? __builtin_nanf("") : qstop[q];
+              keep_branch(qstop[q]);
+            }
+            const float w = alpha * T[q];
+            C0[q] = fmaf(w, c.x, C0[q]);
+            C1[q] = fmaf(w, c.y, C1[q]);
+            C2[q] = fmaf(w, c.z, C2[q]);
+            T[q] = Tn;
+            last[q] = ok ? (int)(base - rg.x) + k + 1 : last[q];
+          }
+          set_lane(used_words, used, i);
         }
-        if (lane == 0 && used) S.used[k] = (uint8_t)used;
+        if (lane < m) S.used[words & 0xFFu] = (uint8_t)used_words;
       }
       // quadrants whose pixels have all stopped (taken once per batch: within a batch a stopped
       // quadrant costs its test per entry, which no longer reaches any pixel)
@@ -606,20 +647,6 @@ __global__ __launch_bounds__(kWave) void render_fwd4_kernel(
     }
   }
 }
-
-// Flags of a staged entry in the one-wavefront compositors (above the quadrant mask).
-constexpr int kEntryWrap = 1;   // some pixel centre of the tile may need the seam wrap
-constexpr int kEntryClamp = 2;  // opacity above 0.99: alpha may be clamped
-
-// A uniform word the compiler cannot relate to its other uses, so that a test of it stays a scalar
-// test beside its branch.
-__device__ inline int opaque(int x) {
-  asm volatile("" : "+s"(x));
-  return x;
-}
-
-// Keeps a rarely taken uniform branch a branch: the value is not computed on the other path.
-__device__ inline void keep_branch(float& x) { asm volatile("" : "+v"(x)); }
 
 // Reverse compositing state of one pixel (back to front from its last contributor).
 struct BwdPixel {
