@@ -115,7 +115,7 @@ int odgs_plan_init(odgs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_view
   plan->pair_blocks = (int32_t)((pair_capacity + kSortBlockItems - 1) / kSortBlockItems);
   if (plan->pair_blocks < 1) plan->pair_blocks = 1;
   plan->depth_final = (4 % 2);                  // 4 passes of 8 bits over 32-bit depths
-  plan->pair_final = ((bits + 7) / 8) % 2;      // passes over the tile bits
+  plan->pair_final = sort_wide(bits, plan->pair_blocks) ? 1 : sort_passes(bits) % 2;  // passes over the tile bits
   // Coarse binning at 16x16 tiles: pairs by 32x32 tile (about half as many), sorted, then split
   // into the four 16x16 tiles' lists, which land in the other pair buffer.  By default from
   // kCoarseMinTiles tiles on (below, its three extra launches cost more than the sort saves).
@@ -133,7 +133,7 @@ int odgs_plan_init(odgs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_view
   if (cbits > 24) coarse = false;  // the sort passes must leave the mask bits (28..31) of the keys alone
   plan->coarse = coarse ? 1 : 0;
   plan->coarse_bits = coarse ? cbits : 0;
-  if (coarse) plan->pair_final = (((cbits + 7) / 8) % 2) ^ 1;
+  if (coarse) plan->pair_final = (sort_passes(cbits) % 2) ^ 1;
   const int64_t I = plan->items;
   const int64_t sblocks = (I + 1023) / 1024 + 1;
   size_t off = 0;
@@ -157,15 +157,16 @@ int odgs_plan_init(odgs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_view
   plan->off_pkey[1] = take((size_t)pair_capacity * 4);
   plan->off_pval[0] = take((size_t)pair_capacity * 4);
   plan->off_pval[1] = take((size_t)pair_capacity * 4);
-  const int64_t hb = plan->item_blocks > plan->pair_blocks ? plan->item_blocks : plan->pair_blocks;
+  const int64_t item_rows = (n + kSortBlockItems - 1) / kSortBlockItems * n_views;  // sort blocks, view by view
   // radix histograms; before binning the preprocess workgroups' item counts, after the pair sort
   // the coarse refinement's per-chunk counts (16 bytes per sort block), then the tile queue's
   // per-(block, bucket) counts
   const int64_t qwords = (tiles + 4095) / 4096 * 1024;
-  int64_t hwords = 256 * hb > qwords ? 256 * hb : qwords;
+  int64_t hwords = (int64_t)sort_hist_words(item_rows, plan->pair_blocks, !coarse && sort_wide(bits, plan->pair_blocks));
+  if (hwords < qwords) hwords = qwords;
   if (hwords < preprocess_blocks(n, n_views)) hwords = preprocess_blocks(n, n_views);
   plan->off_hist = take((size_t)hwords * 4);
-  plan->off_digit = take(256 * 4);
+  plan->off_digit = take((sort_tot_words(n_views) + ODGS_MAX_VIEWS + 1) * 4);
   plan->off_ranges = take((size_t)tiles * 8);
   plan->off_T = take((size_t)pixels * 4);
   plan->off_last = take((size_t)pixels * 4);

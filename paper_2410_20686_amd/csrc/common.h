@@ -232,6 +232,17 @@ hipError_t launch_l1_noalloc(const float* rgb, const float* tgt, int64_t count, 
 hipError_t launch_adam_step(int64_t n, int32_t sh_degree, const odgs_param_ptrs& raw, const odgs_param_ptrs& act,
                             const odgs_param_ptrs& grad, const odgs_param_ptrs& m, const odgs_param_ptrs& v,
                             const float* lr, int32_t* step, const odgs_adam_hyper& hp, hipStream_t st);
+// Passes of the tile sort over `bits` key bits, whether it takes one pass over the whole id instead,
+// and the words of the radix histograms (item_rows: sort blocks over the items of all views) and of
+// the digit totals with the item counts behind them (sort_tot_words + ODGS_MAX_VIEWS + 1).
+int sort_passes(int bits);
+bool sort_wide(int bits, int pair_blocks);
+size_t sort_hist_words(int64_t item_rows, int64_t pair_blocks, bool wide);
+size_t sort_tot_words(int32_t n_views);
+// Whether the items of a plan are sorted by counting, and their ranks (one word per item, which the
+// preprocess clears then).
+bool sort_by_rank(const odgs_plan* p);
+uint32_t* item_ranks(const odgs_plan* p, void* ws);
 hipError_t launch_fill_u32(uint32_t* ptr, uint32_t value, int64_t n, hipStream_t st);
 hipError_t launch_status_reset(const odgs_plan* p, void* ws, hipStream_t st);
 // Scheduling of a compositor launch: the queue, and for persistent launches the counter pair

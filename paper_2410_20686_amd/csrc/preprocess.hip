@@ -491,7 +491,7 @@ __global__ __launch_bounds__(256) void preprocess_kernel(int64_t n, const float*
                                                          float* __restrict__ depth_out, odgs_status* __restrict__ status,
                                                          SphRec* __restrict__ srec, SphCull* __restrict__ cone,
                                                          double* __restrict__ g2d, int g2d_stride, int vgroups,
-                                                         uint32_t* __restrict__ part) {
+                                                         uint32_t* __restrict__ part, uint32_t* __restrict__ rank) {
   // One thread per Gaussian and group of views (the views split into `vgroups` runs of equal
   // length but the last).  Workgroups go to the eight XCDs in turn, so the workgroups b, b + 8,
   // b + 16, ... share an XCD: those of one 256-Gaussian chunk (one per view group) are placed
@@ -626,6 +626,7 @@ __global__ __launch_bounds__(256) void preprocess_kernel(int64_t n, const float*
       rect[item] = rr;
       count[item] = cnt;
       dkey[item] = kept ? __float_as_uint(depth) : 0xffffffffu;
+      if (rank) rank[item] = 0;  // uniform: the sort counts into it
     }
     visible += kept ? 1 : 0;
     culled += (live && !kept) ? 1 : 0;
@@ -1063,6 +1064,7 @@ hipError_t launch_preprocess(const odgs_plan* p, const float* means, const float
   const unsigned grid = (unsigned)preprocess_blocks(p->n, vgroups);
   // (up to kFoldMinBlocks workgroups add their counts with one atomic each, without the fold launch)
   uint32_t* part = grid > kFoldMinBlocks ? ws_ptr<uint32_t>(ws, p->off_hist) : nullptr;
+  uint32_t* rank = sort_by_rank(p) ? item_ranks(p, ws) : nullptr;
   Rec* rec = ws_ptr<Rec>(ws, p->off_rec);
   Rect* rect = ws_ptr<Rect>(ws, p->off_rect);
   uint32_t* count = ws_ptr<uint32_t>(ws, p->off_count);
@@ -1083,11 +1085,11 @@ hipError_t launch_preprocess(const odgs_plan* p, const float* means, const float
   if (srec)                                                                                                       \
     hipLaunchKernelGGL((preprocess_kernel<KK, true>), dim3(grid), dim3(256), 0, st, p->n, means, scales, quats,     \
                        opac, sh, cams, vt, P, rec, rect, count, dkey, depth, status, srec, cone, g2d, p->g2d_stride,    \
-                       vgroups, part);                                                                                  \
+                       vgroups, part, rank);                                                                                  \
   else                                                                                                            \
     hipLaunchKernelGGL((preprocess_kernel<KK, false>), dim3(grid), dim3(256), 0, st, p->n, means, scales, quats,    \
                        opac, sh, cams, vt, P, rec, rect, count, dkey, depth, status, srec, cone, g2d, p->g2d_stride,    \
-                       vgroups, part)
+                       vgroups, part, rank)
   switch (p->sh_degree) {
     case 0: ODGS_PRE(1); break;
     case 1: ODGS_PRE(4); break;

@@ -1,16 +1,19 @@
-// Binning of the omnidirectional rasterizer, gfx950: depth pre-sort of the (Gaussian, view)
-// items, pair emission, stable LSD radix sort of the pairs by global tile, per-tile ranges.
+// Binning of the omnidirectional rasterizer, gfx950: depth sort of the (Gaussian, view) items view
+// by view, pair emission, stable LSD radix sort of the pairs by global tile, per-tile ranges.
 //
 // The pairs must end up ordered by the 64-bit key (global tile << 32 | depth bits), ties by
-// Gaussian index.  Instead of sorting 64-bit keys over all pairs, the items (far fewer than the
-// pairs) are first sorted by their 32-bit depth; pairs are then emitted in that order and sorted
-// stably by tile id alone, which needs only ceil(log2(tiles) / 8) passes over the pairs.  The
-// result is the same permutation as a stable sort of the 64-bit keys of index-ordered pairs.
+// Gaussian index.  Instead of sorting 64-bit keys over all pairs, each view's items (far fewer than
+// its pairs) are first sorted by their 32-bit depth; pairs are then emitted in (view, depth) order
+// and sorted stably by tile id alone.  The result is the same permutation as a stable sort of the
+// 64-bit keys of index-ordered pairs, since a tile belongs to one view.
 //
-// Radix sort: 8-bit digits, reduce-then-scan (no inter-workgroup spinning, so no forward-progress
-// assumption): per-block digit histograms, an exclusive scan per digit across blocks, then a
-// stable scatter in which each wavefront ranks its keys with 8 ballots (multi-split).
-// Every count the kernels need (number of pairs) is read from device memory, so the whole
+// Culled items leave the sort in its first pass (or the ranks' placement), so everything after it
+// handles the kept items only: a view that sees a part of the scene costs that part.
+//
+// Radix sort: reduce-then-scan (no inter-workgroup spinning, so no forward-progress assumption):
+// per-block digit histograms, exclusive scans per digit across blocks, then a stable scatter in which
+// each wavefront ranks its keys by ballots over the digit's bits (multi-split).
+// Every count the kernels need (kept items, pairs) is read from device memory, so the whole
 // chain runs without a host round trip and can be captured in a graph.
 #include "common.h"
 
@@ -27,18 +30,25 @@ __device__ inline uint32_t wave_incl_scan(uint32_t x) {
   return x;
 }
 
-// Inclusive scan across a 256-thread block.  `lds` holds 4 words; contains two barriers.
-__device__ inline uint32_t block_incl_scan256(uint32_t x, uint32_t* lds, uint32_t& total) {
+// Inclusive scan across a block of NT threads.  `lds` holds NT / 64 words; contains two barriers.
+template <int NT>
+__device__ inline uint32_t block_incl_scan(uint32_t x, uint32_t* lds, uint32_t& total) {
   const uint32_t incl = wave_incl_scan(x);
   const int w = threadIdx.x >> 6, lane = threadIdx.x & (kWave - 1);
   if (lane == kWave - 1) lds[w] = incl;
   __syncthreads();
   uint32_t pre = 0;
+  total = 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) pre += (k < w) ? lds[k] : 0u;
-  total = lds[0] + lds[1] + lds[2] + lds[3];
+  for (int k = 0; k < NT / kWave; ++k) {
+    pre += (k < w) ? lds[k] : 0u;
+    total += lds[k];
+  }
   __syncthreads();
   return incl + pre;
+}
+__device__ inline uint32_t block_incl_scan256(uint32_t x, uint32_t* lds, uint32_t& total) {
+  return block_incl_scan<256>(x, lds, total);
 }
 
 __global__ void fill_u32_kernel(uint32_t* __restrict__ p, uint32_t value, int64_t n) {
@@ -46,196 +56,302 @@ __global__ void fill_u32_kernel(uint32_t* __restrict__ p, uint32_t value, int64_
   if (i < n) p[i] = value;
 }
 
-__device__ inline uint32_t active_count(const uint32_t* n_dev, uint32_t n_host) {
-  return n_dev ? min(*n_dev, n_host) : n_host;
+// A key no kept item has (a kept depth is a finite float): culled items.
+constexpr uint32_t kCulledKey = 0xffffffffu;
+
+// Keys of segment `seg` (a view's items, or the whole pair list): all n_host, or the first n_dev[seg].
+__device__ inline uint32_t active_count(const uint32_t* n_dev, int seg, uint32_t n_host) {
+  return n_dev ? min(n_dev[seg], n_host) : n_host;
 }
 
-// Per-block histogram of the digit of `dbits` (<= 8) bits at `shift`: hist[digit * nblocks + block].  Each
-// wavefront counts into its own LDS histogram (a quarter of the same-address atomics), reading
-// four consecutive keys per 16-byte load.  AGG (for a pass over a key's top digit, which takes few
-// distinct values): the lanes of a round holding the same digit are found by ballots over its
-// bits and only the lowest of them adds their number, instead of one contended atomic per key.
-template <bool AGG>
-__global__ __launch_bounds__(kSortThreads) void radix_hist_kernel(const uint32_t* __restrict__ keys,
+// Lanes of the wavefront with the same digit of `dbits` (<= MAX) bits as this one, among those with
+// `valid` set.
+template <int MAX>
+__device__ inline uint64_t digit_peers(uint32_t d, int dbits, bool valid) {
+  uint64_t peers = __builtin_amdgcn_ballot_w64(valid);
+#pragma unroll
+  for (int b = 0; b < MAX; ++b) {
+    if (b >= dbits) break;  // uniform
+    const bool bit = (d >> b) & 1u;
+    const uint64_t bb = __builtin_amdgcn_ballot_w64(bit);
+    peers &= bit ? bb : ~bb;
+  }
+  return peers;
+}
+
+// Per-block histogram of the digit of `dbits` (<= 8) bits at `shift`: hist[block][digit], `nblocks`
+// blocks per segment of `stride` keys.  Each wavefront counts into its own LDS histogram (a quarter
+// of the same-address atomics).  DROP: culled keys are not counted.  AGG (for a pass over a key's
+// top digit, which takes few distinct values): the lanes of a round holding the same digit are found
+// by ballots over its bits and only the lowest of them adds their number, instead of one contended
+// atomic per key.
+template <bool DROP, bool AGG>
+__global__ __launch_bounds__(kSortThreads) void radix_hist_kernel(const uint32_t* __restrict__ keys, uint32_t stride,
                                                                  const uint32_t* __restrict__ n_dev, uint32_t n_host,
-                                                                 int shift, int dbits, uint32_t* __restrict__ hist,
-                                                                 int nblocks) {
+                                                                 int nblocks, int shift, int dbits,
+                                                                 uint32_t* __restrict__ hist) {
   const uint32_t dmask = (1u << dbits) - 1u;
   constexpr int NW = kSortThreads / kWave;
   __shared__ uint32_t h[NW][256];
-  const int t = threadIdx.x, wave = t >> 6;
-  const uint32_t n = active_count(n_dev, n_host);
-  const uint32_t start = blockIdx.x * (uint32_t)kSortBlockItems;
+  const int t = threadIdx.x, wave = t >> 6, lane = t & (kWave - 1);
+  const int seg = (int)blockIdx.x / nblocks, c = (int)blockIdx.x - seg * nblocks;
+  const uint32_t n = active_count(n_dev, seg, n_host);
+  const uint32_t start = (uint32_t)c * (uint32_t)kSortBlockItems;
   if (start >= n) return;  // uniform: blocks past the keys are neither scanned nor scattered
+  keys += (size_t)seg * stride;
 #pragma unroll
   for (int w = 0; w < NW; ++w) h[w][t] = 0;
   __syncthreads();
-  if constexpr (AGG) {
-    const int lane = t & (kWave - 1);
-    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
-    uint32_t k[kSortIpt];
+  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+  uint32_t k[kSortIpt];
 #pragma unroll
-    for (int r = 0; r < kSortIpt; ++r)  // unconditional loads stay in flight together
-      k[r] = keys[min(start + (uint32_t)(r * kSortThreads + t), n - 1)];
+  for (int r = 0; r < kSortIpt; ++r)  // unconditional loads stay in flight together
+    k[r] = keys[min(start + (uint32_t)(r * kSortThreads + t), n - 1)];
 #pragma unroll
-    for (int r = 0; r < kSortIpt; ++r) {
-      const uint32_t idx = start + (uint32_t)(r * kSortThreads + t);
-      const bool valid = idx < n;
-      const uint32_t d = (k[r] >> shift) & dmask;
-      uint64_t peers = __builtin_amdgcn_ballot_w64(valid);
-      for (int b = 0; b < dbits; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t bb = __builtin_amdgcn_ballot_w64(bit);
-        peers &= bit ? bb : ~bb;
-      }
+  for (int r = 0; r < kSortIpt; ++r) {
+    const bool valid = start + (uint32_t)(r * kSortThreads + t) < n && !(DROP && k[r] == kCulledKey);
+    const uint32_t d = (k[r] >> shift) & dmask;
+    if constexpr (AGG) {
+      const uint64_t peers = digit_peers<8>(d, dbits, valid);
       if (valid && (peers & below) == 0ull) atomicAdd(&h[wave][d], (uint32_t)__popcll(peers));
+    } else {
+      if (valid) atomicAdd(&h[wave][d], 1u);
     }
-  } else if (start + (uint32_t)kSortBlockItems <= n) {  // a whole block: 16-byte loads, all in flight
-    uint4 k4[kSortIpt / 4];
-#pragma unroll
-    for (int r = 0; r < kSortIpt / 4; ++r)
-      k4[r] = *reinterpret_cast<const uint4*>(keys + start + 4u * (uint32_t)(r * kSortThreads + t));
-#pragma unroll
-    for (int r = 0; r < kSortIpt / 4; ++r) {
-      atomicAdd(&h[wave][(k4[r].x >> shift) & dmask], 1u);
-      atomicAdd(&h[wave][(k4[r].y >> shift) & dmask], 1u);
-      atomicAdd(&h[wave][(k4[r].z >> shift) & dmask], 1u);
-      atomicAdd(&h[wave][(k4[r].w >> shift) & dmask], 1u);
-    }
-  } else {
-    for (uint32_t i = start + (uint32_t)t; i < n; i += kSortThreads) atomicAdd(&h[wave][(keys[i] >> shift) & dmask], 1u);
   }
   __syncthreads();
-  uint32_t c = 0;
+  uint32_t sum = 0;
 #pragma unroll
-  for (int w = 0; w < NW; ++w) c += h[w][t];
-  hist[t * nblocks + blockIdx.x] = c;
+  for (int w = 0; w < NW; ++w) sum += h[w][t];
+  hist[(size_t)blockIdx.x * 256 + t] = sum;
 }
 
-// Block d: exclusive scan of hist[d][0..live) in place, over the blocks that hold keys; digit
-// total to digit_tot[d].  Each thread takes kDigitIpt consecutive entries per round, so a row of
-// thousands of sort blocks needs a few block-wide scans rather than one per 256 entries.
-constexpr int kDigitIpt = 8;
-
-__global__ __launch_bounds__(256) void radix_digit_scan_kernel(uint32_t* __restrict__ hist, int nblocks,
-                                                               const uint32_t* __restrict__ n_dev, uint32_t n_host,
-                                                               uint32_t* __restrict__ digit_tot) {
-  __shared__ uint32_t lds[4];
-  uint32_t* row = hist + (size_t)blockIdx.x * nblocks;
-  const uint32_t n = active_count(n_dev, n_host);
-  const int live = min(nblocks, (int)((n + (uint32_t)kSortBlockItems - 1) / (uint32_t)kSortBlockItems));
-  uint32_t carry = 0;
-  for (int base = 0; base < live; base += 256 * kDigitIpt) {
-    const int k0 = base + (int)threadIdx.x * kDigitIpt;
-    uint32_t x[kDigitIpt], sum = 0;
+// Exclusive scan of hist[block][digit] over the blocks of each segment that hold keys, in place, and
+// the digit totals tot[segment][digit]: a workgroup per COLS digits (pieces of the rows) and segment,
+// COLS threads along the digits and 1024 / COLS groups of consecutive blocks.
+template <int COLS>
+__global__ __launch_bounds__(1024) void radix_scan_kernel(uint32_t* __restrict__ hist,
+                                                          const uint32_t* __restrict__ n_dev, uint32_t n_host,
+                                                          int nblocks, int bins, uint32_t* __restrict__ tot) {
+  constexpr int G = 1024 / COLS;
+  __shared__ uint32_t s[G][COLS + 1];
+  __shared__ uint32_t wtot[1024 / kWave];
+  const int t = threadIdx.x, col = t % COLS, g = t / COLS, seg = (int)blockIdx.y;
+  const int d = (int)blockIdx.x * COLS + col;
+  const uint32_t n = active_count(n_dev, seg, n_host);
+  const int rows = min(nblocks, (int)((n + (uint32_t)kSortBlockItems - 1) / (uint32_t)kSortBlockItems));
+  uint32_t* h = hist + (size_t)seg * nblocks * bins + d;
+  const int chunk = (rows + G - 1) / G, r0 = min(rows, g * chunk), r1 = min(rows, r0 + chunk);
+  uint32_t sum = 0;
+#pragma unroll 8
+  for (int r = r0; r < r1; ++r) sum += h[(size_t)r * bins];
+  s[g][col] = sum;
+  __syncthreads();
+  // exclusive prefix over the groups of each digit: G consecutive threads per digit
+  {
+    const int c2 = t / G, g2 = t % G, lane = t & (kWave - 1), w = t >> 6;
+    const uint32_t x = s[g2][c2];
+    constexpr int SPAN = G < kWave ? G : kWave;
+    uint32_t incl = x;
 #pragma unroll
-    for (int j = 0; j < kDigitIpt; ++j) {
-      x[j] = k0 + j < live ? row[k0 + j] : 0u;
-      sum += x[j];
+    for (int off = 1; off < SPAN; off <<= 1) {
+      const uint32_t y = __shfl_up(incl, off);
+      if ((lane % SPAN) >= off) incl += y;
     }
-    uint32_t total;
-    uint32_t run = carry + block_incl_scan256(sum, lds, total) - sum;
-#pragma unroll
-    for (int j = 0; j < kDigitIpt; ++j) {
-      if (k0 + j < live) row[k0 + j] = run;
-      run += x[j];
+    if (lane == kWave - 1) wtot[w] = incl;
+    __syncthreads();
+    if constexpr (G > kWave) {
+      for (int k = c2 * (G / kWave); k < w; ++k) incl += wtot[k];
     }
-    carry += total;
+    if (g2 == G - 1) tot[(size_t)seg * bins + (int)blockIdx.x * COLS + c2] = incl;
+    s[g2][c2] = incl - x;
   }
-  if (threadIdx.x == 0) digit_tot[blockIdx.x] = carry;
+  __syncthreads();
+  uint32_t run = s[g][col];
+#pragma unroll 8
+  for (int r = r0; r < r1; ++r) {
+    const uint32_t x = h[(size_t)r * bins];
+    h[(size_t)r * bins] = run;
+    run += x;
+  }
 }
 
-// Stable scatter of one digit pass (a digit of `dbits` <= 8 bits at `shift`).  vin == nullptr
-// means the values are the input positions.
-// Phase 1: each wavefront ranks its own contiguous quarter of the block's keys (rounds of 64 in
+struct ScatterArgs {
+  const uint32_t* kin;
+  const uint32_t* vin;  // nullptr: the values are the input positions
+  uint32_t* kout;
+  uint32_t* vout;
+  const uint32_t* n_dev;  // live keys per segment (nullptr: n_host)
+  uint32_t n_host;
+  uint32_t stride;  // keys from one segment to the next, in input and output
+  int nblocks;      // blocks per segment
+  int shift, dbits;
+  const uint32_t* hist;  // [block][digit]: scanned over the blocks, or (FOLD) the counts themselves
+  const uint32_t* tot;   // [segment][digit] (not with FOLD)
+  uint32_t* live_out;    // first pass over items: kept keys per segment
+  uint32_t* packed_out;  // last pass over items: the segments are written without gaps, their sum here
+  uint2* ranges;         // single pass over tile ids: every tile's [start, end)
+  int tiles;
+};
+
+// Stable scatter of one digit pass.  DROP: culled keys are left out (and the kept ones counted).
+// Phase 1: each wavefront ranks its own contiguous part of the block's keys (rounds of 64 in
 // input order; per round a multi-split by dbits ballots gives the rank among same-digit peers, added
 // to the wavefront's running per-digit count in LDS) with no block barriers; one exclusive prefix
 // over the wavefronts per digit then makes the ranks block-wide and stable.  Phase 2 places the
 // keys digit-sorted in LDS; phase 3 writes them out in that order, so consecutive threads store
 // consecutive addresses of each digit's output run.
-__global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
-    const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
-    uint32_t* __restrict__ vout, const uint32_t* __restrict__ n_dev, uint32_t n_host, int shift, int dbits,
-    const uint32_t* __restrict__ hist, const uint32_t* __restrict__ digit_tot, int nblocks) {
-  const uint32_t dmask = (1u << dbits) - 1u;
-  constexpr int NW = kSortThreads / kWave;
+// FOLD: the block sums the earlier blocks' counts of each digit itself (few blocks per segment), which
+// saves the scan's launch.
+//
+// At small sizes the kernel is one chain of rounds per wavefront (11 us at 6,000 keys with 256 threads
+// and 16 rounds; 8 us with 512 threads and eight), at large ones bound by its scattered stores: at 4M
+// items of eight views a pass takes 34 us (39 us over all views at once: a view's segment is small enough
+// for the stores of neighbouring blocks to meet in the caches).
+template <int NT, int BINS, bool DROP, bool FOLD>
+__global__ __launch_bounds__(NT) void radix_scatter_kernel(ScatterArgs a) {
+  const uint32_t dmask = (1u << a.dbits) - 1u;
+  constexpr int NW = NT / kWave;
   constexpr int PER_WAVE = kSortBlockItems / NW;
   constexpr int ROUNDS = PER_WAVE / kWave;
+  constexpr int DPT = BINS >= NT ? BINS / NT : 1;  // consecutive digits per thread
   __shared__ uint32_t s_key[kSortBlockItems];
   __shared__ uint32_t s_val[kSortBlockItems];
-  __shared__ uint32_t wh[NW][256];    // per-wavefront running digit counts, then local placement starts
-  __shared__ uint32_t gshift[256];    // global start minus local start of each digit for this block
-  __shared__ uint32_t lds[4];
+  __shared__ uint16_t wh[NW][BINS];  // per-wavefront running digit counts, then local placement starts
+  __shared__ uint32_t gshift[BINS];  // global start minus local start of each digit for this block
+  __shared__ uint32_t lds[NW];
   const int t = threadIdx.x, lane = t & (kWave - 1), wave = t >> 6;
-  const uint32_t n = active_count(n_dev, n_host);
-  const uint32_t start = blockIdx.x * (uint32_t)kSortBlockItems;
-  if (start >= n) return;  // uniform across the block
-  const uint32_t nb = min((uint32_t)kSortBlockItems, n - start);
-  uint32_t total;
-  const uint32_t dt = digit_tot[t];
-  const uint32_t incl = block_incl_scan256(dt, lds, total);
-  const uint32_t gstart = incl - dt + hist[t * nblocks + blockIdx.x];  // global start of digit t
-#pragma unroll
-  for (int w = 0; w < NW; ++w) wh[w][t] = 0;
-  __syncthreads();
-  const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
+  const int seg = (int)blockIdx.x / a.nblocks, c = (int)blockIdx.x - seg * a.nblocks;
+  const uint32_t n = active_count(a.n_dev, seg, a.n_host);
+  const uint32_t start = (uint32_t)c * (uint32_t)kSortBlockItems;
+  uint32_t base = (uint32_t)seg * a.stride;  // first output position of the segment
+  if (a.packed_out) {
+    base = 0;
+    for (int u = 0; u < seg; ++u) base += a.n_dev[u];  // uniform
+    if (blockIdx.x == 0 && t == 0) {
+      uint32_t kept = 0;
+      const int segs = (int)gridDim.x / a.nblocks;
+      for (int u = 0; u < segs; ++u) kept += a.n_dev[u];
+      *a.packed_out = kept;
+    }
+  }
+  if (start >= n && !(a.ranges && blockIdx.x == 0)) return;  // uniform across the block
+  const uint32_t nb = start < n ? min((uint32_t)kSortBlockItems, n - start) : 0u;
+  // the keys first: their latency overlaps the digit offsets below
+  const size_t in0 = (size_t)seg * a.stride + start;
   uint32_t key[ROUNDS], val[ROUNDS], rank[ROUNDS];
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     const uint32_t li = (uint32_t)(wave * PER_WAVE + r * kWave + lane);
-    const bool valid = li < nb;
-    key[r] = valid ? kin[start + li] : 0u;
-    val[r] = valid ? (vin ? vin[start + li] : start + li) : 0u;
+    const bool in = li < nb;
+    key[r] = in ? a.kin[in0 + li] : 0u;
+    val[r] = in ? (a.vin ? a.vin[in0 + li] : (uint32_t)(in0 + li)) : 0u;
   }
+  for (int k = t; k < NW * BINS / 2; k += NT) reinterpret_cast<uint32_t*>(wh)[k] = 0;
+  // global start of each digit: the digits below it in the whole segment, and its keys in earlier blocks
+  uint32_t gstart[DPT], total;
+  {
+    uint32_t dt[DPT], sum = 0;
+    if constexpr (FOLD) {
+      static_assert(DPT == 1, "one digit per thread");
+      const int rows = min(a.nblocks, (int)((n + (uint32_t)kSortBlockItems - 1) / (uint32_t)kSortBlockItems));
+      const uint32_t* h = a.hist + (size_t)seg * a.nblocks * BINS;
+      // NT / BINS groups of threads take every other (...) row each
+      constexpr int G = NT / BINS;
+      const int d = t % BINS, g = t / BINS;
+      uint32_t pre = 0, all = 0;
+#pragma unroll 8
+      for (int r = g; r < rows; r += G) {
+        const uint32_t x = h[(size_t)r * BINS + d];
+        all += x;
+        pre += r < c ? x : 0u;
+      }
+      if constexpr (G > 1) {  // combined in the key buffer, unused so far
+        s_key[t] = pre;
+        s_val[t] = all;
+        __syncthreads();
+        if (g == 0) {
+#pragma unroll
+          for (int k = 1; k < G; ++k) {
+            pre += s_key[t + k * BINS];
+            all += s_val[t + k * BINS];
+          }
+        } else {
+          pre = all = 0;
+        }
+      }
+      dt[0] = sum = all;
+      gstart[0] = base + pre;
+    } else {
+#pragma unroll
+      for (int j = 0; j < DPT; ++j) {
+        const int d = t * DPT + j;
+        dt[j] = d < BINS ? a.tot[(size_t)seg * BINS + d] : 0u;
+        gstart[j] = base + (d < BINS && nb > 0 ? a.hist[(size_t)blockIdx.x * BINS + d] : 0u);
+        sum += dt[j];
+      }
+    }
+    uint32_t run = block_incl_scan<NT>(sum, lds, total) - sum;
+#pragma unroll
+    for (int j = 0; j < DPT; ++j) {
+      const int d = t * DPT + j;
+      if (a.ranges && blockIdx.x == 0 && d < a.tiles) a.ranges[d] = make_uint2(run, run + dt[j]);
+      gstart[j] += run;
+      run += dt[j];
+    }
+  }
+  const uint32_t out_end = base + total;
+  if (DROP && c == 0 && t == 0) a.live_out[seg] = total;
+  if (nb == 0) return;  // uniform
+  const uint64_t lanes_below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     const uint32_t li = (uint32_t)(wave * PER_WAVE + r * kWave + lane);
-    const bool valid = li < nb;
-    const uint32_t d = (key[r] >> shift) & dmask;
-    uint64_t peers = __builtin_amdgcn_ballot_w64(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      if (b >= dbits) break;  // uniform
-      const bool bit = (d >> b) & 1u;
-      const uint64_t bb = __builtin_amdgcn_ballot_w64(bit);
-      peers &= bit ? bb : ~bb;
-    }
+    const bool valid = li < nb && !(DROP && key[r] == kCulledKey);
+    const uint32_t d = (key[r] >> a.shift) & dmask;
+    const uint64_t peers = digit_peers<BINS == 256 ? 8 : 11>(d, a.dbits, valid);
     const uint32_t wr = __popcll(peers & lanes_below);
     // every lane of a peer group reads the group's running count, then its first lane advances it
     // (one wavefront's LDS operations execute in order)
-    const uint32_t base = wh[wave][d];
+    const uint32_t cnt = wh[wave][d];
     __builtin_amdgcn_wave_barrier();
-    rank[r] = base + wr;
-    if (valid && wr == 0) wh[wave][d] = base + (uint32_t)__popcll(peers);
+    rank[r] = cnt + wr;
+    if (valid && wr == 0) wh[wave][d] = (uint16_t)(cnt + (uint32_t)__popcll(peers));
     __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
   // per digit: block-local start (exclusive prefix over digits of the block totals) plus the
   // wavefront's exclusive prefix, folded into one placement start per (wavefront, digit); and
   // the digit's global-minus-local shift for the write-out (one LDS read per key in each phase)
+  uint32_t placed;
   {
-    uint32_t run = 0;
-    uint32_t c[NW];
+    uint32_t sum = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      c[w] = wh[w][t];
-      run += c[w];
+    for (int j = 0; j < DPT; ++j) {
+      const int d = t * DPT + j;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) sum += d < BINS ? wh[w][d] : 0u;
     }
-    const uint32_t ci = block_incl_scan256(run, lds, total);
-    uint32_t start = ci - run;  // local start of digit t
-    gshift[t] = gstart - start;
+    uint32_t run = block_incl_scan<NT>(sum, lds, placed) - sum;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      wh[w][t] = start;
-      start += c[w];
+    for (int j = 0; j < DPT; ++j) {
+      const int d = t * DPT + j;
+      if (d < BINS) {
+        gshift[d] = gstart[j] - run;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          const uint32_t x = wh[w][d];
+          wh[w][d] = (uint16_t)run;
+          run += x;
+        }
+      }
     }
   }
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     const uint32_t li = (uint32_t)(wave * PER_WAVE + r * kWave + lane);
-    if (li < nb) {
-      const uint32_t d = (key[r] >> shift) & dmask;
+    if (li < nb && !(DROP && key[r] == kCulledKey)) {
+      const uint32_t d = (key[r] >> a.shift) & dmask;
       const uint32_t p = wh[wave][d] + rank[r];
       s_key[p] = key[r];
       s_val[p] = val[r];
@@ -243,15 +359,15 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
   }
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < kSortIpt; ++r) {
-    const uint32_t i = r * kSortThreads + t;
-    if (i < nb) {
+  for (int r = 0; r < kSortBlockItems / NT; ++r) {
+    const uint32_t i = r * NT + t;
+    if (i < placed) {
       const uint32_t k = s_key[i];
-      const uint32_t d = (k >> shift) & dmask;
+      const uint32_t d = (k >> a.shift) & dmask;
       const uint32_t pos = gshift[d] + i;  // unsigned wrap-around: global start + (i - local start)
-      if (pos < n) {  // always true for a consistent histogram; keeps a corrupted one in bounds
-        kout[pos] = k;
-        vout[pos] = s_val[i];
+      if (pos < out_end) {  // always true for a consistent histogram; keeps a corrupted one in bounds
+        a.kout[pos] = k;
+        a.vout[pos] = s_val[i];
       }
     }
   }
@@ -300,54 +416,74 @@ __device__ inline uint32_t coarse_mask(const Rect& r, int ntx16, int cu, int ru)
 constexpr int kMaskShift = 28;
 constexpr uint32_t kTileIdMask = (1u << kMaskShift) - 1u;
 
-// Gathers the items' tile rectangles into depth order (the one random access of binning; the
-// offset and emission passes then read them sequentially), writes each item's pair count in depth
-// order (scnt; 32x32 tiles with coarse binning) and reduces the counts per block.
+// Pairs of an item: its 16x16 (or the plan's) tiles, or the 32x32 tiles with coarse binning.
+__device__ inline uint32_t item_pairs(const Rect& r, int coarse, int ntx16) {
+  if (!coarse) return (uint32_t)r.ncols * (uint32_t)r.nrows;
+  const CoarseRect cr = coarse_rect(r, ntx16);
+  return (uint32_t)(cr.nc * cr.nr);
+}
+
+// Gathers the items' tile rectangles into (view, depth) order (the one random access of binning; the
+// offset and emission passes then read them sequentially), writes each item's pair count in that
+// order (scnt; 32x32 tiles with coarse binning) and reduces the counts per block.  Workgroups go to
+// the eight XCDs in turn, so those of one XCD take one consecutive eighth of the items: the
+// rectangles an XCD gathers are those of few views, which its own L2 holds (4M items of eight views:
+// 77 -> 38 us against a gather in depth order over all views).
 __global__ __launch_bounds__(256) void count_reduce_kernel(const uint32_t* __restrict__ sorted_ids,
-                                                           const Rect* __restrict__ rect, int64_t items, int64_t n,
-                                                           ViewTable vt, int coarse, Rect* __restrict__ srect,
+                                                           const uint32_t* __restrict__ kept,
+                                                           const Rect* __restrict__ rect, int64_t n, ViewTable vt,
+                                                           int coarse, Rect* __restrict__ srect,
                                                            uint32_t* __restrict__ scnt,
                                                            uint32_t* __restrict__ block_sum) {
   __shared__ uint32_t lds[4];
   __shared__ int s_w16[ODGS_MAX_VIEWS];  // 16x16 tiles per row of each view (coarse binning)
+  const uint32_t items = *kept;
+  const uint32_t blocks = (items + (uint32_t)kScanBlockItems - 1) / (uint32_t)kScanBlockItems;
+  const uint32_t per = (blocks + 7) / 8, b = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+  if ((blockIdx.x >> 3) >= per || b >= blocks) return;  // uniform
   if (threadIdx.x < vt.n_views) s_w16[threadIdx.x] = vt.W[threadIdx.x] / 16;
   __syncthreads();
-  const int64_t start = (int64_t)blockIdx.x * kScanBlockItems;
+  const uint32_t start = b * (uint32_t)kScanBlockItems;
   // all loads first (indices clamped into the list), so the four gathers are in flight together
   uint32_t id[kScanIpt];
   Rect r[kScanIpt];
 #pragma unroll
-  for (int k = 0; k < kScanIpt; ++k) {
-    const int64_t j = start + k * 256 + threadIdx.x;  // coalesced
-    id[k] = sorted_ids[j < items ? j : items - 1];
-  }
+  for (int k = 0; k < kScanIpt; ++k) id[k] = sorted_ids[min(start + k * 256 + threadIdx.x, items - 1)];  // coalesced
 #pragma unroll
   for (int k = 0; k < kScanIpt; ++k) r[k] = rect[id[k]];
   uint32_t s = 0;
 #pragma unroll
   for (int k = 0; k < kScanIpt; ++k) {
-    const int64_t j = start + k * 256 + threadIdx.x;
+    const uint32_t j = start + k * 256 + threadIdx.x;
     if (j < items) {
       srect[j] = r[k];
-      uint32_t c = (uint32_t)r[k].ncols * (uint32_t)r[k].nrows;
-      if (coarse) {
-        const CoarseRect cr = coarse_rect(r[k], s_w16[id[k] / (uint32_t)n]);  // item ids are below 2^32
-        c = (uint32_t)(cr.nc * cr.nr);
-      }
+      const uint32_t c = item_pairs(r[k], coarse, coarse ? s_w16[id[k] / (uint32_t)n] : 0);  // ids are below 2^31
       scnt[j] = c;
       s += c;
     }
   }
   uint32_t total;
   block_incl_scan256(s, lds, total);
-  if (threadIdx.x == 0) block_sum[blockIdx.x] = total;
+  if (threadIdx.x == 0) block_sum[b] = total;
+}
+
+// The pair total into the status record of a new pair list (no forward has composited it yet).
+__device__ inline void set_pair_total(uint64_t total, int64_t capacity, odgs_status* __restrict__ status) {
+  const uint32_t gen = status->bin_gen + 1u;
+  status->bin_gen = gen;
+  status->fwd_gen = ~gen;
+  status->n_pairs = (int64_t)total;
+  status->n_pairs_stored = (int32_t)((int64_t)total < capacity ? (int64_t)total : capacity);
+  if ((int64_t)total > capacity) status->flags |= ODGS_STATUS_OVERFLOW;
 }
 
 // Exclusive scan of the block sums (in place, as 64-bit offsets) and the pair total.
 __global__ __launch_bounds__(256) void count_top_kernel(const uint32_t* __restrict__ block_sum,
-                                                        uint64_t* __restrict__ block_off, int nblocks,
-                                                        int64_t capacity, odgs_status* __restrict__ status) {
+                                                        uint64_t* __restrict__ block_off,
+                                                        const uint32_t* __restrict__ kept, int64_t capacity,
+                                                        odgs_status* __restrict__ status) {
   constexpr int IPT = 16;  // consecutive block sums per thread and round
+  const int nblocks = (int)((*kept + (uint32_t)kScanBlockItems - 1) / (uint32_t)kScanBlockItems);
   __shared__ uint64_t wtot[4];
   uint64_t carry = 0;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & (kWave - 1);
@@ -380,25 +516,19 @@ __global__ __launch_bounds__(256) void count_top_kernel(const uint32_t* __restri
     }
     carry += total;
   }
-  if (threadIdx.x == 0) {
-    // a new pair list: no forward has composited it yet
-    const uint32_t gen = status->bin_gen + 1u;
-    status->bin_gen = gen;
-    status->fwd_gen = ~gen;
-    status->n_pairs = (int64_t)carry;
-    const int64_t stored = (int64_t)carry < capacity ? (int64_t)carry : capacity;
-    status->n_pairs_stored = (int32_t)stored;
-    if ((int64_t)carry > capacity) status->flags |= ODGS_STATUS_OVERFLOW;
-  }
+  if (threadIdx.x == 0) set_pair_total(carry, capacity, status);
 }
 
 // First pair position of every depth-sorted item (clamped to the capacity: items starting past
 // it emit nothing).  Pairs of one item are contiguous and items follow depth order, so a later
 // stable sort by tile keeps (depth, index) order inside every tile.
 __global__ __launch_bounds__(256) void item_offsets_kernel(const uint32_t* __restrict__ scnt,
-                                                           const uint64_t* __restrict__ block_off, int64_t items,
-                                                           int64_t capacity, uint32_t* __restrict__ ioff) {
+                                                           const uint64_t* __restrict__ block_off,
+                                                           const uint32_t* __restrict__ kept, int64_t capacity,
+                                                           uint32_t* __restrict__ ioff) {
   __shared__ uint32_t lds[4];
+  const int64_t items = *kept;
+  if ((int64_t)blockIdx.x * kScanBlockItems >= items) return;  // uniform
   const int64_t start = (int64_t)blockIdx.x * kScanBlockItems;
   uint32_t cnt[kScanIpt];
   uint32_t s = 0;
@@ -419,12 +549,171 @@ __global__ __launch_bounds__(256) void item_offsets_kernel(const uint32_t* __res
   }
 }
 
+// Small launches (sort_by_rank) take two kernels instead of the radix sort, the counts and their scans:
+// fifteen launches whose length at such sizes is their start-up and their chains of dependent steps.
+// The first counts, for every item, the items of its view that come before it in (depth, index) order,
+// by comparing it with all of them; the second places the items by that rank.  Measured, all of the
+// binning as a graph: 51 against 86 us at 1,500 Gaussians and a 256x128 view (115 before the scans were
+// folded), 73 against 102 us at 8,000 and 512x256, but 113 against 103 us at 12,000: the line lies at
+// 8,192.  With many views the two meet (40 views of 2,000: 204 and 202 us), at 2^28 comparisons.
+constexpr int kRankThreads = 256;
+constexpr int kRankKeys = 256;  // keys a workgroup compares its items with: a thread's chain of adds sets the length
+constexpr int kPlaceThreads = 1024;
+constexpr int kRankItems = 8192;            // Gaussians, eight per thread of the placing workgroup
+constexpr int64_t kRankPairs = 1ll << 28;  // comparisons over all views
+
+__global__ __launch_bounds__(kRankThreads) void depth_rank_kernel(const uint32_t* __restrict__ dkey, int n,
+                                                                  uint32_t* __restrict__ rank) {
+  __shared__ uint4 s_key[kRankKeys / 4];
+  const int t = threadIdx.x, i0 = (int)blockIdx.x * kRankThreads, j0 = (int)blockIdx.y * kRankKeys, i = i0 + t;
+  const uint32_t* keys = dkey + (int64_t)blockIdx.z * n;
+#pragma unroll
+  for (int k = 0; k < kRankKeys / kRankThreads; ++k) {
+    const int j = j0 + k * kRankThreads + t;
+    reinterpret_cast<uint32_t*>(s_key)[k * kRankThreads + t] = j < n ? keys[j] : kCulledKey;  // (below no limit)
+  }
+  const uint32_t key = i < n ? keys[i] : kCulledKey;
+  __syncthreads();
+  // an equal key comes before if its index does: the limit is one higher for the keys before item i
+  uint32_t c[4] = {0u, 0u, 0u, 0u};
+  if (j0 + kRankKeys <= i0 || j0 >= i0 + kRankThreads) {
+    const uint32_t lim = j0 < i0 ? key + 1u : key;
+#pragma unroll 8
+    for (int k = 0; k < kRankKeys / 4; ++k) {
+      const uint4 x = s_key[k];
+      c[0] += x.x < lim ? 1u : 0u;
+      c[1] += x.y < lim ? 1u : 0u;
+      c[2] += x.z < lim ? 1u : 0u;
+      c[3] += x.w < lim ? 1u : 0u;
+    }
+  } else {
+    const int before = i - j0;
+#pragma unroll 8
+    for (int k = 0; k < kRankKeys / 4; ++k) {
+      const uint4 x = s_key[k];
+      c[0] += x.x < key + (4 * k < before ? 1u : 0u) ? 1u : 0u;
+      c[1] += x.y < key + (4 * k + 1 < before ? 1u : 0u) ? 1u : 0u;
+      c[2] += x.z < key + (4 * k + 2 < before ? 1u : 0u) ? 1u : 0u;
+      c[3] += x.w < key + (4 * k + 3 < before ? 1u : 0u) ? 1u : 0u;
+    }
+  }
+  const uint32_t all = (c[0] + c[1]) + (c[2] + c[3]);
+  if (key != kCulledKey && all != 0) atomicAdd(&rank[(int64_t)blockIdx.z * n + i], all);
+}
+
+// One workgroup per view: its kept items in rank order behind those of the views before it (which it
+// counts by reading their rectangles), with their rectangles and first pair positions.  IPT: items
+// per thread (the smallest of 2, 4, 8 that holds n).  Leaves the ranks cleared.
+template <int IPT>
+__global__ __launch_bounds__(kPlaceThreads) void rank_place_kernel(
+    const uint32_t* __restrict__ dkey, const Rect* __restrict__ rect, int n, ViewTable vt, int coarse, int64_t capacity,
+    uint32_t* __restrict__ rank, uint32_t* __restrict__ sorted_ids, Rect* __restrict__ srect,
+    uint32_t* __restrict__ ioff, uint32_t* __restrict__ kept_out, odgs_status* __restrict__ status) {
+  constexpr int NW = kPlaceThreads / kWave;
+  __shared__ uint32_t s_cnt[IPT * kPlaceThreads];  // pair counts by rank
+  __shared__ uint16_t s_id[IPT * kPlaceThreads];
+  __shared__ uint64_t lds64[NW][3];
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t >> 6, view = (int)blockIdx.x;
+  const int64_t item0 = (int64_t)view * n;
+  const int w16 = vt.W[view] / 16;
+  uint32_t key[IPT], rk[IPT];
+  Rect rc[IPT];
+#pragma unroll
+  for (int r = 0; r < IPT; ++r) {
+    const int64_t i = item0 + min(r * kPlaceThreads + t, n - 1);
+    key[r] = dkey[i];
+    rk[r] = rank[i];
+    rc[r] = rect[i];
+    s_cnt[r * kPlaceThreads + t] = 0;
+    s_id[r * kPlaceThreads + t] = 0;
+  }
+  // kept items and pairs of the views before this one
+  uint64_t v3[3] = {0, 0, 0};  // kept here; kept and pairs before
+  for (int u = 0; u < view; ++u) {
+    const int wu = vt.W[u] / 16;
+#pragma unroll 4
+    for (int k = t; k < n; k += kPlaceThreads) {
+      const uint32_t c = item_pairs(rect[(int64_t)u * n + k], coarse, wu);
+      v3[1] += c != 0 ? 1u : 0u;
+      v3[2] += c;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < IPT; ++r) {
+    const int i = r * kPlaceThreads + t;
+    if (i < n && key[r] != kCulledKey) {
+      ++v3[0];
+      rank[item0 + i] = 0;
+      if (rk[r] < (uint32_t)n) {  // always true for ranks of these keys; keeps others in bounds
+        s_cnt[rk[r]] = item_pairs(rc[r], coarse, w16);
+        s_id[rk[r]] = (uint16_t)i;
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v3[k] += __shfl_xor(v3[k], off);
+    if (lane == 0) lds64[wave][k] = v3[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    v3[k] = 0;
+    for (int w = 0; w < NW; ++w) v3[k] += lds64[w][k];
+  }
+  const int live = (int)v3[0];
+  const int64_t out0 = (int64_t)v3[1];
+  // consecutive positions per thread, and a 64-bit scan of their counts
+  const int ipt = (live + kPlaceThreads - 1) / kPlaceThreads, p0 = t * ipt;
+  uint32_t id[IPT], cnt[IPT];
+  uint64_t mine = 0;
+#pragma unroll
+  for (int k = 0; k < IPT; ++k) {
+    const bool in = k < ipt && p0 + k < live;
+    id[k] = in ? s_id[p0 + k] : 0u;
+    cnt[k] = in ? s_cnt[p0 + k] : 0u;
+    rc[k] = rect[item0 + id[k]];
+    mine += cnt[k];
+  }
+  uint64_t incl = mine;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const uint64_t y = __shfl_up(incl, off);
+    if (lane >= off) incl += y;
+  }
+  __syncthreads();
+  if (lane == kWave - 1) lds64[wave][0] = incl;
+  __syncthreads();
+  uint64_t off = v3[2], all = v3[2];
+  for (int w = 0; w < NW; ++w) {
+    off += w < wave ? lds64[w][0] : 0ull;
+    all += lds64[w][0];
+  }
+  off += incl - mine;
+#pragma unroll
+  for (int k = 0; k < IPT; ++k) {
+    if (k < ipt && p0 + k < live) {
+      const int64_t j = out0 + p0 + k;
+      sorted_ids[j] = (uint32_t)(item0 + id[k]);
+      srect[j] = rc[k];
+      ioff[j] = (uint32_t)(off < (uint64_t)capacity ? off : (uint64_t)capacity);
+    }
+    off += cnt[k];
+  }
+  if (view == (int)gridDim.x - 1 && t == 0) {
+    *kept_out = (uint32_t)(out0 + live);
+    set_pair_total(all, capacity, status);
+  }
+}
+
 // Pair-parallel emission: block b writes the pairs of sort block b, [b * kSortBlockItems,
 // (b + 1) * kSortBlockItems), in rounds of kEmitPairs, four consecutive pairs per thread, so
 // stores are coalesced whatever the items' sizes.  Per round the block locates its items with one
 // search over the item offsets, stages them in LDS, and each thread finds the item of its first
 // pair by a binary search in LDS.  The block also counts the low tile digit of its pairs: the
-// histogram the tile sort's first pass needs (hist[digit * nblocks + b]), so that pass does not
+// histogram the tile sort's first pass needs (hist[b][digit]), so that pass does not
 // read the keys once more to count them.
 constexpr int kEmitRun = 4;  // consecutive pairs per thread
 constexpr int kEmitPairs = 256 * kEmitRun;
@@ -546,32 +835,36 @@ __device__ inline void emit_round(const uint32_t* __restrict__ sorted_ids, const
   }
 }
 
-template <bool COARSE>
+template <bool COARSE, int BINS>
 __global__ __launch_bounds__(256) void emit_pairs_kernel(const uint32_t* __restrict__ sorted_ids,
                                                          const uint32_t* __restrict__ ioff,
                                                          const Rect* __restrict__ srect,
-                                                         const odgs_status* __restrict__ status, int64_t items,
+                                                         const odgs_status* __restrict__ status,
+                                                         const uint32_t* __restrict__ kept,
                                                          int64_t n, ViewTable vt, int tile, uint32_t* __restrict__ pkey,
                                                          uint32_t* __restrict__ pval, uint32_t* __restrict__ hist,
-                                                         int nblocks, uint32_t dmask) {
+                                                         uint32_t dmask) {
   __shared__ uint32_t s_off[kEmitPairs + 1];
   __shared__ uint32_t s_item[kEmitPairs + 1];
   __shared__ Rect s_rect[kEmitPairs + 1];
   __shared__ uint32_t s_tb[kEmitPairs + 1];
   __shared__ uint16_t s_ntx[kEmitPairs + 1];
   __shared__ int64_t s_range[kEmitRounds][2];
-  __shared__ uint32_t h[kSortThreads / kWave][256];  // per-wavefront digit counts
+  // digit counts, per wavefront when there are few digits
+  constexpr int NH = BINS > 256 ? 1 : kSortThreads / kWave;
+  __shared__ uint32_t h[NH][BINS];
   __shared__ uint32_t s_vtb[ODGS_MAX_VIEWS];  // per view: first global tile id (32x32 with coarse binning)
   __shared__ uint16_t s_vntx[ODGS_MAX_VIEWS];  // per view: tiles per row (16x16 with coarse binning)
   const int t = threadIdx.x;
-#pragma unroll
-  for (int w = 0; w < kSortThreads / kWave; ++w) h[w][t] = 0;
+  for (int k = t; k < NH * BINS; k += kSortThreads) (&h[0][0])[k] = 0;
   if (t < vt.n_views) {
     s_vtb[t] = (uint32_t)(COARSE ? vt.tile_base32[t] : vt.tile_base[t]);
     s_vntx[t] = (uint16_t)(vt.W[t] / tile);
   }
   const uint32_t np = (uint32_t)status->n_pairs_stored;
   const uint32_t b0 = blockIdx.x * (uint32_t)kSortBlockItems;
+  if (b0 >= np) return;  // uniform: sort blocks past the pairs are neither scanned nor scattered
+  const int64_t items = *kept;
   {
     // wavefront w finds the items holding the first and last pair of round w (all rounds' searches
     // at once: their dependent loads overlap)
@@ -594,13 +887,15 @@ __global__ __launch_bounds__(256) void emit_pairs_kernel(const uint32_t* __restr
     __syncthreads();  // the searches are done, the previous round's staging has been read
     emit_round<COARSE>(sorted_ids, ioff, srect, items, n, vt, tile, pkey, pval, p0,
                        min(p0 + (uint32_t)kEmitPairs, np), s_off, s_item, s_rect, s_tb, s_ntx, s_range[round],
-                       h[t >> 6], dmask, s_vtb, s_vntx);
+                       h[NH > 1 ? t >> 6 : 0], dmask, s_vtb, s_vntx);
   }
   __syncthreads();
-  uint32_t c = 0;
+  for (int d = t; d < BINS; d += kSortThreads) {
+    uint32_t c = 0;
 #pragma unroll
-  for (int w = 0; w < kSortThreads / kWave; ++w) c += h[w][t];
-  hist[t * nblocks + blockIdx.x] = c;  // every (digit, block) entry, zero past the pairs
+    for (int w = 0; w < NH; ++w) c += h[w][d];
+    hist[(size_t)blockIdx.x * BINS + d] = c;
+  }
 }
 
 // Tile ranges from the sorted keys: each thread scans eight consecutive keys (two 16-byte loads
@@ -917,8 +1212,52 @@ __global__ __launch_bounds__(256) void queue_scatter_kernel(const uint2* __restr
   }
 }
 
+// The same queue of at most kQueueSmallTiles tiles by one workgroup (8,192 tiles: 7 us against 17 for the
+// three launches; at 65,536 one workgroup takes 57 us against 23).
+constexpr int kQueueSmallTiles = 8192;
+
+__global__ __launch_bounds__(kQueueBuckets) void queue_small_kernel(const uint2* __restrict__ ranges, int tiles,
+                                                                    uint32_t* __restrict__ queue, uint32_t split_cap,
+                                                                    uint32_t split_floor,
+                                                                    const uint32_t* __restrict__ n_pairs) {
+  constexpr int TPT = kQueueSmallTiles / kQueueBuckets;
+  __shared__ uint32_t h[kQueueBuckets];
+  __shared__ uint32_t lds[kQueueBuckets / kWave];
+  const int t = threadIdx.x;
+  h[t] = 0;
+  if (t < 4) queue[t] = 0u;
+  uint32_t b[TPT];
+#pragma unroll
+  for (int k = 0; k < TPT; ++k) {
+    const uint2 r = ranges[min(k * kQueueBuckets + t, tiles - 1)];
+    b[k] = cost_bucket(r.y - r.x);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < TPT; ++k)
+    if (k * kQueueBuckets + t < tiles) atomicAdd(&h[b[k]], 1u);
+  __syncthreads();
+  const int bucket = kQueueBuckets - 1 - t;
+  const uint32_t c = h[bucket];
+  uint32_t total;
+  const uint32_t incl = block_incl_scan<kQueueBuckets>(c, lds, total);
+  if (bucket == (int)cost_bucket(max(split_floor, *n_pairs / kSplitShare))) queue[4] = min(incl, split_cap);
+  h[bucket] = incl - c;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < TPT; ++k) {
+    const int i = k * kQueueBuckets + t;
+    if (i < tiles) queue[16 + atomicAdd(&h[b[k]], 1u)] = (uint32_t)i;
+  }
+}
+
 hipError_t launch_tile_queue(const uint2* ranges, int tiles, const uint32_t* n_pairs, uint32_t* bstart,
                              uint32_t* queue, hipStream_t st) {
+  if (tiles <= kQueueSmallTiles) {
+    hipLaunchKernelGGL(queue_small_kernel, dim3(1), dim3(kQueueBuckets), 0, st, ranges, tiles, queue,
+                       (uint32_t)split_tile_cap(tiles), tiles >= kSplitAllTiles ? kSplitLen : 1u, n_pairs);
+    return hipGetLastError();
+  }
   const int nb = (tiles + kQueueTiles - 1) / kQueueTiles;
   if (nb > 0) hipLaunchKernelGGL(queue_count_kernel, dim3(nb), dim3(256), 0, st, ranges, tiles, bstart);
   hipLaunchKernelGGL(queue_scan_kernel, dim3(1), dim3(kQueueBuckets), 0, st, bstart, nb, queue,
@@ -947,36 +1286,69 @@ int sort_digit_bits(int bits) {
   return (bits + passes - 1) / passes;
 }
 
-// first_hist: the first pass's histogram is already in `hist` (written by the producer of the keys).
-hipError_t radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, bool identity_vals,
-                      const uint32_t* n_dev, uint32_t n_host, int bits, int nblocks, uint32_t* hist,
-                      uint32_t* digit_tot, hipStream_t st, bool first_hist = false) {
-  uint32_t* kb[2] = {k0, k1};
-  uint32_t* vb[2] = {v0, v1};
-  int cur = 0;
-  const int dw = sort_digit_bits(bits);
-  for (int shift = 0; shift < bits; shift += dw) {
-    const uint32_t* vin = (shift == 0 && identity_vals) ? nullptr : vb[cur];
-    const int dbits = bits - shift < dw ? bits - shift : dw;
-    if (shift > 0 || !first_hist) {
-      if (shift + dw >= bits)  // the top digit: few distinct values
-        hipLaunchKernelGGL(radix_hist_kernel<true>, dim3(nblocks), dim3(kSortThreads), 0, st, kb[cur], n_dev, n_host,
-                           shift, dbits, hist, nblocks);
-      else
-        hipLaunchKernelGGL(radix_hist_kernel<false>, dim3(nblocks), dim3(kSortThreads), 0, st, kb[cur], n_dev, n_host,
-                           shift, dbits, hist, nblocks);
-    }
-    hipLaunchKernelGGL(radix_digit_scan_kernel, dim3(256), dim3(256), 0, st, hist, nblocks, n_dev, n_host, digit_tot);
-    hipLaunchKernelGGL(radix_scatter_kernel, dim3(nblocks), dim3(kSortThreads), 0, st, kb[cur], vin, kb[cur ^ 1],
-                       vb[cur ^ 1], n_dev, n_host, shift, dbits, hist, digit_tot, nblocks);
-    cur ^= 1;
+// Threads of a scatter's workgroup, and the blocks per segment up to which its blocks sum the digit
+// counts of earlier blocks themselves instead of leaving that to a scan launch.
+constexpr int kScatterThreads = 512;
+constexpr int kFoldBlocks = 32;
+
+template <bool DROP>
+void launch_scatter(const ScatterArgs& a, int segs, hipStream_t st) {
+  const dim3 grid((unsigned)(segs * a.nblocks));
+  if (a.nblocks <= kFoldBlocks)
+    hipLaunchKernelGGL((radix_scatter_kernel<kScatterThreads, 256, DROP, true>), grid, dim3(kScatterThreads), 0, st, a);
+  else
+    hipLaunchKernelGGL((radix_scatter_kernel<kScatterThreads, 256, DROP, false>), grid, dim3(kScatterThreads), 0, st, a);
+}
+
+// (many rows: narrower pieces of them, for more workgroups)
+void launch_scan(const ScatterArgs& a, int segs, int bins, uint32_t* hist, uint32_t* tot, hipStream_t st) {
+  if (a.nblocks > 512)
+    hipLaunchKernelGGL(radix_scan_kernel<8>, dim3((unsigned)bins / 8, (unsigned)segs), dim3(1024), 0, st, hist, a.n_dev,
+                       a.n_host, a.nblocks, bins, tot);
+  else
+    hipLaunchKernelGGL(radix_scan_kernel<32>, dim3((unsigned)bins / 32, (unsigned)segs), dim3(1024), 0, st, hist, a.n_dev,
+                       a.n_host, a.nblocks, bins, tot);
+}
+
+// One digit pass: the histogram unless it is there already, its scan unless the scatter folds it, the
+// scatter.
+template <bool DROP>
+void radix_pass(ScatterArgs a, int segs, bool have_hist, bool top, uint32_t* hist, uint32_t* tot, hipStream_t st) {
+  const dim3 grid((unsigned)(segs * a.nblocks));
+  if (!have_hist) {
+    if (top)  // the top digit: few distinct values
+      hipLaunchKernelGGL((radix_hist_kernel<DROP, true>), grid, dim3(kSortThreads), 0, st, a.kin, a.stride, a.n_dev,
+                         a.n_host, a.nblocks, a.shift, a.dbits, hist);
+    else
+      hipLaunchKernelGGL((radix_hist_kernel<DROP, false>), grid, dim3(kSortThreads), 0, st, a.kin, a.stride, a.n_dev,
+                         a.n_host, a.nblocks, a.shift, a.dbits, hist);
   }
-  return hipGetLastError();
+  if (a.nblocks > kFoldBlocks) launch_scan(a, segs, 256, hist, tot, st);
+  a.hist = hist;
+  a.tot = tot;
+  launch_scatter<DROP>(a, segs, st);
 }
 
 }  // namespace
 
 int sort_passes(int bits) { return (bits + 7) / 8; }
+
+// Pairs of up to 2^kWideBits tiles are sorted by one pass over the whole id, whose digit totals are
+// the tile ranges (1,953 tiles, 200k pairs: 12 + 5 us against 2 x 13 for two scatters, 2 x 4.7 for their
+// scans, 6 for the second histogram and 4 for the ranges); above, the histogram rows (and with more
+// sort blocks their number) outgrow what the second pass costs.
+constexpr int kWideBits = 11;
+constexpr int kWideBlocks = 1024;
+bool sort_wide(int bits, int pair_blocks) { return bits > 8 && bits <= kWideBits && pair_blocks <= kWideBlocks; }
+size_t sort_hist_words(int64_t item_rows, int64_t pair_blocks, bool wide) {
+  return (size_t)std::max<int64_t>(256 * item_rows, (wide ? 1 << kWideBits : 256) * pair_blocks);
+}
+// (the digit totals per view, or of the tile digits; then the kept items per view and in all)
+size_t sort_tot_words(int32_t n_views) { return std::max<size_t>(256 * (size_t)n_views, 1 << kWideBits); }
+
+
+bool sort_by_rank(const odgs_plan* p) { return p->n <= kRankItems && p->items * p->n <= kRankPairs; }
+uint32_t* item_ranks(const odgs_plan* p, void* ws) { return ws_ptr<uint32_t>(ws, p->off_did[p->depth_final ^ 1]); }
 
 hipError_t launch_status_reset(const odgs_plan* p, void* ws, hipStream_t st) {
   hipLaunchKernelGGL(status_reset_kernel, dim3(1), dim3(64), 0, st, ws_ptr<odgs_status>(ws, p->off_status));
@@ -1017,58 +1389,121 @@ hipError_t launch_bin_sort(const odgs_plan* p, void* ws, hipStream_t st) {
   odgs_status* status = ws_ptr<odgs_status>(ws, p->off_status);
   const int64_t items = p->items;
   uint32_t* hist = ws_ptr<uint32_t>(ws, p->off_hist);
-  uint32_t* digit = ws_ptr<uint32_t>(ws, p->off_digit);
+  uint32_t* tot = ws_ptr<uint32_t>(ws, p->off_digit);
+  uint32_t* live = tot + sort_tot_words(p->n_views);  // kept items per view
+  uint32_t* kept = live + ODGS_MAX_VIEWS;             // and in all
   uint2* ranges = ws_ptr<uint2>(ws, p->off_ranges);
-  hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t*>(ranges), 0u, 2 * (int64_t)p->tile_base[p->n_views], st);
-  if (e != hipSuccess) return e;
   const int tiles = p->tile_base[p->n_views];
+  const bool coarse = p->coarse != 0;
+  const int bits = coarse ? p->coarse_bits : p->tile_bits;
+  const bool wide = !coarse && sort_wide(bits, p->pair_blocks);
+  if (!wide || items == 0) {  // (the wide pass writes every tile's range)
+    const hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t*>(ranges), 0u, 2 * (int64_t)tiles, st);
+    if (e != hipSuccess) return e;
+  }
   uint32_t* queue = ws_ptr<uint32_t>(ws, p->off_queue);
   const uint32_t* n_dev = reinterpret_cast<const uint32_t*>(&status->n_pairs_stored);
   if (items == 0) return launch_tile_queue(ranges, tiles, n_dev, hist, queue, st);
-  // 1. items by radial depth (culled items carry the largest key)
   uint32_t* dk[2] = {ws_ptr<uint32_t>(ws, p->off_dkey[0]), ws_ptr<uint32_t>(ws, p->off_dkey[1])};
   uint32_t* di[2] = {ws_ptr<uint32_t>(ws, p->off_did[0]), ws_ptr<uint32_t>(ws, p->off_did[1])};
-  e = radix_sort(dk[0], di[0], dk[1], di[1], true, nullptr, (uint32_t)items, 32, p->item_blocks, hist, digit, st);
-  if (e != hipSuccess) return e;
   const uint32_t* sorted_ids = di[p->depth_final];
-  // 2. pair offsets in depth order, and P
-  const int sblocks = (int)((items + kScanBlockItems - 1) / kScanBlockItems);
-  uint32_t* bsum = ws_ptr<uint32_t>(ws, p->off_blocksum);
-  uint64_t* boff = reinterpret_cast<uint64_t*>(bsum + align_up((size_t)sblocks, 64));
   Rect* srect = ws_ptr<Rect>(ws, p->off_srect);
+  uint32_t* ioff = dk[p->depth_final ^ 1];  // first pair positions (a free buffer by then)
+  const Rect* rect = ws_ptr<Rect>(ws, p->off_rect);
   const ViewTable vt = make_view_table(p);
-  const bool coarse = p->coarse != 0;
-  uint32_t* scnt = di[p->depth_final ^ 1];  // per-item pair counts in depth order (free id buffer)
-  hipLaunchKernelGGL(count_reduce_kernel, dim3(sblocks), dim3(256), 0, st, sorted_ids, ws_ptr<Rect>(ws, p->off_rect),
-                     items, p->n, vt, coarse ? 1 : 0, srect, scnt, bsum);
-  hipLaunchKernelGGL(count_top_kernel, dim3(1), dim3(256), 0, st, bsum, boff, sblocks, p->pair_capacity, status);
-  // 3. emit pairs: per-item offsets (into the free ping-pong buffer), then pair-parallel writes
+  if (sort_by_rank(p)) {
+    // 1., 2. ranks (cleared by the preprocess) and placement
+    uint32_t* rank = item_ranks(p, ws);
+    const int n = (int)p->n;
+    hipLaunchKernelGGL(depth_rank_kernel, dim3((n + kRankThreads - 1) / kRankThreads, (n + kRankKeys - 1) / kRankKeys,
+                                              (unsigned)p->n_views),
+                       dim3(kRankThreads), 0, st, dk[0], n, rank);
+#define ODGS_PLACE(IPT)                                                                                              \
+  hipLaunchKernelGGL(rank_place_kernel<IPT>, dim3((unsigned)p->n_views), dim3(kPlaceThreads), 0, st, dk[0], rect, n,   \
+                     vt, coarse ? 1 : 0, p->pair_capacity, rank, di[p->depth_final], srect, ioff, kept, status)
+    if (n <= 2 * kPlaceThreads)
+      ODGS_PLACE(2);
+    else if (n <= 4 * kPlaceThreads)
+      ODGS_PLACE(4);
+    else
+      ODGS_PLACE(8);
+#undef ODGS_PLACE
+  } else {
+    // 1. each view's items by depth; the first pass drops the culled ones, the last one closes the
+    //    gaps between the views
+    for (int pass = 0; pass < 4; ++pass) {
+      ScatterArgs a{};
+      a.kin = dk[pass & 1];
+      a.vin = pass == 0 ? nullptr : di[pass & 1];
+      a.kout = dk[(pass & 1) ^ 1];
+      a.vout = di[(pass & 1) ^ 1];
+      a.n_dev = pass == 0 ? nullptr : live;
+      a.n_host = (uint32_t)p->n;
+      a.stride = (uint32_t)p->n;
+      a.nblocks = (int)((p->n + kSortBlockItems - 1) / kSortBlockItems);
+      a.shift = 8 * pass;
+      a.dbits = 8;
+      a.live_out = live;
+      a.packed_out = pass == 3 ? kept : nullptr;
+      if (pass == 0)
+        radix_pass<true>(a, p->n_views, false, false, hist, tot, st);
+      else
+        radix_pass<false>(a, p->n_views, false, pass == 3, hist, tot, st);
+    }
+    // 2. pair counts and offsets in (view, depth) order, and P
+    const int sblocks = (int)((items + kScanBlockItems - 1) / kScanBlockItems);
+    uint32_t* bsum = ws_ptr<uint32_t>(ws, p->off_blocksum);
+    uint64_t* boff = reinterpret_cast<uint64_t*>(bsum + align_up((size_t)sblocks, 64));
+    uint32_t* scnt = di[p->depth_final ^ 1];  // per-item pair counts (free id buffer)
+    hipLaunchKernelGGL(count_reduce_kernel, dim3((unsigned)align_up((size_t)sblocks, 8)), dim3(256), 0, st, sorted_ids,
+                       kept, rect, p->n, vt, coarse ? 1 : 0, srect, scnt, bsum);
+    hipLaunchKernelGGL(count_top_kernel, dim3(1), dim3(256), 0, st, bsum, boff, kept, p->pair_capacity, status);
+    hipLaunchKernelGGL(item_offsets_kernel, dim3(sblocks), dim3(256), 0, st, scnt, boff, kept, p->pair_capacity, ioff);
+  }
+  // 3. emit pairs
   uint32_t* pk[2] = {ws_ptr<uint32_t>(ws, p->off_pkey[0]), ws_ptr<uint32_t>(ws, p->off_pkey[1])};
   uint32_t* pv[2] = {ws_ptr<uint32_t>(ws, p->off_pval[0]), ws_ptr<uint32_t>(ws, p->off_pval[1])};
-  uint32_t* ioff = dk[p->depth_final ^ 1];
-  hipLaunchKernelGGL(item_offsets_kernel, dim3(sblocks), dim3(256), 0, st, scnt, boff, items, p->pair_capacity,
-                     ioff);
-  const int bits = coarse ? p->coarse_bits : p->tile_bits;
-  const uint32_t dmask0 = (1u << sort_digit_bits(bits)) - 1u;  // the first tile pass's digit
-  if (p->pair_blocks > 0) {
-    if (coarse)
-      hipLaunchKernelGGL(emit_pairs_kernel<true>, dim3((unsigned)p->pair_blocks), dim3(kSortThreads), 0, st,
-                         sorted_ids, ioff, srect, status, items, p->n, vt, p->s.tile, pk[0], pv[0], hist,
-                         p->pair_blocks, dmask0);
-    else
-      hipLaunchKernelGGL(emit_pairs_kernel<false>, dim3((unsigned)p->pair_blocks), dim3(kSortThreads), 0, st,
-                         sorted_ids, ioff, srect, status, items, p->n, vt, p->s.tile, pk[0], pv[0], hist,
-                         p->pair_blocks, dmask0);
-  }
+  const int dw = wide ? bits : sort_digit_bits(bits);  // the first tile pass's digit
+#define ODGS_EMIT(C, BINS)                                                                                         \
+  hipLaunchKernelGGL((emit_pairs_kernel<C, BINS>), dim3((unsigned)p->pair_blocks), dim3(kSortThreads), 0, st,        \
+                     sorted_ids, ioff, srect, status, kept, p->n, vt, p->s.tile, pk[0], pv[0], hist, (1u << dw) - 1u)
+  if (coarse)
+    ODGS_EMIT(true, 256);
+  else if (wide)
+    ODGS_EMIT(false, 1 << kWideBits);
+  else
+    ODGS_EMIT(false, 256);
+#undef ODGS_EMIT
   // 4. stable sort of the pairs by global tile (the first pass's histogram counted by the emission)
-  e = radix_sort(pk[0], pv[0], pk[1], pv[1], false, n_dev, (uint32_t)p->pair_capacity, bits, p->pair_blocks, hist,
-                 digit, st, true);
-  if (e != hipSuccess) return e;
-  const int sorted = sort_passes(bits) % 2;  // the buffer pair holding the sorted list
+  int sorted = 0;  // the buffer pair holding the sorted list
+  for (int shift = 0; shift < bits; shift += dw, sorted ^= 1) {
+    ScatterArgs a{};
+    a.kin = pk[sorted];
+    a.vin = pv[sorted];
+    a.kout = pk[sorted ^ 1];
+    a.vout = pv[sorted ^ 1];
+    a.n_dev = n_dev;
+    a.n_host = (uint32_t)p->pair_capacity;
+    a.nblocks = p->pair_blocks;
+    a.shift = shift;
+    a.dbits = std::min(dw, bits - shift);
+    if (wide) {
+      launch_scan(a, 1, 1 << kWideBits, hist, tot, st);
+      a.hist = hist;
+      a.tot = tot;
+      a.ranges = ranges;
+      a.tiles = tiles;
+      hipLaunchKernelGGL((radix_scatter_kernel<kScatterThreads, 1 << kWideBits, false, false>),
+                         dim3((unsigned)p->pair_blocks), dim3(kScatterThreads), 0, st, a);
+    } else {
+      radix_pass<false>(a, 1, shift == 0, shift + dw >= bits, hist, tot, st);
+    }
+  }
   if (!coarse) {
     // 5. tile ranges
-    hipLaunchKernelGGL(ranges_kernel, dim3((unsigned)((p->pair_capacity + 256 * kRangeKeys - 1) / (256 * kRangeKeys))),
-                       dim3(256), 0, st, pk[sorted], status, ranges);
+    if (!wide)
+      hipLaunchKernelGGL(ranges_kernel, dim3((unsigned)((p->pair_capacity + 256 * kRangeKeys - 1) / (256 * kRangeKeys))),
+                         dim3(256), 0, st, pk[sorted], status, ranges);
   } else {
     // 5. the 32x32 tiles' list split into the 16x16 tiles' lists and ranges, in the other pair
     //    buffer (scratch: the free radix histograms)
