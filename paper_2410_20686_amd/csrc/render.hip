@@ -487,25 +487,6 @@ struct FwdStage4 {
   uint8_t used[BATCH];
 };
 
-// Flags of a staged entry in the one-wavefront compositors (above the quadrant mask).
-constexpr int kEntryWrap = 1;   // some pixel centre of the tile may need the seam wrap
-constexpr int kEntryClamp = 2;  // opacity above 0.99: alpha may be clamped
-
-// A uniform word the compiler cannot relate to its other uses, so that a test of it stays a scalar
-// test beside its branch.
-__device__ inline int opaque(int x) {
-  asm volatile("" : "+s"(x));
-  return x;
-}
-
-// Lane `lane` (uniform) of `x` takes the uniform word `value`.
-__device__ inline void set_lane(uint32_t& x, uint32_t value, int lane) {
-  asm("s_mov_b32 m0, %2\n\tv_writelane_b32 %0, %1, m0" : "+v"(x) : "s"(value), "s"(lane));
-}
-
-// Keeps a rarely taken uniform branch a branch: the value is not computed on the other path.
-__device__ inline void keep_branch(float& x) { asm volatile("" : "+v"(x)); }
-
 template <int BIN, int BATCH>
 __global__ __launch_bounds__(kWave) void render_fwd4_kernel(
     ViewTable vt, const uint2* __restrict__ ranges, const uint32_t* __restrict__ pair_items, const Rec* __restrict__ rec,

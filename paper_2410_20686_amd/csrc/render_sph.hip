@@ -98,11 +98,11 @@ __device__ inline uint32_t sph_quadrant_mask(const SphCull& cu, const float3* qd
     // (p_c - p0)^T M (p_c - p0) <= (rho + sqrt(lambda_max) r_q)^2 (1e-3 relative slack).
     const float cmax = fmaf(sd, cq, -sqrtf(fmaxf(0.0f, fmaf(-sd, sd, 1.0f))) * sq);  // cos(gamma_max)
     if (hit && cu.c3.z > 0.0f && cmax > 0.05f) {
-      const float inv = 1.0f / sd;
+      const float inv = __builtin_amdgcn_rcpf(sd);
       const float px = fmaf(d.z, cu.c1.y, d.x * cu.c1.x) * inv - cu.c2.y;
       const float py = fmaf(d.z, cu.c2.x, fmaf(d.y, cu.c1.w, d.x * cu.c1.z)) * inv - cu.c2.z;
       const float qv = fmaf(cu.c2.w * px, px, py * fmaf(2.0f * cu.c3.x, px, cu.c3.y * py));
-      const float rr = fmaf(cu.c3.w, qrad / (cmax * cmax), cu.c3.z);
+      const float rr = fmaf(cu.c3.w, qrad * __builtin_amdgcn_rcpf(cmax * cmax), cu.c3.z);
       hit = qv <= rr * rr * 1.001f + 1e-6f;
     }
     m |= hit ? (1u << q) : 0u;
@@ -181,17 +181,29 @@ __device__ inline void sph_stage_batch(SphStage<TILE, BATCH>& S, const uint32_t*
   }
 }
 
-// Float evaluation of one record for ray d: returns the acceptance; power = -qh / D (correctly
-// rounded division); also hands out t1, t2, h, D and qh for the backward.
-__device__ inline bool sph_eval(const float4& a, const float4& b, const float4& c, const float3& d, float& power,
-                                float& t1, float& t2, float& h, float& D, float& qh) {
+// Float evaluation of one record for ray d: whether it reaches the ray; also hands out t1, t2, h, D
+// and qh (the exponent, -qh / D, is formed where it does: sph_power).
+__device__ inline bool sph_eval(const float4& a, const float4& b, const float4& c, const float3& d, float& t1, float& t2,
+                                float& h, float& D, float& qh) {
   t1 = fmaf(a.z, d.z, fmaf(a.y, d.y, a.x * d.x));
   t2 = fmaf(b.y, d.z, fmaf(b.x, d.y, a.w * d.x));
   h = fmaf(c.x, d.z, fmaf(b.w, d.y, b.z * d.x));
   qh = fmaf(t1, t1, t2 * t2);
   D = fmaf(c.y, qh, h * h);
-  power = -__fdiv_rn(qh, D);
   return h > 0.0f && !(fmaf(c.w, D, qh) > 0.0f);
+}
+
+// Exponent -qh / D of a ray that is reached, correctly rounded, and 1 / D (to an ulp): Newton steps on
+// the hardware reciprocal and on the quotient with fused residuals.  The scaling that a general division
+// adds serves quotients near the ends of the float range; here qh <= -p_min D (below 6 D) with D
+// the square of a direction component, and a quotient small enough to lose bits has an exponential of 1.
+__device__ inline float sph_power(float qh, float D, float& inv_D) {
+  float r = __builtin_amdgcn_rcpf(D);
+  r = fmaf(fmaf(-D, r, 1.0f), r, r);
+  float q = qh * r;
+  q = fmaf(fmaf(-D, q, qh), r, q);
+  inv_D = r;
+  return -fmaf(fmaf(-D, q, qh), r, q);
 }
 
 template <int TILE, int BATCH, bool DEPTH>
@@ -256,10 +268,11 @@ __global__ __launch_bounds__(TILE* TILE) void render_sph_fwd_kernel(
         if (__builtin_amdgcn_ballot_w64(done == 0) == 0ull) break;  // uniform: every pixel has finished
         const int k = S.list[wq][i];
         const float4 c = S.s2[k];
-        float power, t1, t2, h, D, qh;
-        const bool hit = sph_eval(S.s0[k], S.s1[k], c, d, power, t1, t2, h, D, qh);
+        float power, inv_D, t1, t2, h, D, qh;
+        const bool hit = sph_eval(S.s0[k], S.s1[k], c, d, t1, t2, h, D, qh);
         const bool ok = done == 0 && hit;
         if (__builtin_amdgcn_ballot_w64(ok) == 0ull) continue;  // uniform
+        power = sph_power(qh, D, inv_D);
         s_used[wq][k] = 1;  // reached here (accepted unless that pixel stops at it: a superset)
         const float alpha = fminf(c.z * __expf(power), kAlphaMax);
         const float Tn = T * (1.0f - alpha);
@@ -299,6 +312,30 @@ __global__ __launch_bounds__(TILE* TILE) void render_sph_fwd_kernel(
 // no partner slot) are summed in place in the first step.  Lane i ends with the row sum of value
 // kSphRowSlot[i % 16] (none where the table says 15: the second copies of values 5, 6, 7).
 constexpr uint64_t kSphRowSlot = 0xFBF9FAC873516240ull;  // nibble i = value index held by row lane i
+
+// The first two steps alone, with bank-masked DPP adds (two per pair of values, one per value without a
+// partner; two instructions lie between every write and the DPP read of it).  They leave four partial
+// sums of each value in the four lanes of one bank of a row: in banks 0 to 3, register 0 holds values
+// 0, 1, 8, 9, register 2 values 2, 3, 10, 11, register 4 values 4, 5, 12, 5 and register 6 values 6, 7, 6, 7.
+// Nibble q of kSphQuad: value q's place, 2 register + bank.
+constexpr uint64_t kSphQuad = 0xA7632DC985410ull;
+
+__device__ inline void quad_reduce13(float (&g)[kNV]) {
+#define ODGS_FOLD(D, S, CTRL, BANKS) "v_add_f32_dpp %" #D ", %" #S ", %" #S " " CTRL " row_mask:0xf bank_mask:" BANKS "\n"
+  asm("s_nop 1\n"
+      ODGS_FOLD(0, 0, "row_mirror", "0xf") ODGS_FOLD(1, 1, "row_mirror", "0xf") ODGS_FOLD(2, 2, "row_mirror", "0xf")
+      ODGS_FOLD(3, 3, "row_mirror", "0xf") ODGS_FOLD(4, 4, "row_mirror", "0xf") ODGS_FOLD(5, 5, "row_mirror", "0xf")
+      ODGS_FOLD(6, 6, "row_mirror", "0xf") ODGS_FOLD(7, 7, "row_mirror", "0xf")
+      ODGS_FOLD(0, 8, "row_mirror", "0xc") ODGS_FOLD(1, 9, "row_mirror", "0xc") ODGS_FOLD(2, 10, "row_mirror", "0xc")
+      ODGS_FOLD(3, 11, "row_mirror", "0xc") ODGS_FOLD(4, 12, "row_mirror", "0xc")
+      ODGS_FOLD(0, 0, "row_half_mirror", "0xf") ODGS_FOLD(2, 2, "row_half_mirror", "0xf")
+      ODGS_FOLD(4, 4, "row_half_mirror", "0xf") ODGS_FOLD(6, 6, "row_half_mirror", "0xf")
+      ODGS_FOLD(0, 1, "row_half_mirror", "0xa") ODGS_FOLD(2, 3, "row_half_mirror", "0xa")
+      ODGS_FOLD(4, 5, "row_half_mirror", "0xa") ODGS_FOLD(6, 7, "row_half_mirror", "0xa")
+      : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]), "+v"(g[4]), "+v"(g[5]), "+v"(g[6]), "+v"(g[7])
+      : "v"(g[8]), "v"(g[9]), "v"(g[10]), "v"(g[11]), "v"(g[12]));
+#undef ODGS_FOLD
+}
 
 __device__ inline float row_reduce13(const float (&g)[kNV], int lane) {
 #pragma clang fp contract(off)  // keeps the in-place sums single DPP adds (not an FMA with the product)
@@ -439,12 +476,13 @@ __global__ __launch_bounds__(TILE* TILE) void render_sph_bwd_kernel(
         const int jrel = end - 1 - k;
         if (jrel >= wmax) continue;  // uniform: behind every contributor of this wavefront
         const float4 a = S.s0[k], b = S.s1[k], c = S.s2[k];
-        float power, t1, t2, h, D, qh;
+        float inv_D, t1, t2, h, D, qh;
         // evaluated on every lane (no short circuit): the gradient terms below are formed on all
         // lanes and zeroed by selects, which needs finite operands
-        const bool hit = sph_eval(a, b, c, d, power, t1, t2, h, D, qh);
+        const bool hit = sph_eval(a, b, c, d, t1, t2, h, D, qh);
         const bool ok = jrel < last && hit;
         if (__builtin_amdgcn_ballot_w64(ok) == 0ull) continue;  // uniform
+        const float power = sph_power(qh, D, inv_D);
         const float G = __expf(power);
         const float araw = c.z * G;
         const bool live = ok && !(araw > kAlphaMax);  // contributes and unclamped
@@ -461,7 +499,7 @@ __global__ __launch_bounds__(TILE* TILE) void render_sph_bwd_kernel(
         const float dpow = dla * alpha;
         // whitened offset y = (h t1, h t2, qh) / D, zero on lanes that do not contribute (D may be
         // 0 there)
-        const float s1 = live ? __builtin_amdgcn_rcpf(D) : 0.0f;
+        const float s1 = live ? inv_D : 0.0f;
         const float y1 = s1 * (h * t1), y2 = s1 * (h * t2), y3 = s1 * qh;
         const float gx = dpow * y1, gy = dpow * y2, gz = dpow * y3;
         const float gv[kNV] = {gx,      gy,      gz,       gx * y1,  gx * y2,  gx * y3, gy * y2,
@@ -497,6 +535,11 @@ __global__ __launch_bounds__(TILE* TILE) void render_sph_bwd_kernel(
 // of a split tile (TileSched); the culling masks handed from the forward to the backward are one
 // byte per list position, in the byte plane of the task's quadrant (plane q at byte offset
 // q * qplane; whole tiles use plane 0).
+//
+// Bound by VALU issue.  Measured at 200k Gaussians, two views of 2048x1024: forward 433 -> 385 us, reverse
+// 530 -> 446 us when the exponent's division moved behind the acceptance test (and lost the scaling that
+// its range does not need, its reciprocal serving the reverse step too), stops and clamps behind branches
+// that are rarely taken, and the reverse sums took the affine compositor's two-stage reduction.
 template <int BATCH, bool DEPTH>
 struct SphFwdStage4 {
   float4 s0[BATCH];
@@ -539,13 +582,12 @@ __global__ __launch_bounds__(kWave) void render_sph_fwd4_kernel(
     __syncthreads();
     const uint2 rg = ranges[g];
     float T[4], C0[4], C1[4], C2[4], Ds[4];
-    int last[4], done[4];
+    int last[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       T[q] = 1.0f;
       C0[q] = C1[q] = C2[q] = Ds[q] = 0.0f;
       last[q] = 0;
-      done[q] = 0;
     }
     uint32_t alive = sel;  // selected quadrants with a pixel still compositing (uniform)
     uint8_t* qm = qmask + (sel == 0xFu ? 0 : (int64_t)__builtin_ctz(sel) * qplane);
@@ -565,48 +607,66 @@ __global__ __launch_bounds__(kWave) void render_sph_fwd4_kernel(
           if constexpr (DEPTH) S.dep[e] = depth[item];
           S.used[e] = 0;
           m = sph_quadrant_mask<4>(cull[item], S.qdir, qrad, sel);
+          if (m != 0u && r.s2.z > kAlphaMax) m |= kEntryClamp << 4;
         }
         const uint64_t bl = __builtin_amdgcn_ballot_w64(m != 0u);
         if (m != 0u) S.list[n + __popcll(bl & below)] = (uint16_t)(e | (m << 8));
         n += __popcll(bl);
       }
       __syncthreads();
-      uint32_t kmn = S.list[0];  // the next entry's list word, read one entry ahead
-      for (int i = 0; i < n; ++i) {
-        const uint32_t km = __builtin_amdgcn_readfirstlane(kmn);
-        kmn = S.list[min(i + 1, n - 1)];
-        const int k = (int)(km & 0xFFu);
-        const uint32_t mq = (km >> 8) & alive;
-        if (mq == 0u) continue;  // uniform
-        const float4 a = S.s0[k], b = S.s1[k], c = S.s2[k];
-        const float4 col = S.s3[k];  // once per entry, not per accepting quadrant
-        uint32_t used = 0;
+      for (int i0 = 0; i0 < n; i0 += kWave) {
+        // the list words of 64 entries, one per lane, and the quadrants used of each
+        const uint32_t words = S.list[min(i0 + lane, n - 1)];
+        uint32_t used_words = 0;
+        const int m = min(kWave, n - i0);
+        for (int i = 0; i < m; ++i) {
+          const uint32_t km = __builtin_amdgcn_readlane(words, i);
+          const int k = (int)(km & 0xFFu);
+          const uint32_t mq = (km >> 8) & (alive | 0xF0u);
+          if ((mq & 0xFu) == 0u) continue;  // uniform
+          const float4 a = S.s0[k], b = S.s1[k], c = S.s2[k];
+          const float4 col = S.s3[k];  // once per entry, not per accepting quadrant
+          uint32_t used = 0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (!((mq >> q) & 1u)) continue;  // uniform
-          float power, t1, t2, h, D, qh;
-          const bool hit = sph_eval(a, b, c, d[q], power, t1, t2, h, D, qh);
-          const bool ok = done[q] == 0 && hit;
-          if (__builtin_amdgcn_ballot_w64(ok) == 0ull) continue;  // uniform
-          used |= 1u << q;  // reached here (accepted unless that pixel stops at it: a superset)
-          const float alpha = fminf(c.z * __expf(power), kAlphaMax);
-          const float Tn = T[q] * (1.0f - alpha);
-          const bool acc = ok && !(Tn < kTStop);
-          done[q] = ok != acc ? 1 : done[q];  // stop: reached, but T would drop below 1e-4
-          const float w = acc ? alpha * T[q] : 0.0f;
-          C0[q] = fmaf(w, col.x, C0[q]);
-          C1[q] = fmaf(w, col.y, C1[q]);
-          C2[q] = fmaf(w, col.z, C2[q]);
-          if constexpr (DEPTH) Ds[q] = Ds[q] + w * S.dep[k];
-          T[q] = acc ? Tn : T[q];
-          last[q] = acc ? (int)(base - rg.x) + k + 1 : last[q];
+          for (int q = 0; q < 4; ++q) {
+            if (!((mq >> q) & 1u)) continue;  // uniform
+            float inv_D, t1, t2, h, D, qh;
+            bool ok = sph_eval(a, b, c, d[q], t1, t2, h, D, qh);  // (false once the pixel has stopped)
+            if (__builtin_amdgcn_ballot_w64(ok) == 0ull) continue;  // uniform
+            used |= 1u << q;  // reached here (accepted unless that pixel stops at it: a superset)
+            // alpha = 0 where the entry does not reach the pixel: T (1 - 0) = T exactly
+            float alpha = ok ? c.z * __expf(sph_power(qh, D, inv_D)) : 0.0f;
+            if (__builtin_expect(opaque((int)(mq & (kEntryClamp << 4))) != 0, 0)) {
+              alpha = fminf(alpha, kAlphaMax);
+              keep_branch(alpha);
+            }
+            float Tn = T[q] * (1.0f - alpha);
+            // a pixel stops at the entry that would take T below 1e-4, without it (once per pixel): its
+            // ray becomes NaN, which no entry reaches
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(Tn < kTStop) != 0ull, 0)) {
+              const bool stop = Tn < kTStop;
+              ok = ok && !stop;
+              alpha = stop ? 0.0f : alpha;
+              Tn = stop ? T[q] : Tn;
+              d[q].x = stop ? __builtin_nanf("") : d[q].x;
+              keep_branch(d[q].x);
+            }
+            const float w = alpha * T[q];
+            C0[q] = fmaf(w, col.x, C0[q]);
+            C1[q] = fmaf(w, col.y, C1[q]);
+            C2[q] = fmaf(w, col.z, C2[q]);
+            if constexpr (DEPTH) Ds[q] = Ds[q] + w * S.dep[k];
+            T[q] = Tn;
+            last[q] = ok ? (int)(base - rg.x) + k + 1 : last[q];
+          }
+          set_lane(used_words, used, i);
         }
-        if (lane == 0 && used) S.used[k] = (uint8_t)used;
+        if (lane < m) S.used[words & 0xFFu] = (uint8_t)used_words;
       }
       // quadrants whose pixels have all stopped, taken once per batch
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        if (((alive >> q) & 1u) && __builtin_amdgcn_ballot_w64(done[q] == 0) == 0ull) alive &= ~(1u << q);
+        if (((alive >> q) & 1u) && __builtin_amdgcn_ballot_w64(d[q].x == d[q].x) == 0ull) alive &= ~(1u << q);
       __syncthreads();
       for (int e = lane; e < cnt; e += kWave) qm[base + e] = S.used[e];
       __syncthreads();
@@ -638,8 +698,15 @@ struct SphBwdStage4 {
   float4 s2[BATCH];
   float4 s3[BATCH];
   uint32_t sid[BATCH];
-  uint16_t list[BATCH];
+  uint16_t list[BATCH];  // entry index | quadrant mask << 8 | flags << 12
 };
+
+// The thirteen sums of an entry are reduced across lanes by two steps (quad_reduce13); the sixteen
+// partial sums that leaves of each value go to LDS, and groups of kSphRing entries are finished at
+// once, one lane per (entry, value), as in the affine reverse compositor.
+constexpr int kSphRing = 4;  // 4 x 13 = 52 lanes
+constexpr int kSphRow = 64;  // per 16-lane row: four registers of 16 words
+constexpr int kSphStride = 4 * kSphRow;
 
 template <int BATCH>
 __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
@@ -649,13 +716,20 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
     float bg1, float bg2, const uint8_t* __restrict__ qmask, int64_t qplane, TileSched sc) {
   constexpr int TILE = 16;
   __shared__ SphBwdStage4<BATCH> S;
-  __shared__ float acc[1][kNV][BATCH + 1];
+  __shared__ __attribute__((aligned(16))) float ring[kSphRing * kSphStride];
+  __shared__ float sums[kSphRing * kNV + 8];  // (a lane reads six from its value's first one on)
   if (forward_is_stale(sc)) return;  // uniform
   const int nsplit = reverse_split(sc);
   __shared__ uint32_t s_claim;
   uint32_t round = 0, sel = 0;
   const int lane = threadIdx.x;
-  const int slot = (int)((kSphRowSlot >> (4 * (lane & 15))) & 0xF);
+  // this lane's words of an entry's ring record; in a flush its entry fe, its value fq, the first of its
+  // value's partials, and the first of the six sums its value is mapped from
+  float* const out = ring + (lane >> 4) * kSphRow + (lane & 15);
+  const int fe = lane / kNV, fq = lane - kNV * fe;
+  const float4* const fin = reinterpret_cast<const float4*>(ring + fe * kSphStride + 4 * (int)((kSphQuad >> (4 * fq)) & 0xF));
+  const float* const fsum = sums + kNV * fe + (fq < 3 ? 0 : (fq < 9 ? 3 : fq));
+  for (int k = lane; k < kSphRing * kNV + 8; k += kWave) sums[k] = 0.0f;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
   for (int g; (g = claim_task(sc, nsplit, round, &s_claim, sel)) >= 0;) {
     const int v = view_of_tile(vt, g);
@@ -711,10 +785,9 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
             S.s0[e] = r.s0;
             S.s1[e] = r.s1;
             S.s2[e] = r.s2;
-            S.s3[e] = r.s3;
+            S.s3[e] = make_float4(r.s3.x, r.s3.y, r.s3.z, 1.0f / r.s2.z);
             S.sid[e] = item;
-#pragma unroll
-            for (int j = 0; j < kNV; ++j) acc[0][j][e] = 0.0f;
+            if (r.s2.z > kAlphaMax) m |= kEntryClamp << 4;
           }
         }
         const uint64_t bl = __builtin_amdgcn_ballot_w64(m != 0u);
@@ -722,75 +795,111 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
         n += __popcll(bl);
       }
       __syncthreads();
-      uint32_t kmn = S.list[0];  // the next entry's list word, read one entry ahead
-      for (int i = 0; i < n; ++i) {
-        const uint32_t km = __builtin_amdgcn_readfirstlane(kmn);
-        kmn = S.list[min(i + 1, n - 1)];
-        const int k = (int)(km & 0xFFu);
-        const int jrel = end - 1 - k;
-        const uint32_t mq = km >> 8;
-        const float4 a = S.s0[k], b = S.s1[k], c = S.s2[k];
-        const float4 col = S.s3[k];
-        float gv[kNV];
+      for (int i0 = 0; i0 < n; i0 += kSphRing) {
+        const int m = min(kSphRing, n - i0);
+        const uint32_t words = S.list[min(i0 + lane, n - 1)];  // the group's list words, one per lane
+        for (int i = 0; i < m; ++i) {
+          const uint32_t km = __builtin_amdgcn_readlane(words, i);
+          const int k = (int)(km & 0xFFu);
+          const int jrel = end - 1 - k;
+          const uint32_t mq = km >> 8;
+          const float4 a = S.s0[k], b = S.s1[k], c = S.s2[k];
+          const float4 col = S.s3[k];
+          float gv[kNV];
 #pragma unroll
-        for (int j = 0; j < kNV; ++j) gv[j] = 0.0f;
-        bool any = false;
+          for (int j = 0; j < kNV; ++j) gv[j] = 0.0f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (!((mq >> q) & 1u) || jrel >= qmax[q]) continue;  // uniform
-          float power, t1, t2, h, D, qh;
-          // evaluated on every lane (no short circuit): the gradient terms below are formed on
-          // all lanes and zeroed by selects, which needs finite operands
-          const bool hit = sph_eval(a, b, c, d[q], power, t1, t2, h, D, qh);
-          const bool ok = jrel < last[q] && hit;
-          if (__builtin_amdgcn_ballot_w64(ok) == 0ull) continue;  // uniform
-          any = true;
-          const float G = __expf(power);
-          const float araw = c.z * G;
-          const bool live = ok && !(araw > kAlphaMax);  // contributes and unclamped
-          // alpha = 0 where the Gaussian does not contribute, so its weight below is 0 without a select
-          const float alpha = ok ? fminf(araw, kAlphaMax) : 0.0f;
-          const float inv_om = __builtin_amdgcn_rcpf(1.0f - alpha);
-          T[q] = T[q] * inv_om;  // transmittance in front of this Gaussian (alpha = 0: times exactly 1)
-          const float wk = alpha * T[q];
-          const float dc = fmaf(dl0[q], col.x, fmaf(dl1[q], col.y, dl2[q] * col.z));  // dL/dC . colour
-          const float dL_da = fmaf(dc, T[q], -DS[q] * inv_om);
-          DS[q] = fmaf(dc, wk, DS[q]);
-          const float dla = live ? dL_da : 0.0f;
-          const float dpow = dla * alpha;
-          // whitened offset y = (h t1, h t2, qh) / D, zero on lanes that do not contribute
-          const float s1 = live ? __builtin_amdgcn_rcpf(D) : 0.0f;
-          const float y1 = s1 * (h * t1), y2 = s1 * (h * t2), y3 = s1 * qh;
-          const float gx = dpow * y1, gy = dpow * y2, gz = dpow * y3;
-          gv[0] += gx;
-          gv[1] += gy;
-          gv[2] += gz;
-          gv[3] = fmaf(gx, y1, gv[3]);
-          gv[4] = fmaf(gx, y2, gv[4]);
-          gv[5] = fmaf(gx, y3, gv[5]);
-          gv[6] = fmaf(gy, y2, gv[6]);
-          gv[7] = fmaf(gy, y3, gv[7]);
-          gv[8] = fmaf(gz, y3, gv[8]);
-          gv[9] = fmaf(dla, G, gv[9]);
-          gv[10] = fmaf(wk, dl0[q], gv[10]);
-          gv[11] = fmaf(wk, dl1[q], gv[11]);
-          gv[12] = fmaf(wk, dl2[q], gv[12]);
+          for (int q = 0; q < 4; ++q) {
+            if (!((mq >> q) & 1u) || jrel >= qmax[q]) continue;  // uniform
+            float inv_D, t1, t2, h, D, qh;
+            // evaluated on every lane (no short circuit): the gradient terms below are formed on
+            // all lanes and are zero where alpha is, which needs finite operands
+            const bool hit = sph_eval(a, b, c, d[q], t1, t2, h, D, qh);
+            const bool ok = jrel < last[q] && hit;
+            if (__builtin_amdgcn_ballot_w64(ok) == 0ull) continue;  // uniform
+            const float araw = c.z * __expf(sph_power(qh, D, inv_D));
+            // alpha = 0 where the Gaussian does not contribute, so its weight below is 0 without a select
+            float alpha = ok ? araw : 0.0f;
+            if (__builtin_expect(opaque((int)(mq & (kEntryClamp << 4))) != 0, 0)) {
+              alpha = fminf(alpha, kAlphaMax);
+              keep_branch(alpha);
+            }
+            const float inv_om = __builtin_amdgcn_rcpf(1.0f - alpha);
+            T[q] = T[q] * inv_om;  // transmittance in front of this Gaussian (alpha = 0: times exactly 1)
+            const float wk = alpha * T[q];
+            const float dc = fmaf(dl0[q], col.x, fmaf(dl1[q], col.y, dl2[q] * col.z));  // dL/dC . colour
+            // dL/dalpha alpha = (dc T - DS / (1 - alpha)) alpha
+            float dpow = fmaf(-DS[q], alpha * inv_om, dc * wk);
+            if (__builtin_expect(opaque((int)(mq & (kEntryClamp << 4))) != 0, 0)) {
+              dpow = araw > kAlphaMax ? 0.0f : dpow;  // a clamped alpha does not depend on the inputs
+              keep_branch(dpow);
+            }
+            DS[q] = fmaf(dc, wk, DS[q]);
+            // whitened offset y = (h t1, h t2, qh) / D, zero on lanes that do not contribute
+            const float s1 = ok ? inv_D : 0.0f, s1h = s1 * h;
+            const float y1 = s1h * t1, y2 = s1h * t2, y3 = s1 * qh;
+            const float gx = dpow * y1, gy = dpow * y2, gz = dpow * y3;
+            gv[0] += gx;
+            gv[1] += gy;
+            gv[2] += gz;
+            gv[3] = fmaf(gx, y1, gv[3]);
+            gv[4] = fmaf(gx, y2, gv[4]);
+            gv[5] = fmaf(gx, y3, gv[5]);
+            gv[6] = fmaf(gy, y2, gv[6]);
+            gv[7] = fmaf(gy, y3, gv[7]);
+            gv[8] = fmaf(gz, y3, gv[8]);
+            gv[9] += dpow;  // the opacity gradient times the opacity
+            gv[10] = fmaf(wk, dl0[q], gv[10]);
+            gv[11] = fmaf(wk, dl1[q], gv[11]);
+            gv[12] = fmaf(wk, dl2[q], gv[12]);
+          }
+          quad_reduce13(gv);
+          out[i * kSphStride] = gv[0];
+          out[i * kSphStride + 16] = gv[2];
+          out[i * kSphStride + 32] = gv[4];
+          out[i * kSphStride + 48] = gv[6];
         }
-        if (!any) continue;  // uniform
-        const float rs = row_reduce13(gv, lane);
-        const float ws = sum_rows(rs);
-        if (lane < 16 && slot < kNV) acc[0][slot][k] = ws;
+        __syncthreads();
+        if (fe < m) {  // (never lanes 52 to 63)
+          float r[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float4 p = fin[k * (kSphRow / 4)];
+            r[k] = (p.x + p.y) + (p.z + p.w);
+          }
+          sums[lane] = (r[0] + r[1]) + (r[2] + r[3]);
+        }
+        __syncthreads();
+        if (fe < m) {
+          const int t = S.list[i0 + fe] & 0xFF;
+          const float4 a = S.s0[t], b = S.s1[t], c = S.s2[t];
+          // record value fq as x^T Y y, Y the symmetric matrix of the six sums from fsum on: a Sigma~
+          // entry (i, j) takes columns i and j of N; a mu^ component i its column and (1, 0, 0),
+          // with (S_y1, S_y2, S_y3) for Y's first row; the others (1, 0, 0) twice
+          const int ci = fq < 3 ? fq : (fq >= 6) + (fq >= 8), cj = fq == 3 ? 0 : (fq == 4 || fq == 6 ? 1 : 2);
+          float x0, x1, x2, y0, y1, y2;
+          sph_ncol(ci, a, b, c, x0, x1, x2);
+          sph_ncol(cj, a, b, c, y0, y1, y2);
+          const bool vec = fq < 3, plain = fq >= 9;
+          x0 = plain ? 1.0f : x0;
+          x1 = plain ? 0.0f : x1;
+          x2 = plain ? 0.0f : x2;
+          y0 = vec || plain ? 1.0f : y0;
+          y1 = vec || plain ? 0.0f : y1;
+          y2 = vec || plain ? 0.0f : y2;
+          float scale = fq == 3 || fq == 6 || fq == 8 || vec ? 2.0f : 4.0f;
+          scale = plain ? 1.0f : scale;
+          scale = fq == 9 ? S.s3[t].w : scale;
+          const double Y0 = fsum[0], Y1 = fsum[1], Y2 = fsum[2], Y3 = fsum[3], Y4 = fsum[4], Y5 = fsum[5];
+          const double e0 = y0, e1 = y1, e2 = y2;
+          const double m0 = fma(Y0, e0, fma(Y1, e1, Y2 * e2));
+          const double m1 = fma(Y1, e0, fma(Y3, e1, Y4 * e2));
+          const double m2 = fma(Y2, e0, fma(Y4, e1, Y5 * e2));
+          const double v = (double)scale * fma((double)x0, m0, fma((double)x1, m1, (double)x2 * m2));
+          if (v != 0.0) unsafeAtomicAdd(&g2d[(int64_t)S.sid[t] * kNV + fq], v);
+        }
+        __syncthreads();
       }
-      __syncthreads();
-      // thirteen consecutive lanes carry one listed entry's values: contiguous 104-byte records
-#pragma unroll 1
-      for (int xx = lane; xx < kNV * n; xx += kWave) {
-        const int i = xx / kNV, q = xx - kNV * i;
-        const int t = S.list[i] & 0xFF;
-        const double s = sph_flush_value(acc, q, t, S.s0[t], S.s1[t], S.s2[t]);
-        if (s != 0.0) unsafeAtomicAdd(&g2d[(int64_t)S.sid[t] * kNV + q], s);
-      }
-      __syncthreads();
     }
   }
 }

@@ -28,6 +28,25 @@ __device__ inline float sum_rows(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Flags of a staged entry in the one-wavefront compositors (above the quadrant mask).
+constexpr int kEntryWrap = 1;   // some pixel centre of the tile may need the seam wrap
+constexpr int kEntryClamp = 2;  // opacity above 0.99: alpha may be clamped
+
+// A uniform word the compiler cannot relate to its other uses, so that a test of it stays a scalar
+// test beside its branch.
+__device__ inline int opaque(int x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+
+// Lane `lane` (uniform) of `x` takes the uniform word `value`.
+__device__ inline void set_lane(uint32_t& x, uint32_t value, int lane) {
+  asm("s_mov_b32 m0, %2\n\tv_writelane_b32 %0, %1, m0" : "+v"(x) : "s"(value), "s"(lane));
+}
+
+// Keeps a rarely taken uniform branch a branch: the value is not computed on the other path.
+__device__ inline void keep_branch(float& x) { asm volatile("" : "+v"(x)); }
+
 // Pixel of a thread inside a TILE x TILE tile: wavefront w owns quadrant w (row-major over the
 // TILE/8 x TILE/8 quadrants), lane l the pixel (l % 8, l / 8) inside it.
 template <int TILE>
