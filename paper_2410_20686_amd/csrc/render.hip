@@ -863,7 +863,10 @@ __global__ __launch_bounds__(TILE* TILE) void render_bwd_kernel(ViewTable vt, co
 // Bound by VALU issue.  Measured at 500k Gaussians, 8 views of 2048x1024: 1,550 us with the sums
 // finished entry by entry, a divergent map per value and every step clamping; 1,402 us with bank-
 // masked folds, a branch-free map and the clamp only for entries that can need it; 1,350 us with the
-// last two steps of the reduction left to the group and the list words read from one register.
+// last two steps of the reduction left to the group and the list words read from one register.  LDS
+// per wavefront counts too: 7,748 bytes took seven of its 1,280-byte granules and held a CU to 18
+// wavefronts where the registers allow 20; with a group's sums over its partials, 7,492 bytes take six:
+// 1,355 -> 1,290 us.
 template <int BATCH>
 struct Stage4 {
   float4 s0[BATCH];  // u, v, l0, l1
@@ -887,7 +890,7 @@ __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
   constexpr int TILE = 16;
   __shared__ Stage4<BATCH> S;
   __shared__ __attribute__((aligned(16))) float ring[kRingEntries * kRingStride];
-  __shared__ float sums[kWave];  // per (entry, value) of a group; the last word stays zero
+  float* const sums = ring;  // per (entry, value) of a group, over its partials; the last word is zero
   if (forward_is_stale(sc)) return;  // uniform
   const int nsplit = reverse_split(sc);
   __shared__ uint32_t s_claim;
@@ -903,7 +906,6 @@ __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
   const int fa = 9 * fe + (fq < 2 ? 0 : (fq < 5 ? 2 : fq));
   const int fb = fq == 1 ? 9 * fe + 1 : (fq == 3 || fq == 4 ? 9 * fe + 3 : kWave - 1);
   const int fc = fq == 4 ? 9 * fe + 4 : kWave - 1;
-  if (lane == kWave - 1) sums[lane] = 0.0f;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
   for (int g; (g = claim_task(sc, nsplit, round, &s_claim, sel)) >= 0;) {
     const int v = view_of_tile(vt, g);
@@ -1002,6 +1004,7 @@ __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
           if ((lane & 12) == 0) out8[i * kRingStride] = gq[8];
         }
         __syncthreads();
+        float total = 0.0f;
         if (fe < m) {  // (never lane 63: fe = 7)
           float r[4];
 #pragma unroll
@@ -1009,8 +1012,10 @@ __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
             const float4 p = fin[k * (kRingRow / 4)];
             r[k] = (p.x + p.y) + (p.z + p.w);
           }
-          sums[lane] = (r[0] + r[1]) + (r[2] + r[3]);
+          total = (r[0] + r[1]) + (r[2] + r[3]);
         }
+        __syncthreads();
+        sums[lane] = total;
         __syncthreads();
         if (fe < m) {
           const int t = S.list[i0 + fe] & 0xFF;
