@@ -284,7 +284,7 @@ def main():
             kname = ("odgs::render_bwd4_kernel<%d, %d>" if st["tile"] >= 16 else "odgs::render_bwd_kernel<%d, %d>") % (
                 st["tile"], rast.plan.s.batch_bwd)
         elif st["tile"] >= 16:
-            kname = "odgs::render_fwd4_kernel<%d, %d>" % (st["tile"], rast.plan.s.batch)
+            kname = "odgs::render_fwd4_kernel<%d, %d, false>" % (st["tile"], rast.plan.s.batch)
         else:
             kname = "odgs::render_fwd_kernel<%d, %d, false, false>" % (st["tile"], rast.plan.s.batch)
         prof = profiled(kname)

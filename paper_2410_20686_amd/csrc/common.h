@@ -90,7 +90,7 @@ struct TileSched {
   const uint32_t* order;  // tile ids by descending list length, or nullptr
   uint32_t* ctr;          // persistent: {next task, finished workgroups}; nullptr: one task each
   odgs_status* status;
-  uint32_t* split;        // {tiles split by binning, tiles split by the last forward}
+  uint32_t* split;        // {long lists by binning, and of those split by the last forward; tiles to split, and split}
   int32_t tiles;
   int32_t split_cap;      // 0: whole tiles only
   int32_t split_all;      // every tile in four parts (split_cap == tiles)
@@ -153,13 +153,13 @@ __device__ inline int claim_tile(const TileSched& s, uint32_t& round, uint32_t* 
 // (within this launch's cap; none without the queue, which names the longest tiles).
 __device__ inline int forward_split(const TileSched& s) {
   if (s.split_all) return s.tiles;
-  return s.split_cap > 0 && s.order ? (int)min(s.split[0], (uint32_t)s.split_cap) : 0;
+  return s.split_cap > 0 && s.order ? (int)min(s.split[2], (uint32_t)s.split_cap) : 0;
 }
 // Split tiles of a reverse launch: every tile with split_all, else those of the forward it follows
 // (which wrote the culling masks of the split tiles' parts separately), within this launch's cap.
 __device__ inline int reverse_split(const TileSched& s) {
   if (s.split_all) return s.tiles;
-  return s.split_cap > 0 && s.order ? (int)min(s.split[1], (uint32_t)s.split_cap) : 0;
+  return s.split_cap > 0 && s.order ? (int)min(s.split[3], (uint32_t)s.split_cap) : 0;
 }
 
 // The forward marks the pair list it composited, and how many tiles it split; the reverse
@@ -167,7 +167,8 @@ __device__ inline int reverse_split(const TileSched& s) {
 __device__ inline void mark_forward(const TileSched& s, int nsplit = 0) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     s.status->fwd_gen = s.status->bin_gen;
-    s.split[1] = (uint32_t)nsplit;
+    s.split[1] = s.split_all ? (uint32_t)nsplit : min(s.split[0], (uint32_t)nsplit);
+    s.split[3] = (uint32_t)nsplit;
   }
 }
 __device__ inline bool forward_is_stale(const TileSched& s) {

@@ -3,7 +3,7 @@
 // Pixels are grouped in 8x8 quadrants.  At tiles of 16 and 32 one 64-wide wavefront composites a
 // 16x16 block, four pixels per lane (lane l holds pixel (l % 8, l / 8) of each quadrant): a whole
 // 16x16 tile, one quadrant of a split tile, or one of the four blocks of a 32x32 tile (the tasks
-// of TileSched).  At tiles of 8, and in the counting and depth variants of the forward, one
+// of TileSched).  At tiles of 8, and in the counting variants of the forward, one
 // workgroup per (view, tile) with one pixel per lane, each wavefront owning one quadrant.  The
 // tile's depth-ordered list is staged through LDS in batches; while the forward stages, each
 // record gets a bit mask of the quadrants its footprint can reach, so a quadrant skips, with a
@@ -481,17 +481,149 @@ __device__ inline void task_block(const ViewTable& vt, int v, int g, uint32_t& s
 template <int BATCH>
 struct FwdStage4 {
   float4 s0[BATCH];  // u, v, l0, l1
-  float4 s1[BATCH];  // l2, p_min, opacity, unused
+  float4 s1[BATCH];  // l2, p_min, opacity, sort depth (with the depth output)
   float4 s2[BATCH];  // r, g, b, unused
   uint16_t list[BATCH];  // entry index | quadrant mask << 8 | flags << 12
   uint8_t used[BATCH];
 };
 
-template <int BIN, int BATCH>
-__global__ __launch_bounds__(kWave) void render_fwd4_kernel(
+using vec4 = float __attribute__((ext_vector_type(4)));  // (kept in registers across a loop)
+
+// One quadrant of a split tile, one pixel per lane.  A split tile's list is long against the launch, so
+// what counts is the time one wavefront takes per entry and not its instructions: kQuadRun entries are
+// evaluated together (their records read, their exponents and alphas formed without waiting on one
+// another), only the products along T stay a chain, and the next batch's records are loaded while the
+// current one is composited.  Each pixel's float operations and their order are those of the
+// one-entry loop.  Run by a whole wavefront; S is its staging.  60k Gaussians on a cube map and two
+// panoramas (0.57M pairs, lists of up to 901): 214 us unsplit, 129 us split with the one-entry loop, 106 us
+// with this (six entries together: 110); 6k on 512x256 (lists of up to 102): 16.4 -> 14.1 us.
+constexpr int kQuadRun = 4;
+
+template <int BATCH, bool DEPTH>
+__device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, const uint32_t* __restrict__ pair_items,
+                                          const Rec* __restrict__ rec, const float* __restrict__ depth, int tx0, int ty0,
+                                          float Wf, float half, uint8_t* __restrict__ qm, float& T_out, float (&C)[3],
+                                          float& D_out, int& last_out) {
+  constexpr int NB = BATCH < kWave ? BATCH : kWave;
+  const int lane = threadIdx.x;
+  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+  const float px = (float)(tx0 + 8 * (q & 1) + (lane & 7)) + 0.5f;
+  const float py = (float)(ty0 + 8 * (q >> 1) + (lane >> 3)) + 0.5f;
+  float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, D = 0.0f, qstop = 0.0f;  // qstop: NaN once stopped
+  int last = 0;
+  if (rg.x < rg.y) {
+    // records one batch ahead, items two (indices clamped into the list)
+    uint32_t item = pair_items[min(rg.x + lane, rg.y - 1)];
+    const vec4* recs = reinterpret_cast<const vec4*>(rec);  // three words per record
+    vec4 r0 = recs[3 * (int64_t)item], r1 = recs[3 * (int64_t)item + 1], r2 = recs[3 * (int64_t)item + 2];
+    float dep = DEPTH ? depth[item] : 0.0f;
+    item = pair_items[min(rg.x + NB + lane, rg.y - 1)];
+    for (uint32_t base = rg.x; base < rg.y; base += NB) {
+      const int cnt = (int)min((uint32_t)NB, rg.y - base);
+      uint32_t m = 0;
+      if (lane < cnt) {
+        S.s0[lane] = make_float4(r0.x, r0.y, r0.z, r0.w);
+        const float reach = fabsf((float)tx0 + 8.0f - r0.x) + 8.0f + 1.0f;
+        S.s1[lane] = make_float4(r1.x, r1.z, r1.y, dep);
+        S.s2[lane] = make_float4(r2.x, r2.y, r2.z, r2.w);
+        S.used[lane] = 0;
+        const Rec r{make_float4(r0.x, r0.y, r0.z, r0.w), make_float4(r1.x, r1.y, r1.z, r1.w),
+                    make_float4(r2.x, r2.y, r2.z, r2.w)};
+        m = quadrant_mask<16>(r, tx0, ty0, Wf, half, 1u << q);
+        if (m != 0u) m |= (reach < half ? 0 : kEntryWrap << 4) | (r1.y > kAlphaMax ? kEntryClamp << 4 : 0);
+      }
+      const uint64_t bl = __builtin_amdgcn_ballot_w64(m != 0u);
+      if (m != 0u) S.list[__popcll(bl & below)] = (uint16_t)(lane | (m << 8));
+      const int n = __popcll(bl);
+      r0 = recs[3 * (int64_t)item];
+      r1 = recs[3 * (int64_t)item + 1];
+      r2 = recs[3 * (int64_t)item + 2];
+      if (DEPTH) dep = depth[item];
+      item = pair_items[min(base + 2 * NB + lane, rg.y - 1)];
+      __syncthreads();
+      const uint32_t words = S.list[min(lane, max(n, 1) - 1)];
+      uint32_t used_words = 0;
+      for (int i0 = 0; i0 < n; i0 += kQuadRun) {
+        float alpha[kQuadRun];
+        int at[kQuadRun];  // the entries' LDS word (uniform)
+        uint32_t flags = 0;
+#pragma unroll
+        for (int j = 0; j < kQuadRun; ++j) {
+          const uint32_t km = __builtin_amdgcn_readlane(words, min(i0 + j, n - 1));
+          flags |= km >> 12;
+          at[j] = (int)(km & 0xFFu);
+        }
+        bool any = false;
+#pragma unroll
+        for (int j = 0; j < kQuadRun; ++j) {
+          const float4 a = S.s0[at[j]], b = S.s1[at[j]];
+          float du = px - a.x;
+          const float dv = py - a.y;
+          if (flags & kEntryWrap) du = wrap_du(du, Wf, half);  // uniform (the identity where it is not needed)
+          const float t1 = fmaf(a.z, du, a.w * dv), t2 = b.x * dv;
+          const float power = -fmaf(t1, t1, fmaf(t2, t2, qstop));
+          const bool ok = power >= b.y && i0 + j < n;  // alpha >= 1/255 (NaN once the pixel has stopped)
+          alpha[j] = ok ? b.z * __expf(power) : 0.0f;
+          any = any || ok;
+        }
+        if (__builtin_amdgcn_ballot_w64(any) == 0ull) continue;  // uniform
+        if (flags & kEntryClamp) {  // uniform
+#pragma unroll
+          for (int j = 0; j < kQuadRun; ++j) alpha[j] = fminf(alpha[j], kAlphaMax);
+        }
+#pragma unroll
+        for (int j = 0; j < kQuadRun; ++j)
+          if (__builtin_amdgcn_ballot_w64(alpha[j] > 0.0f) != 0ull) set_lane(used_words, 1u << q, i0 + j);
+        // T never rises, so a pixel stops within the run only if its last product is below the threshold
+        float Tn = T;
+#pragma unroll
+        for (int j = 0; j < kQuadRun; ++j) Tn = Tn * (1.0f - alpha[j]);
+        if (__builtin_amdgcn_ballot_w64(Tn < kTStop) != 0ull) {
+          // entry by entry: a pixel stops at the entry that would take T below 1e-4, without it
+          float t = T;
+#pragma unroll
+          for (int j = 0; j < kQuadRun; ++j) {
+            qstop = t * (1.0f - alpha[j]) < kTStop ? __builtin_nanf("") : qstop;
+            alpha[j] = qstop == 0.0f ? alpha[j] : 0.0f;
+            t = t * (1.0f - alpha[j]);
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < kQuadRun; ++j) {
+          const float4 c = S.s2[at[j]];
+          const float w = alpha[j] * T;
+          T = T * (1.0f - alpha[j]);
+          C0 = fmaf(w, c.x, C0);
+          C1 = fmaf(w, c.y, C1);
+          C2 = fmaf(w, c.z, C2);
+          if constexpr (DEPTH) D = D + w * S.s1[at[j]].w;
+          last = alpha[j] > 0.0f ? (int)(base - rg.x) + at[j] + 1 : last;
+        }
+      }
+      if (lane < n) S.used[words & 0xFFu] = (uint8_t)used_words;
+      __syncthreads();
+      // the backward's masks for this batch: whether some pixel reached each entry
+      if (lane < cnt) qm[base + lane] = S.used[lane];
+      __syncthreads();
+      if (__builtin_amdgcn_ballot_w64(qstop == 0.0f) == 0ull) break;  // every pixel has stopped
+    }
+  }
+  T_out = T;
+  C[0] = C0;
+  C[1] = C1;
+  C[2] = C2;
+  D_out = D;
+  last_out = last;
+}
+
+// (Seven wavefronts per SIMD, 71 registers: left to itself the compiler takes more with the quadrant path
+// beside the loop: 814 against 778 us at 500k Gaussians, 8 views, many lists split.)
+template <int BIN, int BATCH, bool DEPTH>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(7))) void render_fwd4_kernel(
     ViewTable vt, const uint2* __restrict__ ranges, const uint32_t* __restrict__ pair_items, const Rec* __restrict__ rec,
     float* __restrict__ out_rgb, float* __restrict__ out_T, float* __restrict__ ws_T, int32_t* __restrict__ ws_last,
-    float bg0, float bg1, float bg2, uint8_t* __restrict__ qmask, int64_t qplane, TileSched sc) {
+    float bg0, float bg1, float bg2, const float* __restrict__ depth, float* __restrict__ out_depth,
+    uint8_t* __restrict__ qmask, int64_t qplane, TileSched sc) {
   constexpr int TILE = 16;
   __shared__ FwdStage4<BATCH> S;
   const int nsplit = forward_split(sc);
@@ -510,17 +642,34 @@ __global__ __launch_bounds__(kWave) void render_fwd4_kernel(
     const float py0 = (float)y + 0.5f, py1 = (float)(y + 8) + 0.5f;
     const float Wf = (float)W, half = wrap_half(vt, v);
     const uint2 rg = ranges[g];
-    float T[4], C0[4], C1[4], C2[4], qstop[4];  // qstop: 0 while compositing, NaN once stopped
+    uint8_t* qm = qmask + (int64_t)pl * qplane;
+    if (sel != 0xFu) {  // uniform: a quadrant of a split tile
+      const int q = __builtin_ctz(sel);
+      float Tq, C[3], Dq;
+      int lastq;
+      composite_quadrant<BATCH, DEPTH>(S, q, rg, pair_items, rec, depth, tx0, ty0, Wf, half, qm, Tq, C, Dq, lastq);
+      const int64_t plane = (int64_t)W * H, pix = (int64_t)(y + 8 * (q >> 1)) * W + x + 8 * (q & 1);
+      const int64_t gp = vt.pix_base[v] + pix;
+      float* img = out_rgb + 3 * vt.pix_base[v];
+      img[pix] = fmaf(Tq, bg0, C[0]);
+      img[plane + pix] = fmaf(Tq, bg1, C[1]);
+      img[2 * plane + pix] = fmaf(Tq, bg2, C[2]);
+      ws_T[gp] = Tq;
+      ws_last[gp] = lastq;
+      if constexpr (DEPTH) out_depth[gp] = Dq;
+      if (out_T) out_T[gp] = Tq;
+      continue;
+    }
+    float T[4], C0[4], C1[4], C2[4], D[4], qstop[4];  // qstop: 0 while compositing, NaN once stopped
     int last[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       T[q] = 1.0f;
-      C0[q] = C1[q] = C2[q] = 0.0f;
+      C0[q] = C1[q] = C2[q] = D[q] = 0.0f;
       qstop[q] = 0.0f;
       last[q] = 0;
     }
-    uint32_t alive = sel;  // selected quadrants with a pixel still compositing (uniform)
-    uint8_t* qm = qmask + (int64_t)pl * qplane;
+    uint32_t alive = 0xFu;  // quadrants with a pixel still compositing (uniform)
     for (uint32_t base = rg.x; base < rg.y && alive != 0u; base += BATCH) {
       const int cnt = (int)min((uint32_t)BATCH, rg.y - base);
       int n = 0;
@@ -528,13 +677,14 @@ __global__ __launch_bounds__(kWave) void render_fwd4_kernel(
         const int e = r0 + lane;
         uint32_t m = 0;
         if (e < cnt) {
-          const Rec r = rec[pair_items[base + e]];
+          const uint32_t item = pair_items[base + e];
+          const Rec r = rec[item];
           S.s0[e] = r.r0;
           const float reach = fabsf((float)tx0 + 0.5f * (float)TILE - r.r0.x) + 0.5f * (float)TILE + 1.0f;
-          S.s1[e] = make_float4(r.r1.x, r.r1.z, r.r1.y, 0.0f);
+          S.s1[e] = make_float4(r.r1.x, r.r1.z, r.r1.y, DEPTH ? depth[item] : 0.0f);
           S.s2[e] = r.r2;
           S.used[e] = 0;
-          m = quadrant_mask<TILE>(r, tx0, ty0, Wf, half, sel);
+          m = quadrant_mask<TILE>(r, tx0, ty0, Wf, half);
           if (m != 0u) m |= (reach < half ? 0 : kEntryWrap << 4) | (r.r1.y > kAlphaMax ? kEntryClamp << 4 : 0);
         }
         const uint64_t bl = __builtin_amdgcn_ballot_w64(m != 0u);
@@ -592,6 +742,7 @@ __global__ __launch_bounds__(kWave) void render_fwd4_kernel(
             C0[q] = fmaf(w, c.x, C0[q]);
             C1[q] = fmaf(w, c.y, C1[q]);
             C2[q] = fmaf(w, c.z, C2[q]);
+            if constexpr (DEPTH) D[q] = D[q] + w * b.w;
             T[q] = Tn;
             last[q] = ok ? (int)(base - rg.x) + k + 1 : last[q];
           }
@@ -614,7 +765,6 @@ __global__ __launch_bounds__(kWave) void render_fwd4_kernel(
     // reads them
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      if (!((sel >> q) & 1u)) continue;
       const int64_t pix = (int64_t)(y + 8 * (q >> 1)) * W + x + 8 * (q & 1);
       float* img = out_rgb + 3 * vt.pix_base[v];
       const int64_t plane = (int64_t)W * H;
@@ -624,6 +774,7 @@ __global__ __launch_bounds__(kWave) void render_fwd4_kernel(
       const int64_t gp = vt.pix_base[v] + pix;
       ws_T[gp] = T[q];
       ws_last[gp] = last[q];
+      if constexpr (DEPTH) out_depth[gp] = D[q];
       if (out_T) out_T[gp] = T[q];
     }
   }
@@ -881,8 +1032,171 @@ constexpr int kRingEntries = 7;
 constexpr int kRingRow = 36;  // per 16-lane row: 16 words of g[0], 16 of g[1], 4 of g[8]
 constexpr int kRingStride = 4 * kRingRow;
 
+// This lane's part in a flush: its entry fe of the group, the first of its value's four rows of
+// partials, and, in one word, the byte offsets of the sums its value is mapped from and its value fq.
+struct FlushLane {
+  int fe;
+  uint32_t fw;  // sums fa | fb << 8 | fc << 16 (byte offsets) | fq << 24
+  const float4* fin;
+};
+
+__device__ inline FlushLane flush_lane(const float* ring, int lane) {
+  FlushLane f;
+  const int fe = lane / 9, fq = lane - 9 * fe;
+  const int fa = 9 * fe + (fq < 2 ? 0 : (fq < 5 ? 2 : fq));
+  const int fb = fq == 1 ? 9 * fe + 1 : (fq == 3 || fq == 4 ? 9 * fe + 3 : kWave - 1);
+  const int fc = fq == 4 ? 9 * fe + 4 : kWave - 1;
+  f.fe = fe;
+  f.fw = (uint32_t)(4 * fa | (4 * fb) << 8 | (4 * fc) << 16 | fq << 24);
+  f.fin = reinterpret_cast<const float4*>(ring + fe * kRingStride + (fq < 8 ? 16 * (fq & 1) + 4 * (fq >> 1) : 32));
+  return f;
+}
+
+// Adds the gradients of the group's m entries (list entries i0 on, their partials in the ring) to
+// their records.
+template <int BATCH>
+__device__ inline void flush_group(const Stage4<BATCH>& S, const FlushLane& f, float* ring, int i0, int m,
+                                   double* __restrict__ g2d) {
+  float* const sums = ring;  // per (entry, value), over the partials; the last word is zero
+  float total = 0.0f;
+  __syncthreads();
+  if (f.fe < m) {  // (never lane 63: fe = 7)
+    float r[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float4 p = f.fin[k * (kRingRow / 4)];
+      r[k] = (p.x + p.y) + (p.z + p.w);
+    }
+    total = (r[0] + r[1]) + (r[2] + r[3]);
+  }
+  __syncthreads();
+  sums[threadIdx.x] = total;
+  __syncthreads();
+  if (f.fe < m) {
+    const int fq = (int)(f.fw >> 24), t = S.list[i0 + f.fe] & 0xFF;
+    const float4 a = S.s0[t];
+    const float l0 = a.z, l1 = a.w, l2 = S.s1[t].x;
+    // value fq of the record, from the sums S0 .. S8:
+    //   0: 2 (l0 S0)   1: 2 (l1 S0 + l2 S1)   2: 2 l0 (l0 S2)   3: 4 l0 (l1 S2 + l2 S3)
+    //   4: 2 l1 (l1 S2 + 2 l2 S3) + 2 l2 (l2 S4)   5: S5 / opacity   6, 7, 8: Sq
+    float x = fq == 5 ? S.s2[t].w : 1.0f, u = fq < 2 ? 2.0f : 1.0f;
+    x = fq < 5 ? l1 : x;
+    x = fq == 0 || fq == 2 ? l0 : x;
+    const float y = fq == 4 ? 2.0f * l2 : l2;
+    u = fq == 2 ? 2.0f * l0 : u;
+    u = fq == 3 ? 4.0f * l0 : u;
+    u = fq == 4 ? 2.0f * l1 : u;
+    const double w = (double)l2;
+    auto sum = [&](uint32_t offset) {
+      return (double)*reinterpret_cast<const float*>(reinterpret_cast<const char*>(sums) + offset);
+    };
+    const double d = fma((double)u, fma((double)x, sum(f.fw & 0xFFu), (double)y * sum((f.fw >> 8) & 0xFFu)),
+                         (w + w) * (w * sum((f.fw >> 16) & 0xFFu)));
+    if (d != 0.0) unsafeAtomicAdd(&g2d[(int64_t)S.sid[t] * 9 + fq], d);
+  }
+  __syncthreads();
+}
+
+// One quadrant of a split tile in reverse, one pixel per lane: as in composite_quadrant, a run of
+// kQuadRunBwd entries is evaluated together and only T and DS stay chains; the culling masks, items and
+// records of the next batches are loaded ahead.  The cases of composite_quadrant: 306 us unsplit, 186 us with
+// the one-entry loop, 145 us with this (three entries together: 148), and 23.4 -> 19.2 us.
+constexpr int kQuadRunBwd = 2;
+
+template <int BATCH>
+__device__ inline void reverse_quadrant(Stage4<BATCH>& S, float* ring, const FlushLane& fl, BwdPixel P,
+                                        float px, float py, uint2 rg, int wmax, const uint32_t* __restrict__ pair_items,
+                                        const Rec* __restrict__ rec, const uint8_t* __restrict__ qm, float tcx, float Wf,
+                                        float half, double* __restrict__ g2d) {
+  constexpr int NB = BATCH < kWave ? BATCH : kWave;
+  const int lane = threadIdx.x;
+  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+  if (wmax <= 0) return;  // uniform
+  // entry e of the batch that ends at `end` is list position end - 1 - e (clamped into the list's start)
+  float* const out01 = ring + (lane >> 4) * kRingRow + (lane & 15);
+  float* const out8 = ring + (lane >> 4) * kRingRow + 32 + (lane & 3);
+  uint32_t pos = rg.x + max(wmax - 1 - lane, 0);
+  uint32_t mask = qm[pos], item = pair_items[pos];
+  const vec4* recs = reinterpret_cast<const vec4*>(rec);  // three words per record
+  vec4 r0 = recs[3 * (int64_t)item], r1 = recs[3 * (int64_t)item + 1], r2 = recs[3 * (int64_t)item + 2];
+  pos = rg.x + max(wmax - NB - 1 - lane, 0);
+  uint32_t mask1 = qm[pos], item1 = pair_items[pos];
+  for (int end = wmax; end > 0; end -= NB) {
+    const int cnt = min(NB, end);
+    uint32_t w = 0;
+    if (lane < cnt && mask != 0u) {  // records only of the entries the forward's pixels reached
+      S.s0[lane] = make_float4(r0.x, r0.y, r0.z, r0.w);
+      const float reach = fabsf(tcx - r0.x) + 9.0f;
+      S.s1[lane] = make_float4(r1.x, r1.z, r1.y, 0.0f);
+      S.sid[lane] = item;
+      S.s2[lane] = make_float4(r2.x, r2.y, r2.z, 1.0f / r1.y);
+      w = 1u | (reach < half ? 0 : kEntryWrap << 4) | (r1.y > kAlphaMax ? kEntryClamp << 4 : 0);
+    }
+    const uint64_t bl = __builtin_amdgcn_ballot_w64(w != 0u);
+    if (w != 0u) S.list[__popcll(bl & below)] = (uint16_t)(lane | (w << 8));
+    const int n = __popcll(bl);
+    mask = mask1;
+    item = item1;
+    // (of the entries not reached too: an unconditional load is issued ahead)
+    r0 = recs[3 * (int64_t)item];
+    r1 = recs[3 * (int64_t)item + 1];
+    r2 = recs[3 * (int64_t)item + 2];
+    pos = rg.x + max(end - 2 * NB - 1 - lane, 0);
+    mask1 = qm[pos];
+    item1 = pair_items[pos];
+    __syncthreads();
+    for (int i0 = 0; i0 < n; i0 += kRingEntries) {
+      const int m = min(kRingEntries, n - i0);
+      const uint32_t words = S.list[min(i0 + lane, n - 1)];  // the group's list words, one per lane
+      for (int i = 0; i < m; i += kQuadRunBwd) {
+        float4 a[kQuadRunBwd], b[kQuadRunBwd], c[kQuadRunBwd];
+        float du[kQuadRunBwd], gq[kQuadRunBwd][9];
+        int k[kQuadRunBwd];
+        uint32_t flags = 0;
+#pragma unroll
+        for (int j = 0; j < kQuadRunBwd; ++j) {
+          const uint32_t km = __builtin_amdgcn_readlane(words, min(i + j, m - 1));
+          flags |= km >> 12;
+          k[j] = (int)(km & 0xFFu);
+          a[j] = S.s0[k[j]];
+          b[j] = S.s1[k[j]];
+          c[j] = S.s2[k[j]];
+        }
+#pragma unroll
+        for (int j = 0; j < kQuadRunBwd; ++j) du[j] = px - a[j].x;
+        if (flags & kEntryWrap) {  // uniform
+#pragma unroll
+          for (int j = 0; j < kQuadRunBwd; ++j) du[j] = wrap_du(du[j], Wf, half);
+        }
+        bool ok[kQuadRunBwd];
+        float p[kQuadRunBwd], t1[kQuadRunBwd], t2[kQuadRunBwd];
+#pragma unroll
+        for (int j = 0; j < kQuadRunBwd; ++j) {
+          const float dv = py - a[j].y;
+          t1[j] = fmaf(a[j].z, du[j], a[j].w * dv);
+          t2[j] = b[j].x * dv;
+          p[j] = -fmaf(t1[j], t1[j], t2[j] * t2[j]);
+          ok[j] = end - 1 - k[j] < P.last && !(p[j] < b[j].y) && i + j < m;
+        }
+#pragma unroll
+        for (int j = 0; j < kQuadRunBwd; ++j)
+          bwd_pixel_step<false>(P, ok[j], (int)(flags & kEntryClamp), p[j], t1[j], t2[j], b[j], c[j], gq[j]);
+#pragma unroll
+        for (int j = 0; j < kQuadRunBwd; ++j) {
+          if (j > 0 && i + j >= m) break;  // uniform (past an odd group)
+          quad_reduce9(gq[j]);
+          out01[(i + j) * kRingStride] = gq[j][0];
+          out01[(i + j) * kRingStride + 16] = gq[j][1];
+          if ((lane & 12) == 0) out8[(i + j) * kRingStride] = gq[j][8];
+        }
+      }
+      flush_group<BATCH>(S, fl, ring, i0, m, g2d);
+    }
+  }
+}
+
 template <int BIN, int BATCH>
-__global__ __launch_bounds__(kWave) void render_bwd4_kernel(
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5))) void render_bwd4_kernel(
     ViewTable vt, const uint2* __restrict__ ranges, const uint32_t* __restrict__ pair_items, const Rec* __restrict__ rec,
     const float* __restrict__ ws_T, const int32_t* __restrict__ ws_last, const float* __restrict__ dL_drgb,
     double* __restrict__ g2d, int64_t items, float bg0, float bg1, float bg2, const uint8_t* __restrict__ qmask,
@@ -890,22 +1204,15 @@ __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
   constexpr int TILE = 16;
   __shared__ Stage4<BATCH> S;
   __shared__ __attribute__((aligned(16))) float ring[kRingEntries * kRingStride];
-  float* const sums = ring;  // per (entry, value) of a group, over its partials; the last word is zero
   if (forward_is_stale(sc)) return;  // uniform
   const int nsplit = reverse_split(sc);
   __shared__ uint32_t s_claim;
   uint32_t round = 0, sel = 0;
   const int lane = threadIdx.x;
-  // this lane's words of an entry's ring record, and in a flush its entry fe, its value fq, the first
-  // of its value's four rows of partials and the words of the sums its value is mapped from
+  // this lane's words of an entry's ring record
   float* const out01 = ring + (lane >> 4) * kRingRow + (lane & 15);
   float* const out8 = ring + (lane >> 4) * kRingRow + 32 + (lane & 3);
-  const int fe = lane / 9, fq = lane - 9 * fe;
-  const float4* const fin = reinterpret_cast<const float4*>(
-      ring + fe * kRingStride + (fq < 8 ? 16 * (fq & 1) + 4 * (fq >> 1) : 32));
-  const int fa = 9 * fe + (fq < 2 ? 0 : (fq < 5 ? 2 : fq));
-  const int fb = fq == 1 ? 9 * fe + 1 : (fq == 3 || fq == 4 ? 9 * fe + 3 : kWave - 1);
-  const int fc = fq == 4 ? 9 * fe + 4 : kWave - 1;
+  const FlushLane fl = flush_lane(ring, lane);
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
   for (int g; (g = claim_task(sc, nsplit, round, &s_claim, sel)) >= 0;) {
     const int v = view_of_tile(vt, g);
@@ -919,26 +1226,37 @@ __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
     const uint2 rg = ranges[g];
     const int64_t plane = (int64_t)W * H;
     const float* dimg = dL_drgb + 3 * vt.pix_base[v];
+    const uint8_t* qm = qmask + (int64_t)pl * qplane;
+    auto load_pixel = [&](int q) {
+      BwdPixel p;
+      const int64_t pix = (int64_t)(y + 8 * (q >> 1)) * W + x + 8 * (q & 1);
+      const int64_t gp = vt.pix_base[v] + pix;
+      p.dl0 = dimg[pix], p.dl1 = dimg[plane + pix], p.dl2 = dimg[2 * plane + pix];
+      p.T = ws_T[gp];
+      p.last = ws_last[gp];
+      p.DS = p.T * fmaf(p.dl0, bg0, fmaf(p.dl1, bg1, p.dl2 * bg2));
+      return p;
+    };
+    auto wave_max = [](int x) {  // the same in every lane
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) x = max(x, __shfl_xor(x, off));
+      return __builtin_amdgcn_readfirstlane(x);
+    };
+    if (sel != 0xFu) {  // uniform: a quadrant of a split tile
+      const int q = __builtin_ctz(sel);
+      const BwdPixel p = load_pixel(q);
+      reverse_quadrant<BATCH>(S, ring, fl, p, q & 1 ? px1 : px0, q >> 1 ? py1 : py0, rg, wave_max(p.last), pair_items, rec,
+                              qm, (float)tx0 + 8.0f, Wf, half, g2d);
+      continue;
+    }
     BwdPixel P[4];  // quadrant q = 2 * qy + qx
     int wmax = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      if (!((sel >> q) & 1u)) {
-        P[q].last = 0;  // not this task's: never reached, its other members never read
-        continue;
-      }
-      const int64_t pix = (int64_t)(y + 8 * (q >> 1)) * W + x + 8 * (q & 1);
-      const int64_t gp = vt.pix_base[v] + pix;
-      P[q].dl0 = dimg[pix], P[q].dl1 = dimg[plane + pix], P[q].dl2 = dimg[2 * plane + pix];
-      P[q].T = ws_T[gp];
-      P[q].last = ws_last[gp];
-      P[q].DS = P[q].T * fmaf(P[q].dl0, bg0, fmaf(P[q].dl1, bg1, P[q].dl2 * bg2));
+      P[q] = load_pixel(q);
       wmax = max(wmax, P[q].last);
     }
-    const uint8_t* qm = qmask + (int64_t)pl * qplane;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) wmax = max(wmax, __shfl_xor(wmax, off));
-    wmax = __builtin_amdgcn_readfirstlane(wmax);
+    wmax = wave_max(wmax);
     for (int end = wmax; end > 0; end -= BATCH) {
       const int cnt = min(BATCH, end);
       // stage entries end - 1 - e (back to front) with their quadrant masks; list those reaching
@@ -949,7 +1267,7 @@ __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
         uint32_t m = 0;
         if (e < cnt) {
           const uint32_t pos = rg.x + end - 1 - e;
-          m = qm[pos] & sel;
+          m = qm[pos];
           if (m != 0u) {  // records only of the entries the forward's pixels reached
             const uint32_t item = pair_items[pos];
             const Rec r = rec[item];
@@ -957,8 +1275,8 @@ __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
             const float reach = fabsf((float)tx0 + 0.5f * (float)TILE - r.r0.x) + 0.5f * (float)TILE + 1.0f;
             m |= (reach < half ? 0 : kEntryWrap << 4) | (r.r1.y > kAlphaMax ? kEntryClamp << 4 : 0);
             S.s1[e] = make_float4(r.r1.x, r.r1.z, r.r1.y, 0.0f);
-            S.s2[e] = make_float4(r.r2.x, r.r2.y, r.r2.z, 1.0f / r.r1.y);
             S.sid[e] = item;
+            S.s2[e] = make_float4(r.r2.x, r.r2.y, r.r2.z, 1.0f / r.r1.y);
           }
         }
         const uint64_t bl = __builtin_amdgcn_ballot_w64(m != 0u);
@@ -1003,40 +1321,7 @@ __global__ __launch_bounds__(kWave) void render_bwd4_kernel(
           out01[i * kRingStride + 16] = gq[1];
           if ((lane & 12) == 0) out8[i * kRingStride] = gq[8];
         }
-        __syncthreads();
-        float total = 0.0f;
-        if (fe < m) {  // (never lane 63: fe = 7)
-          float r[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const float4 p = fin[k * (kRingRow / 4)];
-            r[k] = (p.x + p.y) + (p.z + p.w);
-          }
-          total = (r[0] + r[1]) + (r[2] + r[3]);
-        }
-        __syncthreads();
-        sums[lane] = total;
-        __syncthreads();
-        if (fe < m) {
-          const int t = S.list[i0 + fe] & 0xFF;
-          const float4 a = S.s0[t];
-          const float l0 = a.z, l1 = a.w, l2 = S.s1[t].x;
-          // value fq of the record, from the sums S0 .. S8:
-          //   0: 2 (l0 S0)   1: 2 (l1 S0 + l2 S1)   2: 2 l0 (l0 S2)   3: 4 l0 (l1 S2 + l2 S3)
-          //   4: 2 l1 (l1 S2 + 2 l2 S3) + 2 l2 (l2 S4)   5: S5 / opacity   6, 7, 8: Sq
-          float x = fq == 5 ? S.s2[t].w : 1.0f, u = fq < 2 ? 2.0f : 1.0f;
-          x = fq < 5 ? l1 : x;
-          x = fq == 0 || fq == 2 ? l0 : x;
-          const float y = fq == 4 ? 2.0f * l2 : l2;
-          u = fq == 2 ? 2.0f * l0 : u;
-          u = fq == 3 ? 4.0f * l0 : u;
-          u = fq == 4 ? 2.0f * l1 : u;
-          const double w = (double)l2;
-          const double d = fma((double)u, fma((double)x, (double)sums[fa], (double)y * (double)sums[fb]),
-                               (w + w) * (w * (double)sums[fc]));
-          if (d != 0.0) unsafeAtomicAdd(&g2d[(int64_t)S.sid[t] * 9 + fq], d);
-        }
-        __syncthreads();
+        flush_group<BATCH>(S, fl, ring, i0, m, g2d);
       }
     }
   }
@@ -1136,21 +1421,27 @@ struct FwdRun {
   launch_sched(render_fwd_kernel<TILE, BATCH, C, D>, sc, TILE * TILE, st, vt, ranges, items, rec, out_rgb, out_T, wT, \
                wl, wn, we, wle, p->s.bg[0], p->s.bg[1], p->s.bg[2], depth, out_depth, qmask,                         \
                (int64_t)p->pair_capacity)
-    // the counting and depth variants keep one pixel per lane (counters per 8x8 quadrant)
+#define ODGS_FWD4(BIN, SCHED, D)                                                                                     \
+  launch_sched(render_fwd4_kernel<BIN, BATCH, D>, SCHED, kWave, st, vt, ranges, items, rec, out_rgb, out_T, wT, wl,     \
+               p->s.bg[0], p->s.bg[1], p->s.bg[2], depth, out_depth, qmask, (int64_t)p->pair_capacity)
+    // the counting variants keep one pixel per lane (counters per 8x8 quadrant)
     if (count && out_depth)
       ODGS_FWD1(true, true);
     else if (count)
       ODGS_FWD1(true, false);
-    else if (out_depth)
-      ODGS_FWD1(false, true);
-    else if constexpr (TILE == 16)
-      launch_sched(render_fwd4_kernel<16, BATCH>, with_split(sc), kWave, st, vt, ranges, items, rec, out_rgb, out_T,
-                   wT, wl, p->s.bg[0], p->s.bg[1], p->s.bg[2], qmask, (int64_t)p->pair_capacity);
-    else if constexpr (TILE == 32)
-      launch_sched(render_fwd4_kernel<32, BATCH>, with_parts(sc), kWave, st, vt, ranges, items, rec, out_rgb, out_T,
-                   wT, wl, p->s.bg[0], p->s.bg[1], p->s.bg[2], qmask, (int64_t)p->pair_capacity);
-    else
-      ODGS_FWD1(false, false);
+    else if constexpr (TILE == 8) {
+      if (out_depth)
+        ODGS_FWD1(false, true);
+      else
+        ODGS_FWD1(false, false);
+    } else {
+      const TileSched sc4 = TILE == 16 ? with_split(sc) : with_parts(sc);
+      if (out_depth)
+        ODGS_FWD4(TILE, sc4, true);
+      else
+        ODGS_FWD4(TILE, sc4, false);
+    }
+#undef ODGS_FWD4
 #undef ODGS_FWD1
   }
 };

@@ -1137,13 +1137,27 @@ __global__ __launch_bounds__(kSortThreads) void refine_write_kernel(
 // that turns them into per-(block, bucket) starts, and the scatter.
 constexpr int kQueueBuckets = 1024;
 constexpr int kQueueTiles = 4096;  // tiles per block of the count and scatter kernels (16 per thread)
-// A list is split into quadrant tasks (for compositors that take them) when one wavefront alone
-// would take long against the whole launch: when it holds at least 1 / kSplitShare of all pairs
-// and, with kSplitAllTiles tiles or more, at least kSplitLen pairs (with fewer tiles than that the
-// device has wavefront slots to spare, and every list is split).  At most split_tile_cap(tiles)
-// lists are split: an eighth of the tiles, or kSplitCapMin.
-constexpr uint32_t kSplitLen = 1024;
+// A list is split into quadrant tasks (for compositors that take them) when one wavefront alone would
+// take long against the whole launch: when it holds at least 1 / kSplitShare of all pairs, or is one of
+// the kSplitTop longest and holds half as much and kLongLen pairs; and at least kSplitLen pairs (with fewer
+// than kSplitAllTiles tiles the device has wavefront slots to spare, and no list is too short).  At most split_tile_cap(tiles)
+// lists are split.  Word 4 of the queue's header counts the long lists, those of 1 / kLongShare of all pairs
+// and, from kSplitAllTiles tiles on, kLongLen pairs; word 6 the lists to split.
+//
+// An unsplit list of L pairs takes about 0.23 us L forward, a launch of P pairs at least 28 us P / 10^6, so
+// a list sets the launch's length from L = P / 8200 on; a split list costs about half as much again in
+// staging and culling, which is free only while wavefront slots are.  Forward / reverse us with lists
+// split from 1 / 2730, 1 / 4096, 1 / 8192, 1 / 16384 of the pairs: 60k on a cube map and panoramas
+// (0.57M pairs) 105 / 142, 107 / 145, 107 / 144, 107 / 147 (unsplit 214 / 306); 300k, 2048x1024, 1.8M
+// pairs, forward 193, 175, 175, 175 (unsplit 219); 500k, 4096x2048, 8.4M pairs 261 / 463, 258 / 462,
+// 276 / 513, 294 / 574; 500k, 8 views, 25.8M pairs 735 / 1293, 740 / 1306, 744 / 1316, 776 / 1376; 300k,
+// mixed sizes, 20.8M pairs 957 / 1314, 928 / 1308, 778 / 1356.  The last one's few lists between the two
+// shares are what kSplitTop is for: 772 / 1352, and 500k on 4096x2048 stays at 260 / 469.
+constexpr uint32_t kSplitLen = 64;
 constexpr uint32_t kSplitShare = 4096;
+constexpr uint32_t kSplitTop = 128;
+constexpr uint32_t kLongLen = 1024;
+constexpr uint32_t kLongShare = 4096;
 constexpr int kSplitAllTiles = 4096;
 constexpr int kSplitCapMin = 1024;
 
@@ -1169,14 +1183,26 @@ __global__ __launch_bounds__(256) void queue_count_kernel(const uint2* __restric
   for (int b = threadIdx.x; b < kQueueBuckets; b += 256) bstart[(size_t)blockIdx.x * kQueueBuckets + b] = h[b];
 }
 
+// Header words 4 and 6 from the scan over buckets, whose threads each name their bucket and the number
+// of tiles in it or above.  Contains a barrier; cut: two words of LDS.
+__device__ inline void set_split(int bucket, uint32_t upto, uint32_t cap, bool split_all, uint32_t pairs, uint32_t* cut,
+                                 uint32_t* __restrict__ header) {
+  const uint32_t floor = split_all ? 1u : kSplitLen;
+  if (bucket == (int)cost_bucket(max(split_all ? 1u : kLongLen, pairs / kLongShare))) header[4] = min(upto, cap);
+  if (bucket == (int)cost_bucket(max(floor, pairs / kSplitShare))) cut[0] = upto;
+  if (bucket == (int)cost_bucket(max(kLongLen, pairs / (2 * kSplitShare)))) cut[1] = min(upto, kSplitTop);
+  __syncthreads();
+  if (threadIdx.x == 0) header[6] = min(max(cut[0], cut[1]), cap);
+}
+
 // Buckets in descending order, blocks in order: the counts become each (block, bucket)'s first
 // queue position.  One workgroup; also clears the persistent launches' counters and records the
-// number of tiles to split (those with lists of kSplitLen or more, at most split_cap).
+// numbers of long lists and of lists to split (set_split).
 __global__ __launch_bounds__(kQueueBuckets) void queue_scan_kernel(uint32_t* __restrict__ bstart, int nblocks,
                                                                    uint32_t* __restrict__ ctr, uint32_t split_cap,
-                                                                   uint32_t split_floor,
+                                                                   bool split_all,
                                                                    const uint32_t* __restrict__ n_pairs) {
-  __shared__ uint32_t wsum[kQueueBuckets / kWave];
+  __shared__ uint32_t wsum[kQueueBuckets / kWave], cut[2];
   const int t = threadIdx.x, lane = t & (kWave - 1), w = t >> 6;
   const int bucket = kQueueBuckets - 1 - t;
   if (t < 4) ctr[t] = 0u;
@@ -1188,7 +1214,7 @@ __global__ __launch_bounds__(kQueueBuckets) void queue_scan_kernel(uint32_t* __r
   uint32_t run = incl - c;
   for (int k = 0; k < w; ++k) run += wsum[k];
   // tiles in this bucket or above: the first run + c queue entries
-  if (bucket == (int)cost_bucket(max(split_floor, *n_pairs / kSplitShare))) ctr[4] = min(run + c, split_cap);
+  set_split(bucket, run + c, split_cap, split_all, *n_pairs, cut, ctr);
   for (int b = 0; b < nblocks; ++b) {
     uint32_t* e = bstart + (size_t)b * kQueueBuckets + bucket;
     const uint32_t x = *e;
@@ -1218,11 +1244,11 @@ constexpr int kQueueSmallTiles = 8192;
 
 __global__ __launch_bounds__(kQueueBuckets) void queue_small_kernel(const uint2* __restrict__ ranges, int tiles,
                                                                     uint32_t* __restrict__ queue, uint32_t split_cap,
-                                                                    uint32_t split_floor,
+                                                                    bool split_all,
                                                                     const uint32_t* __restrict__ n_pairs) {
   constexpr int TPT = kQueueSmallTiles / kQueueBuckets;
   __shared__ uint32_t h[kQueueBuckets];
-  __shared__ uint32_t lds[kQueueBuckets / kWave];
+  __shared__ uint32_t lds[kQueueBuckets / kWave], cut[2];
   const int t = threadIdx.x;
   h[t] = 0;
   if (t < 4) queue[t] = 0u;
@@ -1241,7 +1267,7 @@ __global__ __launch_bounds__(kQueueBuckets) void queue_small_kernel(const uint2*
   const uint32_t c = h[bucket];
   uint32_t total;
   const uint32_t incl = block_incl_scan<kQueueBuckets>(c, lds, total);
-  if (bucket == (int)cost_bucket(max(split_floor, *n_pairs / kSplitShare))) queue[4] = min(incl, split_cap);
+  set_split(bucket, incl, split_cap, split_all, *n_pairs, cut, queue);
   h[bucket] = incl - c;
   __syncthreads();
 #pragma unroll
@@ -1255,13 +1281,13 @@ hipError_t launch_tile_queue(const uint2* ranges, int tiles, const uint32_t* n_p
                              uint32_t* queue, hipStream_t st) {
   if (tiles <= kQueueSmallTiles) {
     hipLaunchKernelGGL(queue_small_kernel, dim3(1), dim3(kQueueBuckets), 0, st, ranges, tiles, queue,
-                       (uint32_t)split_tile_cap(tiles), tiles >= kSplitAllTiles ? kSplitLen : 1u, n_pairs);
+                       (uint32_t)split_tile_cap(tiles), tiles < kSplitAllTiles, n_pairs);
     return hipGetLastError();
   }
   const int nb = (tiles + kQueueTiles - 1) / kQueueTiles;
   if (nb > 0) hipLaunchKernelGGL(queue_count_kernel, dim3(nb), dim3(256), 0, st, ranges, tiles, bstart);
   hipLaunchKernelGGL(queue_scan_kernel, dim3(1), dim3(kQueueBuckets), 0, st, bstart, nb, queue,
-                     (uint32_t)split_tile_cap(tiles), tiles >= kSplitAllTiles ? kSplitLen : 1u, n_pairs);
+                     (uint32_t)split_tile_cap(tiles), tiles < kSplitAllTiles, n_pairs);
   if (nb > 0) hipLaunchKernelGGL(queue_scatter_kernel, dim3(nb), dim3(256), 0, st, ranges, tiles, bstart, queue + 16);
   return hipGetLastError();
 }

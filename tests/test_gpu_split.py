@@ -1,0 +1,87 @@
+"""Lists split into quadrant tasks at tiles of 16x16: which lists the queue splits, and the quadrant
+compositors at list lengths around the entries they take together (4 forward, 2 reverse), their
+groups of seven and their batches of 64.  Whole-tile compositing in tile id order is the reference:
+images and depths bit-identical; the compositor's 2D gradients, whose per-(entry, tile) float sums run
+over other pixels, to the parity tolerance."""
+import numpy as np
+import pytest
+
+from paper_2410_20686_amd import scenes
+from tests import _gpu as G
+from tests._util import settings
+
+pytestmark = pytest.mark.gpu
+
+
+def _bucket(x):
+    x = np.asarray(x, dtype=np.int64)
+    b = 1 + ((x.astype(np.float32).view(np.uint32).astype(np.int64) - 0x3F800000) >> 18)
+    return np.where(x == 0, 0, b)
+
+
+def _expected_split(lengths):
+    """Lists of at least 1/4096 of all pairs, or the 128 longest of at least half that and 1024 pairs,
+    and of at least 64 pairs from 4096 tiles on; at most max(1024, tiles / 8)."""
+    tiles, pairs = len(lengths), int(lengths.sum())
+    b = _bucket(lengths)
+    floor = 64 if tiles >= 4096 else 1
+    long = int((b >= _bucket(max(floor, pairs // 4096))).sum())
+    top = min(int((b >= _bucket(max(1024, pairs // 8192))).sum()), 128)
+    return min(max(long, top), tiles if tiles < 1024 else max(1024, tiles // 8))
+
+
+def _run(sc, cams, st, dL):
+    import torch
+    res = G.run_gpu(sc, cams, st, dL=dL, return_rast=True, split_bwd=True)
+    rast = res["rast"]
+    p = rast.plan
+    tiles = int(p.tile_base[cams.n_views])
+    r = rast.ws[p.off_ranges:p.off_ranges + 8 * tiles].view(torch.int32).cpu().numpy().reshape(tiles, 2)
+    res["lengths"] = (r[:, 1] - r[:, 0]).astype(np.int64)
+    res["header"] = rast.ws[p.off_queue:p.off_queue + 64].view(torch.int32).cpu().numpy()
+    depth = torch.empty(rast.pixels, dtype=torch.float32, device="cuda")
+    rgb, _ = rast.render_fwd(out_depth=depth)
+    np.testing.assert_array_equal(rgb.cpu().numpy(), res["rgb"])
+    res["depth"] = depth.cpu().numpy()
+    return res
+
+
+def _check(sc, cams, st, schedules=("queue",)):
+    dL = scenes.upstream_gradient(cams, seed=7)
+    base = _run(sc, cams, dict(st, schedule="tile_id"), dL)
+    assert base["header"][7] == 0
+    for s in schedules:
+        res = _run(sc, cams, dict(st, schedule=s), dL)
+        split = _expected_split(res["lengths"])
+        assert res["header"][6] == split and res["header"][7] == split
+        for k in ("rgb", "T", "depth"):
+            np.testing.assert_array_equal(res[k], base[k])
+        G.assert_grads_close(res, base, names=("g2d",))
+    return split, base["lengths"]
+
+
+@pytest.mark.parametrize("opacity", [0.02, 0.999])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7, 8, 9, 63, 64, 65, 129, 258])
+def test_quadrant_list_lengths(n, opacity):
+    """A stack of n footprints across the image's left and right border; nearly opaque ones reach the
+    alpha clamp and stop pixels inside a run."""
+    sc = scenes.sphere_scene(n, 1, seed=n)
+    dist = np.linspace(1.0, 3.0, n)
+    sc.means[:] = np.stack([0.02 * dist, 0.1 * dist, -dist])
+    sc.scales[:] = (0.15 * dist)[None]
+    sc.opacities[:] = np.float32(opacity)
+    split, lengths = _check(sc, scenes.identity_cameras(64, 32), settings(tile=16))
+    assert split > 0 and lengths.max() == n
+
+
+@pytest.mark.parametrize("n,scale,crowd,top", [(3000, 0.6, 0.03, False), (6000, 10.0, 0.6, True)])
+def test_split_rule(n, scale, crowd, top):
+    """8,192 tiles: few pairs (the lists of 64 and more are split), and 4 million of them and more
+    (lists below 1/4096 of the pairs are split up to the 128th)."""
+    sc = scenes.sphere_scene(n, 0, seed=5)
+    sc.means[:, : n // 4] = sc.means[:, :1] + np.float32(crowd) * sc.means[:, : n // 4]  # one direction
+    sc.scales *= np.float32(scale)
+    sc.opacities *= np.float32(0.05)
+    split, lengths = _check(sc, scenes.identity_cameras(2048, 1024), settings(tile=16), ("queue", "persistent"))
+    assert 0 < split < len(lengths)
+    assert (split == 128) == top
