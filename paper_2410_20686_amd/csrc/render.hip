@@ -158,9 +158,8 @@ __device__ inline float rect_min_quadratic(float a, float b, float c, float nba,
 // (rounding of products and of du, dv) and the rounding of this test, so no contributing pixel
 // is ever skipped.  Quadrants whose horizontal span reaches the +-W/2 wrap point keep the
 // rectangle test only.
-// Only the quadrants in `sel` (uniform) are tested; the others read as not reached.
 template <int TILE>
-__device__ inline uint32_t quadrant_mask(const Rec& r, int tx0, int ty0, float Wf, float half, uint32_t sel = ~0u) {
+__device__ inline uint32_t quadrant_mask(const Rec& r, int tx0, int ty0, float Wf, float half) {
   constexpr int QPR = TILE / 8;
   const float u = r.r0.x, v = r.r0.y, eu = r.r1.w, ev = r.r2.w;
   // inverse covariance [[a, b], [b, c]] = 2 L^T L of the stored factor
@@ -188,7 +187,6 @@ __device__ inline uint32_t quadrant_mask(const Rec& r, int tx0, int ty0, float W
   uint32_t mask = 0;
 #pragma unroll
   for (int q = 0; q < QPR * QPR; ++q) {
-    if (!((sel >> q) & 1u)) continue;
     const float dx = du[q % QPR], dv = dy[q / QPR];
     const bool rect = fabsf(dv) <= ev + 3.5f && (all_cols || fabsf(dx) <= eu + 3.5f);
     const bool near = !(fabsf(dx) + 4.0f < half) ||
@@ -479,24 +477,42 @@ __device__ inline void task_block(const ViewTable& vt, int v, int g, uint32_t& s
 }
 
 template <int BATCH>
-struct FwdStage4 {
-  float4 s0[BATCH];  // u, v, l0, l1
-  float4 s1[BATCH];  // l2, p_min, opacity, sort depth (with the depth output)
-  float4 s2[BATCH];  // r, g, b, unused
+struct FwdStage4 {  // (one entry more for composite_quadrant)
+  float4 s0[BATCH + 1];  // u, v, l0, l1
+  float4 s1[BATCH + 1];  // l2, p_min, opacity, sort depth (with the depth output)
+  float4 s2[BATCH + 1];  // r, g, b, unused
   uint16_t list[BATCH];  // entry index | quadrant mask << 8 | flags << 12
   uint8_t used[BATCH];
 };
 
 using vec4 = float __attribute__((ext_vector_type(4)));  // (kept in registers across a loop)
 
+// `x`, the same in every lane, in a scalar register; and the number of `mask`'s bits below this lane.
+__device__ inline float uniform(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
+__device__ inline int bits_below(uint64_t mask) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// Bit j if `mask` has a bit, in a scalar register.
+__device__ inline int bit_if(uint64_t mask, int j) {
+  int x;
+  asm("s_cmp_lg_u64 %1, 0\n\ts_cselect_b32 %0, %2, 0" : "=s"(x) : "s"(mask), "s"(1 << j) : "scc");
+  return x;
+}
+
+__device__ inline vec4 as_vec4(const float4& f) { return vec4{f.x, f.y, f.z, f.w}; }
+
 // One quadrant of a split tile, one pixel per lane.  A split tile's list is long against the launch, so
-// what counts is the time one wavefront takes per entry and not its instructions: kQuadRun entries are
-// evaluated together (their records read, their exponents and alphas formed without waiting on one
-// another), only the products along T stay a chain, and the next batch's records are loaded while the
-// current one is composited.  Each pixel's float operations and their order are those of the
-// one-entry loop.  Run by a whole wavefront; S is its staging.  60k Gaussians on a cube map and two
-// panoramas (0.57M pairs, lists of up to 901): 214 us unsplit, 129 us split with the one-entry loop, 106 us
-// with this (six entries together: 110); 6k on 512x256 (lists of up to 102): 16.4 -> 14.1 us.
+// what counts is the time one wavefront takes per entry: it issues an instruction every four to five
+// cycles whatever the rest of the device does.  kQuadRun entries are evaluated together: their records
+// are read from LDS at once (the asm statements keep the compiler from waiting for each in turn), the
+// stop test is one per run, wrap and clamp are one branch per run, the entries reached are bits of a
+// scalar, and past the list's end the run reads an entry that nothing reaches, so it needs no bounds.
+// The next batch's records are loaded while the current one is composited.  Each pixel's float operations
+// and their order are those of the one-entry loop.  Run by a whole wavefront; S is its staging.
+// 60k Gaussians on a cube map and two panoramas (0.57M pairs, lists of up to 901): 214 us unsplit, 129 us
+// split with the one-entry loop, 106 us with runs whose reads the compiler had put one behind another, 80 us
+// with this; 6k on 512x256 (lists of up to 102) 16.4 us with the one-entry loop, 11.6 us with this.
 constexpr int kQuadRun = 4;
 
 template <int BATCH, bool DEPTH>
@@ -506,11 +522,12 @@ __device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, 
                                           float& D_out, int& last_out) {
   constexpr int NB = BATCH < kWave ? BATCH : kWave;
   const int lane = threadIdx.x;
-  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
   const float px = (float)(tx0 + 8 * (q & 1) + (lane & 7)) + 0.5f;
   const float py = (float)(ty0 + 8 * (q >> 1) + (lane >> 3)) + 0.5f;
   float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, D = 0.0f, qstop = 0.0f;  // qstop: NaN once stopped
   int last = 0;
+  if (lane == 0)  // the entry nothing reaches
+    S.s0[NB] = make_float4(0, 0, 0, 0), S.s1[NB] = make_float4(0, __builtin_inff(), 0, 0), S.s2[NB] = S.s0[NB];
   if (rg.x < rg.y) {
     // records one batch ahead, items two (indices clamped into the list)
     uint32_t item = pair_items[min(rg.x + lane, rg.y - 1)];
@@ -529,11 +546,11 @@ __device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, 
         S.used[lane] = 0;
         const Rec r{make_float4(r0.x, r0.y, r0.z, r0.w), make_float4(r1.x, r1.y, r1.z, r1.w),
                     make_float4(r2.x, r2.y, r2.z, r2.w)};
-        m = quadrant_mask<16>(r, tx0, ty0, Wf, half, 1u << q);
+        m = quadrant_mask<8>(r, tx0 + 8 * (q & 1), ty0 + 8 * (q >> 1), Wf, half);
         if (m != 0u) m |= (reach < half ? 0 : kEntryWrap << 4) | (r1.y > kAlphaMax ? kEntryClamp << 4 : 0);
       }
       const uint64_t bl = __builtin_amdgcn_ballot_w64(m != 0u);
-      if (m != 0u) S.list[__popcll(bl & below)] = (uint16_t)(lane | (m << 8));
+      if (m != 0u) S.list[bits_below(bl)] = (uint16_t)(lane | (m << 8));
       const int n = __popcll(bl);
       r0 = recs[3 * (int64_t)item];
       r1 = recs[3 * (int64_t)item + 1];
@@ -541,66 +558,89 @@ __device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, 
       if (DEPTH) dep = depth[item];
       item = pair_items[min(base + 2 * NB + lane, rg.y - 1)];
       __syncthreads();
-      const uint32_t words = S.list[min(lane, max(n, 1) - 1)];
-      uint32_t used_words = 0;
+      const uint32_t words = lane < n ? S.list[lane] : NB;  // past the end: the entry nothing reaches
+      uint64_t used = 0;
       for (int i0 = 0; i0 < n; i0 += kQuadRun) {
-        float alpha[kQuadRun];
+        float a[kQuadRun][4], b[kQuadRun][3];
         int at[kQuadRun];  // the entries' LDS word (uniform)
         uint32_t flags = 0;
 #pragma unroll
         for (int j = 0; j < kQuadRun; ++j) {
-          const uint32_t km = __builtin_amdgcn_readlane(words, min(i0 + j, n - 1));
-          flags |= km >> 12;
+          const uint32_t km = __builtin_amdgcn_readlane(words, i0 + j);
+          flags |= km;
           at[j] = (int)(km & 0xFFu);
+          const float4 s0 = S.s0[at[j]], s1 = S.s1[at[j]];
+          a[j][0] = s0.x, a[j][1] = s0.y, a[j][2] = s0.z, a[j][3] = s0.w;
+          b[j][0] = s1.x, b[j][1] = s1.y, b[j][2] = s1.z;
         }
-        bool any = false;
+        // every read is issued before the first is waited for
+        static_assert(kQuadRun == 4, "the operands of the next lines");
+        asm volatile("" : "+v"(b[0][0]), "+v"(b[1][0]), "+v"(b[2][0]), "+v"(b[3][0]), "+v"(a[3][0]), "+v"(a[2][0]), "+v"(a[1][0]), "+v"(a[0][0]));
+        float du[kQuadRun], alpha[kQuadRun], t[kQuadRun + 1];
+        bool ok[kQuadRun];
+        int hit = 0;
 #pragma unroll
-        for (int j = 0; j < kQuadRun; ++j) {
-          const float4 a = S.s0[at[j]], b = S.s1[at[j]];
-          float du = px - a.x;
-          const float dv = py - a.y;
-          if (flags & kEntryWrap) du = wrap_du(du, Wf, half);  // uniform (the identity where it is not needed)
-          const float t1 = fmaf(a.z, du, a.w * dv), t2 = b.x * dv;
-          const float power = -fmaf(t1, t1, fmaf(t2, t2, qstop));
-          const bool ok = power >= b.y && i0 + j < n;  // alpha >= 1/255 (NaN once the pixel has stopped)
-          alpha[j] = ok ? b.z * __expf(power) : 0.0f;
-          any = any || ok;
-        }
-        if (__builtin_amdgcn_ballot_w64(any) == 0ull) continue;  // uniform
-        if (flags & kEntryClamp) {  // uniform
-#pragma unroll
-          for (int j = 0; j < kQuadRun; ++j) alpha[j] = fminf(alpha[j], kAlphaMax);
-        }
-#pragma unroll
-        for (int j = 0; j < kQuadRun; ++j)
-          if (__builtin_amdgcn_ballot_w64(alpha[j] > 0.0f) != 0ull) set_lane(used_words, 1u << q, i0 + j);
-        // T never rises, so a pixel stops within the run only if its last product is below the threshold
-        float Tn = T;
-#pragma unroll
-        for (int j = 0; j < kQuadRun; ++j) Tn = Tn * (1.0f - alpha[j]);
-        if (__builtin_amdgcn_ballot_w64(Tn < kTStop) != 0ull) {
-          // entry by entry: a pixel stops at the entry that would take T below 1e-4, without it
-          float t = T;
+        for (int j = 0; j < kQuadRun; ++j) du[j] = px - a[j][0];
+        if (__builtin_expect(opaque((int)(flags >> 12 & kEntryWrap)), 0)) {  // uniform
 #pragma unroll
           for (int j = 0; j < kQuadRun; ++j) {
-            qstop = t * (1.0f - alpha[j]) < kTStop ? __builtin_nanf("") : qstop;
-            alpha[j] = qstop == 0.0f ? alpha[j] : 0.0f;
-            t = t * (1.0f - alpha[j]);
+            du[j] = wrap_du(du[j], Wf, half);  // (the identity where it is not needed)
+            keep_branch(du[j]);
           }
         }
 #pragma unroll
         for (int j = 0; j < kQuadRun; ++j) {
-          const float4 c = S.s2[at[j]];
-          const float w = alpha[j] * T;
-          T = T * (1.0f - alpha[j]);
-          C0 = fmaf(w, c.x, C0);
-          C1 = fmaf(w, c.y, C1);
-          C2 = fmaf(w, c.z, C2);
-          if constexpr (DEPTH) D = D + w * S.s1[at[j]].w;
-          last = alpha[j] > 0.0f ? (int)(base - rg.x) + at[j] + 1 : last;
+          const float dv = py - a[j][1];
+          const float t1 = fmaf(a[j][2], du[j], a[j][3] * dv), t2 = b[j][0] * dv;
+          const float power = -fmaf(t1, t1, fmaf(t2, t2, qstop));
+          ok[j] = power >= b[j][1];  // alpha >= 1/255 (NaN once the pixel has stopped)
+          alpha[j] = ok[j] ? b[j][2] * __expf(power) : 0.0f;
+          hit |= bit_if(__builtin_amdgcn_ballot_w64(ok[j]), j);
+        }
+        if (hit == 0) continue;  // uniform
+        used |= (uint64_t)(uint32_t)hit << i0;
+        if (__builtin_expect(opaque((int)(flags >> 12 & kEntryClamp)), 0)) {  // uniform
+#pragma unroll
+          for (int j = 0; j < kQuadRun; ++j) {
+            alpha[j] = fminf(alpha[j], kAlphaMax);
+            keep_branch(alpha[j]);
+          }
+        }
+        t[0] = T;
+#pragma unroll
+        for (int j = 0; j < kQuadRun; ++j) t[j + 1] = t[j] * (1.0f - alpha[j]);
+        // T never rises, so a pixel stops within the run only if its last product is below the threshold
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(t[kQuadRun] < kTStop) != 0ull, 0)) {
+          // entry by entry: a pixel stops at the entry that would take T below 1e-4, without it
+#pragma unroll
+          for (int j = 0; j < kQuadRun; ++j) {
+            qstop = t[j] * (1.0f - alpha[j]) < kTStop ? __builtin_nanf("") : qstop;
+            ok[j] = ok[j] && qstop == 0.0f;
+            alpha[j] = ok[j] ? alpha[j] : 0.0f;
+            t[j + 1] = t[j] * (1.0f - alpha[j]);
+          }
+        }
+        T = t[kQuadRun];
+        float c[kQuadRun][3], d[kQuadRun];
+#pragma unroll
+        for (int j = 0; j < kQuadRun; ++j) {
+          const float4 s2 = S.s2[at[j]];
+          c[j][0] = s2.x, c[j][1] = s2.y, c[j][2] = s2.z;
+          if constexpr (DEPTH) d[j] = S.s1[at[j]].w;
+        }
+        asm volatile("" : "+v"(c[0][0]), "+v"(c[1][0]), "+v"(c[2][0]), "+v"(c[3][0]));
+        if constexpr (DEPTH) asm volatile("" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3]));
+#pragma unroll
+        for (int j = 0; j < kQuadRun; ++j) {
+          const float w = alpha[j] * t[j];
+          C0 = fmaf(w, c[j][0], C0);
+          C1 = fmaf(w, c[j][1], C1);
+          C2 = fmaf(w, c[j][2], C2);
+          if constexpr (DEPTH) D = D + w * d[j];
+          last = ok[j] ? (int)(base - rg.x) + at[j] + 1 : last;
         }
       }
-      if (lane < n) S.used[words & 0xFFu] = (uint8_t)used_words;
+      if (lane < n) S.used[words & 0xFFu] = (uint8_t)((used >> lane & 1u) << q);
       __syncthreads();
       // the backward's masks for this batch: whether some pixel reached each entry
       if (lane < cnt) qm[base + lane] = S.used[lane];
@@ -619,7 +659,7 @@ __device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, 
 // (Seven wavefronts per SIMD, 71 registers: left to itself the compiler takes more with the quadrant path
 // beside the loop: 814 against 778 us at 500k Gaussians, 8 views, many lists split.)
 template <int BIN, int BATCH, bool DEPTH>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(7))) void render_fwd4_kernel(
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 64 ? 1 : 7))) void render_fwd4_kernel(
     ViewTable vt, const uint2* __restrict__ ranges, const uint32_t* __restrict__ pair_items, const Rec* __restrict__ rec,
     float* __restrict__ out_rgb, float* __restrict__ out_T, float* __restrict__ ws_T, int32_t* __restrict__ ws_last,
     float bg0, float bg1, float bg2, const float* __restrict__ depth, float* __restrict__ out_depth,
@@ -647,7 +687,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(7))) void
       const int q = __builtin_ctz(sel);
       float Tq, C[3], Dq;
       int lastq;
-      composite_quadrant<BATCH, DEPTH>(S, q, rg, pair_items, rec, depth, tx0, ty0, Wf, half, qm, Tq, C, Dq, lastq);
+      composite_quadrant<BATCH, DEPTH>(S, q, rg, pair_items, rec, depth, tx0, ty0, uniform(Wf), uniform(half), qm, Tq, C, Dq, lastq);
       const int64_t plane = (int64_t)W * H, pix = (int64_t)(y + 8 * (q >> 1)) * W + x + 8 * (q & 1);
       const int64_t gp = vt.pix_base[v] + pix;
       float* img = out_rgb + 3 * vt.pix_base[v];
@@ -1019,10 +1059,10 @@ __global__ __launch_bounds__(TILE* TILE) void render_bwd_kernel(ViewTable vt, co
 // wavefronts where the registers allow 20; with a group's sums over its partials, 7,492 bytes take six:
 // 1,355 -> 1,290 us.
 template <int BATCH>
-struct Stage4 {
-  float4 s0[BATCH];  // u, v, l0, l1
-  float4 s1[BATCH];  // l2, p_min, opacity, unused
-  float4 s2[BATCH];  // r, g, b, 1 / opacity
+struct Stage4 {  // (one entry more for reverse_quadrant)
+  float4 s0[BATCH + 1];  // u, v, l0, l1
+  float4 s1[BATCH + 1];  // l2, p_min, opacity, unused
+  float4 s2[BATCH + 1];  // r, g, b, 1 / opacity
   uint32_t sid[BATCH];
   uint16_t list[BATCH];  // entry index | quadrant mask << 8 | flags << 12
 };
@@ -1100,7 +1140,7 @@ __device__ inline void flush_group(const Stage4<BATCH>& S, const FlushLane& f, f
 // One quadrant of a split tile in reverse, one pixel per lane: as in composite_quadrant, a run of
 // kQuadRunBwd entries is evaluated together and only T and DS stay chains; the culling masks, items and
 // records of the next batches are loaded ahead.  The cases of composite_quadrant: 306 us unsplit, 186 us with
-// the one-entry loop, 145 us with this (three entries together: 148), and 23.4 -> 19.2 us.
+// the one-entry loop, 138 us with this (three entries together: 141), and 23.4 -> 18.9 us.
 constexpr int kQuadRunBwd = 2;
 
 template <int BATCH>
@@ -1110,8 +1150,9 @@ __device__ inline void reverse_quadrant(Stage4<BATCH>& S, float* ring, const Flu
                                         float half, double* __restrict__ g2d) {
   constexpr int NB = BATCH < kWave ? BATCH : kWave;
   const int lane = threadIdx.x;
-  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
   if (wmax <= 0) return;  // uniform
+  if (lane == 0)
+    S.s0[NB] = make_float4(0, 0, 0, 0), S.s1[NB] = make_float4(0, __builtin_inff(), 0, 0), S.s2[NB] = S.s0[NB];
   // entry e of the batch that ends at `end` is list position end - 1 - e (clamped into the list's start)
   float* const out01 = ring + (lane >> 4) * kRingRow + (lane & 15);
   float* const out8 = ring + (lane >> 4) * kRingRow + 32 + (lane & 3);
@@ -1133,7 +1174,7 @@ __device__ inline void reverse_quadrant(Stage4<BATCH>& S, float* ring, const Flu
       w = 1u | (reach < half ? 0 : kEntryWrap << 4) | (r1.y > kAlphaMax ? kEntryClamp << 4 : 0);
     }
     const uint64_t bl = __builtin_amdgcn_ballot_w64(w != 0u);
-    if (w != 0u) S.list[__popcll(bl & below)] = (uint16_t)(lane | (w << 8));
+    if (w != 0u) S.list[bits_below(bl)] = (uint16_t)(lane | (w << 8));
     const int n = __popcll(bl);
     mask = mask1;
     item = item1;
@@ -1147,47 +1188,80 @@ __device__ inline void reverse_quadrant(Stage4<BATCH>& S, float* ring, const Flu
     __syncthreads();
     for (int i0 = 0; i0 < n; i0 += kRingEntries) {
       const int m = min(kRingEntries, n - i0);
-      const uint32_t words = S.list[min(i0 + lane, n - 1)];  // the group's list words, one per lane
+      // the group's list words, one per lane; past its end the entry nothing reaches
+      const uint32_t words = lane < m ? S.list[i0 + lane] : NB;
       for (int i = 0; i < m; i += kQuadRunBwd) {
-        float4 a[kQuadRunBwd], b[kQuadRunBwd], c[kQuadRunBwd];
-        float du[kQuadRunBwd], gq[kQuadRunBwd][9];
+        vec4 a[kQuadRunBwd], b[kQuadRunBwd], c[kQuadRunBwd];
+        float du[kQuadRunBwd], t1[kQuadRunBwd], t2[kQuadRunBwd], araw[kQuadRunBwd], alpha[kQuadRunBwd];
+        float wk[kQuadRunBwd], dpow[kQuadRunBwd];
         int k[kQuadRunBwd];
         uint32_t flags = 0;
 #pragma unroll
         for (int j = 0; j < kQuadRunBwd; ++j) {
-          const uint32_t km = __builtin_amdgcn_readlane(words, min(i + j, m - 1));
-          flags |= km >> 12;
+          const uint32_t km = __builtin_amdgcn_readlane(words, i + j);
+          flags |= km;
           k[j] = (int)(km & 0xFFu);
-          a[j] = S.s0[k[j]];
-          b[j] = S.s1[k[j]];
-          c[j] = S.s2[k[j]];
+          a[j] = as_vec4(S.s0[k[j]]);
+          b[j] = as_vec4(S.s1[k[j]]);
+          c[j] = as_vec4(S.s2[k[j]]);
         }
+        static_assert(kQuadRunBwd == 2, "the operands of the next line");
+        // every read is issued before the first is waited for
+        asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(b[0]), "+v"(b[1]), "+v"(c[0]), "+v"(c[1]));
 #pragma unroll
         for (int j = 0; j < kQuadRunBwd; ++j) du[j] = px - a[j].x;
-        if (flags & kEntryWrap) {  // uniform
+        if (__builtin_expect(opaque((int)(flags >> 12 & kEntryWrap)), 0)) {  // uniform
 #pragma unroll
-          for (int j = 0; j < kQuadRunBwd; ++j) du[j] = wrap_du(du[j], Wf, half);
+          for (int j = 0; j < kQuadRunBwd; ++j) {
+            du[j] = wrap_du(du[j], Wf, half);
+            keep_branch(du[j]);
+          }
         }
-        bool ok[kQuadRunBwd];
-        float p[kQuadRunBwd], t1[kQuadRunBwd], t2[kQuadRunBwd];
+        // the steps of bwd_pixel_step, both entries through each before the next
 #pragma unroll
         for (int j = 0; j < kQuadRunBwd; ++j) {
           const float dv = py - a[j].y;
           t1[j] = fmaf(a[j].z, du[j], a[j].w * dv);
           t2[j] = b[j].x * dv;
-          p[j] = -fmaf(t1[j], t1[j], t2[j] * t2[j]);
-          ok[j] = end - 1 - k[j] < P.last && !(p[j] < b[j].y) && i + j < m;
+          const float p = -fmaf(t1[j], t1[j], t2[j] * t2[j]);
+          const bool ok = end - 1 - k[j] < P.last && !(p < b[j].y);
+          araw[j] = b[j].z * __expf(p);
+          alpha[j] = ok ? araw[j] : 0.0f;
+        }
+        const int clamp = (int)(flags >> 12 & kEntryClamp);
+        if (__builtin_expect(opaque(clamp) != 0, 0)) {  // uniform
+#pragma unroll
+          for (int j = 0; j < kQuadRunBwd; ++j) {
+            alpha[j] = fminf(alpha[j], kAlphaMax);
+            keep_branch(alpha[j]);
+          }
         }
 #pragma unroll
-        for (int j = 0; j < kQuadRunBwd; ++j)
-          bwd_pixel_step<false>(P, ok[j], (int)(flags & kEntryClamp), p[j], t1[j], t2[j], b[j], c[j], gq[j]);
+        for (int j = 0; j < kQuadRunBwd; ++j) {
+          const float inv_om = __builtin_amdgcn_rcpf(1.0f - alpha[j]);
+          P.T = P.T * inv_om;
+          wk[j] = alpha[j] * P.T;
+          const float dc = fmaf(P.dl0, c[j].x, fmaf(P.dl1, c[j].y, P.dl2 * c[j].z));
+          dpow[j] = fmaf(-P.DS, alpha[j] * inv_om, dc * wk[j]);
+          P.DS = fmaf(dc, wk[j], P.DS);
+        }
+        if (__builtin_expect(opaque(clamp) != 0, 0)) {  // uniform
+#pragma unroll
+          for (int j = 0; j < kQuadRunBwd; ++j) {
+            dpow[j] = araw[j] > kAlphaMax ? 0.0f : dpow[j];
+            keep_branch(dpow[j]);
+          }
+        }
 #pragma unroll
         for (int j = 0; j < kQuadRunBwd; ++j) {
           if (j > 0 && i + j >= m) break;  // uniform (past an odd group)
-          quad_reduce9(gq[j]);
-          out01[(i + j) * kRingStride] = gq[j][0];
-          out01[(i + j) * kRingStride + 16] = gq[j][1];
-          if ((lane & 12) == 0) out8[(i + j) * kRingStride] = gq[j][8];
+          const float g0 = dpow[j] * t1[j], g1 = dpow[j] * t2[j];
+          float g[9] = {g0,         g1,           g0 * t1[j],   g0 * t2[j],  g1 * t2[j],
+                        dpow[j],    wk[j] * P.dl0, wk[j] * P.dl1, wk[j] * P.dl2};
+          quad_reduce9(g);
+          out01[(i + j) * kRingStride] = g[0];
+          out01[(i + j) * kRingStride + 16] = g[1];
+          out8[(i + j) * kRingStride] = g[8];  // (four lanes write the same value)
         }
       }
       flush_group<BATCH>(S, fl, ring, i0, m, g2d);
@@ -1196,7 +1270,7 @@ __device__ inline void reverse_quadrant(Stage4<BATCH>& S, float* ring, const Flu
 }
 
 template <int BIN, int BATCH>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5))) void render_bwd4_kernel(
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 64 ? 1 : 5))) void render_bwd4_kernel(
     ViewTable vt, const uint2* __restrict__ ranges, const uint32_t* __restrict__ pair_items, const Rec* __restrict__ rec,
     const float* __restrict__ ws_T, const int32_t* __restrict__ ws_last, const float* __restrict__ dL_drgb,
     double* __restrict__ g2d, int64_t items, float bg0, float bg1, float bg2, const uint8_t* __restrict__ qmask,
