@@ -286,6 +286,20 @@ int odgs_densify(int64_t n, int32_t sh_degree, const float* means, const float* 
                  int64_t capacity, float* out_means, float* out_scales, float* out_quats, float* out_opacities,
                  float* out_sh, int32_t* out_src, int64_t* out_counts, void* ws, size_t ws_bytes, void* stream);
 
+/* The two halves of odgs_densify, for outputs of exact size.  odgs_densify_count writes out_counts and
+ * leaves in the workspace what odgs_densify_write (same inputs and parameters, counts = out_counts, the
+ * workspace unchanged) needs to write the outputs, whose column stride `capacity` may be anything from
+ * the counts' total on (entries past the stride are dropped). */
+int odgs_densify_count(int64_t n, const float* scales, const float* opacities, const float* grad_sum,
+                       const float* tau_sum, const int32_t* count, const odgs_densify_params* dp /*[host]*/,
+                       int64_t* out_counts, void* ws, size_t ws_bytes, void* stream);
+int odgs_densify_write(int64_t n, int32_t sh_degree, const float* means, const float* scales, const float* quats,
+                       const float* opacities, const float* sh, const float* grad_sum, const float* tau_sum,
+                       const int32_t* count, const float* noise, const odgs_densify_params* dp /*[host]*/,
+                       int64_t capacity, float* out_means, float* out_scales, float* out_quats, float* out_opacities,
+                       float* out_sh, int32_t* out_src, const int64_t* counts, const void* ws, size_t ws_bytes,
+                       void* stream);
+
 /* ---- training step around the rasterizer (the 3DGS recipe the paper keeps) ---------------- */
 
 /* Device pointers to the five parameter arrays (layouts as above). */

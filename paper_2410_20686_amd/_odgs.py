@@ -28,7 +28,7 @@ BINNINGS = {"auto": 0, "coarse": FLAG_BIN_COARSE, "direct": FLAG_BIN_DIRECT}
 
 EXPORTS = ("odgs_plan_init", "odgs_plan_set_pinhole", "odgs_workspace_bytes", "odgs_preprocess", "odgs_bin_sort", "odgs_render_fwd",
            "odgs_render_bwd", "odgs_composite_bwd", "odgs_project_bwd", "odgs_status_offset", "odgs_strerror",
-           "odgs_densify", "odgs_densify_workspace_bytes", "odgs_l1_loss", "odgs_l1_loss_workspace_bytes",
+           "odgs_densify", "odgs_densify_count", "odgs_densify_write", "odgs_densify_workspace_bytes", "odgs_l1_loss", "odgs_l1_loss_workspace_bytes",
            "odgs_l1_loss_noalloc",
            "odgs_adam_step",
            "odgs_plan_size", "odgs_debug_records", "odgs_debug_keys", "odgs_debug_pixel_counts", "odgs_debug_g2d")
@@ -123,6 +123,10 @@ def lib():
         L.odgs_densify_workspace_bytes.restype = c_sz
         L.odgs_densify.argtypes = [c_i64, c_i32] + [P] * 9 + [ctypes.POINTER(DensifyParams), c_i64] + [P] * 8 + [c_sz, P]
         L.odgs_densify.restype = c_i32
+        L.odgs_densify_count.argtypes = [c_i64] + [P] * 5 + [ctypes.POINTER(DensifyParams), P, P, c_sz, P]
+        L.odgs_densify_count.restype = c_i32
+        L.odgs_densify_write.argtypes = L.odgs_densify.argtypes
+        L.odgs_densify_write.restype = c_i32
         L.odgs_l1_loss_workspace_bytes.argtypes = [c_i64]
         L.odgs_l1_loss_workspace_bytes.restype = c_sz
         L.odgs_l1_loss.argtypes = [P, P, c_i64, P, P, P, c_sz, P]
@@ -268,6 +272,19 @@ def odgs_densify(n, sh_degree, means, scales, quats, opac, sh, grad_sum, tau_sum
     _check(lib().odgs_densify(int(n), int(sh_degree), means, scales, quats, opac, sh, grad_sum, tau_sum, count, noise,
                               ctypes.byref(params), int(capacity), out_means, out_scales, out_quats, out_opac, out_sh,
                               out_src, out_counts, ws, ws_bytes, stream), "odgs_densify")
+
+
+def odgs_densify_count(n, scales, opac, grad_sum, tau_sum, count, params: DensifyParams, out_counts, ws, ws_bytes, stream):
+    _check(lib().odgs_densify_count(int(n), scales, opac, grad_sum, tau_sum, count, ctypes.byref(params), out_counts, ws,
+                                    ws_bytes, stream), "odgs_densify_count")
+
+
+def odgs_densify_write(n, sh_degree, means, scales, quats, opac, sh, grad_sum, tau_sum, count, noise,
+                       params: DensifyParams, capacity, out_means, out_scales, out_quats, out_opac, out_sh, out_src,
+                       counts, ws, ws_bytes, stream):
+    _check(lib().odgs_densify_write(int(n), int(sh_degree), means, scales, quats, opac, sh, grad_sum, tau_sum, count,
+                                    noise, ctypes.byref(params), int(capacity), out_means, out_scales, out_quats,
+                                    out_opac, out_sh, out_src, counts, ws, ws_bytes, stream), "odgs_densify_write")
 
 
 def odgs_debug_pixel_counts(plan, ws, out, stream):

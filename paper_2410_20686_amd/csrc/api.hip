@@ -297,6 +297,52 @@ int odgs_adam_step(int64_t n, int32_t sh_degree, const odgs_param_ptrs* raw, con
 
 size_t odgs_densify_workspace_bytes(int64_t n) { return n < 0 ? 0 : densify_workspace_bytes(n); }
 
+static int check_densify(int64_t n, const odgs_densify_params* dp, const void* counts, const void* ws, size_t ws_bytes) {
+  if (n < 0 || n >= ((int64_t)1 << 30) || !dp) return ODGS_EINVAL;
+  if (!counts || !aligned(counts, 8) || !ws || !aligned(ws, 256)) return ODGS_EINVAL;
+  if (!std::isfinite(dp->extent) || !std::isfinite(dp->percent_dense) || !std::isfinite(dp->min_opacity) ||
+      !std::isfinite(dp->max_scale_frac) || dp->max_scale_frac < 0.0f)
+    return ODGS_EINVAL;
+  return ws_bytes < densify_workspace_bytes(n) ? ODGS_ENOSPACE : ODGS_OK;
+}
+
+int odgs_densify_count(int64_t n, const float* scales, const float* opacities, const float* grad_sum,
+                       const float* tau_sum, const int32_t* count, const odgs_densify_params* dp, int64_t* out_counts,
+                       void* ws, size_t ws_bytes, void* stream) {
+  const int rc = check_densify(n, dp, out_counts, ws, ws_bytes);
+  if (rc != ODGS_OK) return rc;
+  if (n > 0) {
+    const void* in[5] = {scales, opacities, grad_sum, tau_sum, count};
+    for (const void* q : in)
+      if (!q || !aligned(q, 4)) return ODGS_EINVAL;
+  }
+  return hip_status(launch_densify_count(n, scales, opacities, grad_sum, tau_sum, count, *dp, out_counts, ws,
+                                         static_cast<hipStream_t>(stream)));
+}
+
+int odgs_densify_write(int64_t n, int32_t sh_degree, const float* means, const float* scales, const float* quats,
+                       const float* opacities, const float* sh, const float* grad_sum, const float* tau_sum,
+                       const int32_t* count, const float* noise, const odgs_densify_params* dp, int64_t capacity,
+                       float* out_means, float* out_scales, float* out_quats, float* out_opacities, float* out_sh,
+                       int32_t* out_src, const int64_t* counts, const void* ws, size_t ws_bytes, void* stream) {
+  if (sh_degree < 0 || sh_degree > 3 || capacity < 0) return ODGS_EINVAL;
+  const int rc = check_densify(n, dp, counts, ws, ws_bytes);
+  if (rc != ODGS_OK) return rc;
+  if (n > 0) {
+    const void* in[9] = {means, scales, quats, opacities, sh, grad_sum, tau_sum, count, noise};
+    for (const void* q : in)
+      if (!q || !aligned(q, 4)) return ODGS_EINVAL;
+  }
+  if (n > 0 && capacity > 0) {
+    const void* out[6] = {out_means, out_scales, out_quats, out_opacities, out_sh, out_src};
+    for (const void* q : out)
+      if (!q || !aligned(q, 4)) return ODGS_EINVAL;
+  }
+  return hip_status(launch_densify_write(n, sh_degree, means, scales, quats, opacities, sh, grad_sum, tau_sum, count,
+                                         noise, *dp, capacity, out_means, out_scales, out_quats, out_opacities, out_sh,
+                                         out_src, counts, ws, static_cast<hipStream_t>(stream)));
+}
+
 int odgs_densify(int64_t n, int32_t sh_degree, const float* means, const float* scales, const float* quats,
                  const float* opacities, const float* sh, const float* grad_sum, const float* tau_sum,
                  const int32_t* count, const float* noise, const odgs_densify_params* dp, int64_t capacity,
@@ -305,21 +351,19 @@ int odgs_densify(int64_t n, int32_t sh_degree, const float* means, const float* 
   if (n < 0 || n >= ((int64_t)1 << 30) || sh_degree < 0 || sh_degree > 3 || !dp) return ODGS_EINVAL;
   if (!out_counts || !aligned(out_counts, 8) || !ws || !aligned(ws, 256)) return ODGS_EINVAL;
   if (capacity < 2 * n) return ODGS_EINVAL;
-  if (!std::isfinite(dp->extent) || !std::isfinite(dp->percent_dense) || !std::isfinite(dp->min_opacity) ||
-      !std::isfinite(dp->max_scale_frac) || dp->max_scale_frac < 0.0f)
-    return ODGS_EINVAL;
-  if (ws_bytes < densify_workspace_bytes(n)) return ODGS_ENOSPACE;
-  if (n > 0) {
-    const void* in[10] = {means, scales, quats, opacities, sh, grad_sum, tau_sum, count, noise, nullptr};
-    for (int k = 0; k < 9; ++k)
-      if (!in[k] || !aligned(in[k], 4)) return ODGS_EINVAL;
-    const void* out[6] = {out_means, out_scales, out_quats, out_opacities, out_sh, out_src};
-    for (const void* q : out)
+  int rc = check_densify(n, dp, out_counts, ws, ws_bytes);
+  if (rc != ODGS_OK) return rc;
+  if (n > 0) {  // everything is checked before the first launch
+    const void* in[15] = {means, scales,    quats,      opacities, sh,            grad_sum, tau_sum, count,
+                          noise, out_means, out_scales, out_quats, out_opacities, out_sh,   out_src};
+    for (const void* q : in)
       if (!q || !aligned(q, 4)) return ODGS_EINVAL;
   }
-  return hip_status(launch_densify(n, sh_degree, means, scales, quats, opacities, sh, grad_sum, tau_sum, count, noise,
-                                   *dp, capacity, out_means, out_scales, out_quats, out_opacities, out_sh, out_src,
-                                   out_counts, ws, static_cast<hipStream_t>(stream)));
+  rc = odgs_densify_count(n, scales, opacities, grad_sum, tau_sum, count, dp, out_counts, ws, ws_bytes, stream);
+  if (rc != ODGS_OK) return rc;
+  return odgs_densify_write(n, sh_degree, means, scales, quats, opacities, sh, grad_sum, tau_sum, count, noise, dp,
+                            capacity, out_means, out_scales, out_quats, out_opacities, out_sh, out_src, out_counts, ws,
+                            ws_bytes, stream);
 }
 
 int odgs_render_bwd(const odgs_plan* plan, const float* means, const float* scales, const float* quats,

@@ -218,11 +218,14 @@ hipError_t launch_preprocess_bwd(const odgs_plan* p, const float* means, const f
                                  const float* opac, const float* sh, const float* cams, void* ws, float* d_means,
                                  float* d_scales, float* d_quats, float* d_opac, float* d_sh,
                                  const odgs_densify_acc* acc, hipStream_t st);
-hipError_t launch_densify(int64_t n, int32_t sh_degree, const float* means, const float* scales, const float* quats,
-                          const float* opac, const float* sh, const float* grad_sum, const float* tau_sum,
-                          const int32_t* count, const float* noise, const odgs_densify_params& dp, int64_t capacity,
-                          float* out_means, float* out_scales, float* out_quats, float* out_opac, float* out_sh,
-                          int32_t* out_src, int64_t* out_counts, void* ws, hipStream_t st);
+hipError_t launch_densify_count(int64_t n, const float* scales, const float* opac, const float* grad_sum,
+                                const float* tau_sum, const int32_t* count, const odgs_densify_params& dp,
+                                int64_t* out_counts, void* ws, hipStream_t st);
+hipError_t launch_densify_write(int64_t n, int32_t sh_degree, const float* means, const float* scales, const float* quats,
+                                const float* opac, const float* sh, const float* grad_sum, const float* tau_sum,
+                                const int32_t* count, const float* noise, const odgs_densify_params& dp, int64_t capacity,
+                                float* out_means, float* out_scales, float* out_quats, float* out_opac, float* out_sh,
+                                int32_t* out_src, const int64_t* counts, const void* ws, hipStream_t st);
 size_t densify_workspace_bytes(int64_t n);
 size_t l1_workspace_bytes(int64_t count);
 hipError_t launch_l1(const float* rgb, const float* tgt, int64_t count, float* dL, float* loss, void* ws,

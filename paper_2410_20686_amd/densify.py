@@ -74,19 +74,19 @@ def densify(params, stats: DensifyStats, noise: torch.Tensor, extent: float, sh_
     if tuple(noise.shape) != (2, 3, n) or noise.dtype != torch.float32:
         raise ValueError("noise must be float32 [2, 3, %d]" % n)
     stats.acc(n)
-    cap = max(2 * n, 1)
-    out = (torch.empty((3, cap), dtype=torch.float32, device=dev), torch.empty((3, cap), dtype=torch.float32, device=dev),
-           torch.empty((4, cap), dtype=torch.float32, device=dev), torch.empty(cap, dtype=torch.float32, device=dev),
-           torch.empty((sh.shape[0], cap), dtype=torch.float32, device=dev))
-    src = torch.empty(cap, dtype=torch.int32, device=dev)
     counts = torch.empty(4, dtype=torch.int64, device=dev)
     ws_bytes = B.odgs_densify_workspace_bytes(n)
     ws = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
     p = B.DensifyParams(float(extent), float(percent_dense), float(min_opacity), float(max_scale_frac))
-    B.odgs_densify(n, sh_degree, *[_ptr(t) for t in params], _ptr(stats.grad_sum), _ptr(stats.tau_sum),
-                   _ptr(stats.count), _ptr(noise), p, cap, *[_ptr(t) for t in out], _ptr(src), _ptr(counts),
-                   _ptr(ws), ws_bytes, _stream())
-    c = tuple(int(x) for x in counts.cpu())
+    st = _stream()
+    rule = [_ptr(t) for t in (scales, opac, stats.grad_sum, stats.tau_sum, stats.count)]
+    B.odgs_densify_count(n, *rule, p, _ptr(counts), _ptr(ws), ws_bytes, st)
+    c = tuple(counts.tolist())
     m = sum(c)
-    new = tuple(t[..., :m].contiguous() for t in out)
-    return new, src[:m], c
+    # the outputs at their exact size: nothing is copied out of larger arrays afterwards
+    new = tuple(torch.empty(shape, dtype=torch.float32, device=dev) for shape in ((3, m), (3, m), (4, m), (m,), (sh.shape[0], m)))
+    src = torch.empty(m, dtype=torch.int32, device=dev)
+    if m > 0:
+        B.odgs_densify_write(n, sh_degree, *[_ptr(t) for t in params], *rule[2:], _ptr(noise), p, m,
+                             *[_ptr(t) for t in new], _ptr(src), _ptr(counts), _ptr(ws), ws_bytes, st)
+    return new, src, c
