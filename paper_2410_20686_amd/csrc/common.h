@@ -85,26 +85,33 @@ __device__ inline int view_of_item(int64_t item, int64_t n) { return (int)(item 
 // is composited by four wavefronts at once instead of setting the launch's length by itself.
 // Tasks 0 .. 4 nsplit - 1 are those parts (task e: part e % 4 of queue entry e / 4; of tile
 // e / 4 without a queue), then come the remaining queue entries as whole tiles.  With split_all
-// every tile is split (32x32 tiles composited as four 16x16 parts).
+// every tile is split (32x32 tiles composited as four 16x16 parts); then a forward takes the first nfine
+// queue entries (the longest, at most fine_cap) before all others in sixteen tasks each, quadrant e % 4
+// of part e / 4 % 4.
 struct TileSched {
   const uint32_t* order;  // tile ids by descending list length, or nullptr
   uint32_t* ctr;          // persistent: {next task, finished workgroups}; nullptr: one task each
   odgs_status* status;
-  uint32_t* split;        // {long lists by binning, and of those split by the last forward; tiles to split, and split}
+  uint32_t* split;        // counts by binning and of those the last forward's: long lists, tiles to split, and
+                          // 32x32 tiles to take in sixteen tasks
   int32_t tiles;
   int32_t split_cap;      // 0: whole tiles only
   int32_t split_all;      // every tile in four parts (split_cap == tiles)
+  int32_t fine_cap;       // with split_all: most tiles in sixteen tasks
 };
 
 // Upper bound of the task count of a launch (its grid without a persistent launch).
-inline int sched_tasks(const TileSched& s) { return s.tiles + 3 * s.split_cap; }
+inline int sched_tasks(const TileSched& s) { return s.tiles + 3 * s.split_cap + 12 * s.fine_cap; }
 
 // Next task of this workgroup (uniform): returns its tile and sets `sel` to the part it covers
-// (1 << part; 0xF: the whole tile), or returns -1 when the workgroup is done.  `nsplit` (uniform,
-// at most split_cap) is the number of split tiles; `round` starts at 0; `slot` is a
-// workgroup-shared word.  Contains barriers in persistent mode.
-__device__ inline int claim_task(const TileSched& s, int nsplit, uint32_t& round, uint32_t* slot, uint32_t& sel) {
-  const uint32_t total = (uint32_t)(s.tiles + 3 * nsplit);
+// (1 << part; 0xF: the whole tile; 1 << part | 0x10 << quadrant), or returns -1 when the workgroup is
+// done.  `nsplit` (uniform, at most split_cap) is the number of split tiles, `nfine` (at most nsplit and
+// fine_cap) of those in sixteen; the first `marked` queue entries have bit 8 of `sel` set; `round` starts
+// at 0; `slot` is a workgroup-shared word.  Contains barriers in persistent mode.
+__device__ inline int claim_task(const TileSched& s, int nsplit, int nfine, int marked, uint32_t& round, uint32_t* slot,
+                                 uint32_t& sel) {
+  const uint32_t total = (uint32_t)(s.tiles + 3 * nsplit + 12 * nfine);
+  const uint32_t fine = 16u * (uint32_t)nfine, ns = (uint32_t)(nsplit - nfine);
   uint32_t e;
   if (!s.ctr) {
     if (round++) return -1;
@@ -113,9 +120,14 @@ __device__ inline int claim_task(const TileSched& s, int nsplit, uint32_t& round
     // of a split tile (which stage the same list) go to four consecutive workgroups of one XCD
     // (groups of eight tiles, in queue order; the tail of an incomplete group stays in order).
     constexpr uint32_t kXcds = 8;
-    if (e < (uint32_t)(nsplit / kXcds) * 4u * kXcds) {
-      const uint32_t k = e / kXcds;
-      e = 4u * ((k / 4u) * kXcds + e % kXcds) + k % 4u;
+    if (e < fine) {
+      if (e < ((uint32_t)nfine / kXcds) * 16u * kXcds) {
+        const uint32_t k = e / kXcds;
+        e = 16u * ((k / 16u) * kXcds + e % kXcds) + k % 16u;
+      }
+    } else if (e - fine < (ns / kXcds) * 4u * kXcds) {
+      const uint32_t k = (e - fine) / kXcds;
+      e = fine + 4u * ((k / 4u) * kXcds + e % kXcds) + k % 4u;
     }
   } else {
     __syncthreads();  // every thread has read the previous claim
@@ -133,20 +145,24 @@ __device__ inline int claim_task(const TileSched& s, int nsplit, uint32_t& round
   }
   if (e >= total) return -1;
   uint32_t idx;
-  if (e < 4u * (uint32_t)nsplit) {
+  if (e < fine) {
+    sel = 1u << ((e >> 2) & 3u) | 0x10u << (e & 3u);
+    idx = e >> 4;
+  } else if (e - fine < 4u * ns) {
     sel = 1u << (e & 3u);
-    idx = e >> 2;
+    idx = (uint32_t)nfine + ((e - fine) >> 2);
   } else {
     sel = 0xFu;
-    idx = e - 3u * (uint32_t)nsplit;
+    idx = (uint32_t)nfine + (e - fine) - 3u * ns;
   }
+  if (idx < (uint32_t)marked) sel |= 0x100u;
   return s.order ? (int)s.order[idx] : (int)idx;
 }
 
 // Next whole tile of this workgroup (compositors that take no quadrant tasks).
 __device__ inline int claim_tile(const TileSched& s, uint32_t& round, uint32_t* slot) {
   uint32_t sel;
-  return claim_task(s, 0, round, slot, sel);
+  return claim_task(s, 0, 0, 0, round, slot, sel);
 }
 
 // Split tiles of a forward launch (uniform): every tile with split_all, else what binning chose
@@ -162,13 +178,23 @@ __device__ inline int reverse_split(const TileSched& s) {
   return s.split_cap > 0 && s.order ? (int)min(s.split[3], (uint32_t)s.split_cap) : 0;
 }
 
+// Tiles in sixteen tasks of a forward launch, and of the forward that a reverse launch follows (whose
+// culling masks are laid out for them).
+__device__ inline int forward_fine(const TileSched& s) {
+  return s.fine_cap > 0 ? (int)min(s.split[4], (uint32_t)s.fine_cap) : 0;
+}
+__device__ inline int reverse_fine(const TileSched& s) {
+  return s.fine_cap > 0 ? (int)min(s.split[5], (uint32_t)s.fine_cap) : 0;
+}
+
 // The forward marks the pair list it composited, and how many tiles it split; the reverse
 // compositor runs only on that list.
-__device__ inline void mark_forward(const TileSched& s, int nsplit = 0) {
+__device__ inline void mark_forward(const TileSched& s, int nsplit = 0, int nfine = 0) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     s.status->fwd_gen = s.status->bin_gen;
     s.split[1] = s.split_all ? (uint32_t)nsplit : min(s.split[0], (uint32_t)nsplit);
     s.split[3] = (uint32_t)nsplit;
+    s.split[5] = (uint32_t)nfine;
   }
 }
 __device__ inline bool forward_is_stale(const TileSched& s) {
@@ -254,14 +280,16 @@ hipError_t launch_status_reset(const odgs_plan* p, void* ws, hipStream_t st);
 // tiles only (split_cap 0); split_tile_cap gives the cap of compositors that take quadrant tasks.
 TileSched make_sched(const odgs_plan* p, void* ws, int which);
 int split_tile_cap(int tiles);
+int fine_tile_cap(int tiles);
 // The schedule of a compositor that takes quadrant tasks (only with the queue, which names the
 // longest tiles).
 inline TileSched with_split(TileSched s) {
   if (s.order) s.split_cap = split_tile_cap(s.tiles);
   return s;
 }
-// The schedule of a compositor that takes every tile in four parts.
+// The schedule of a compositor that takes every tile in four parts, and the longest in sixteen.
 inline TileSched with_parts(TileSched s) {
+  if (s.order) s.fine_cap = fine_tile_cap(s.tiles);
   s.split_cap = s.tiles;
   s.split_all = 1;
   return s;

@@ -458,19 +458,19 @@ __global__ __launch_bounds__(TILE* TILE) void render_fwd_kernel(
 // footprint test took the two edges that face the centre instead of all four.
 // The 16x16 pixel block a task composites: its origin (bx0, by0), its quadrants (`sel`, updated)
 // and the byte plane of its culling masks.  BIN = 16: the tile, or one quadrant of a split tile
-// (plane q); BIN = 32: part p of the tile, the 16x16 block p = 2 by + bx with all four quadrants
-// (plane p).
+// (plane q); BIN = 32: part p of the tile, the 16x16 block p = 2 by + bx, with all four quadrants or, of
+// a tile in sixteen tasks, one (plane p: four runs of bits in the bytes of the tile's list, see quadrant_masks).
 template <int BIN>
 __device__ inline void task_block(const ViewTable& vt, int v, int g, uint32_t& sel, int& bx0, int& by0, int& plane) {
   const int ntx = vt.W[v] / BIN;
   const int lt = g - vt.tile_base[v];
   bx0 = (lt % ntx) * BIN;
   by0 = (lt / ntx) * BIN;
-  plane = sel == 0xFu ? 0 : __builtin_ctz(sel);
+  plane = sel == 0xFu ? 0 : __builtin_ctz(sel & 0xFu);
   if constexpr (BIN == 32) {
     bx0 += 16 * (plane & 1);
     by0 += 16 * (plane >> 1);
-    sel = 0xFu;
+    sel = sel >> 4 != 0u ? sel >> 4 : 0xFu;
   } else {
     static_assert(BIN == 16, "blocks of 16x16 pixels in tiles of 16 or 32");
   }
@@ -515,7 +515,24 @@ __device__ inline vec4 as_vec4(const float4& f) { return vec4{f.x, f.y, f.z, f.w
 // with this; 6k on 512x256 (lists of up to 102) 16.4 us with the one-entry loop, 11.6 us with this.
 constexpr int kQuadRun = 4;
 
-template <int BATCH, bool DEPTH>
+// A quadrant task's culling masks are a byte per list entry at BIN = 16, whose planes it has to itself,
+// and a bit per entry at BIN = 32, where the four quadrants of a part share a plane: quadrant q's bits start
+// at q quarters of the list's bytes (an eighth of them each; the lists are long ones).  The reverse takes
+// the part whole, so that its float sums do not depend on the forward's tasks, and puts its masks together.
+template <int BIN>
+__device__ inline uint8_t* quadrant_masks(uint8_t* plane, uint2 rg, int q) {
+  return BIN == 32 ? plane + rg.x + (uint32_t)q * ((rg.y - rg.x) >> 2) : plane;
+}
+__device__ inline uint32_t part_mask(const uint8_t* __restrict__ plane, uint2 rg, uint32_t k) {
+  const uint8_t* p = plane + rg.x + (k >> 3);
+  const uint32_t step = (rg.y - rg.x) >> 2;
+  uint32_t m = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) m |= ((uint32_t)p[(uint32_t)q * step] >> (k & 7u) & 1u) << q;
+  return m;
+}
+
+template <int BIN, int BATCH, bool DEPTH>
 __device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, const uint32_t* __restrict__ pair_items,
                                           const Rec* __restrict__ rec, const float* __restrict__ depth, int tx0, int ty0,
                                           float Wf, float half, uint8_t* __restrict__ qm, float& T_out, float (&C)[3],
@@ -643,9 +660,18 @@ __device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, 
       if (lane < n) S.used[words & 0xFFu] = (uint8_t)((used >> lane & 1u) << q);
       __syncthreads();
       // the backward's masks for this batch: whether some pixel reached each entry
-      if (lane < cnt) qm[base + lane] = S.used[lane];
+      if constexpr (BIN == 32) {
+        const uint64_t reached = __builtin_amdgcn_ballot_w64(lane < cnt && S.used[lane] != 0);
+        if (8 * lane < cnt) qm[((base - rg.x) >> 3) + lane] = (uint8_t)(reached >> (8 * lane));
+      } else {
+        if (lane < cnt) qm[base + lane] = S.used[lane];
+      }
       __syncthreads();
-      if (__builtin_amdgcn_ballot_w64(qstop == 0.0f) == 0ull) break;  // every pixel has stopped
+      if (__builtin_amdgcn_ballot_w64(qstop == 0.0f) == 0ull) {  // every pixel has stopped
+        if constexpr (BIN == 32)  // the reverse of the part may go further
+          for (uint32_t k = ((base + NB - rg.x) >> 3) + lane; k < (rg.y - rg.x + 7) >> 3; k += kWave) qm[k] = 0;
+        break;
+      }
     }
   }
   T_out = T;
@@ -666,13 +692,13 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 6
     uint8_t* __restrict__ qmask, int64_t qplane, TileSched sc) {
   constexpr int TILE = 16;
   __shared__ FwdStage4<BATCH> S;
-  const int nsplit = forward_split(sc);
-  mark_forward(sc, nsplit);
+  const int nsplit = forward_split(sc), nfine = BIN == 32 ? forward_fine(sc) : 0;
+  mark_forward(sc, nsplit, nfine);
   __shared__ uint32_t s_claim;
   uint32_t round = 0, sel = 0;
   const int lane = threadIdx.x;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
-  for (int g; (g = claim_task(sc, nsplit, round, &s_claim, sel)) >= 0;) {
+  for (int g; (g = claim_task(sc, nsplit, nfine, 0, round, &s_claim, sel)) >= 0;) {
     const int v = view_of_tile(vt, g);
     const int W = vt.W[v], H = vt.H[v];
     int tx0, ty0, pl;
@@ -687,7 +713,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 6
       const int q = __builtin_ctz(sel);
       float Tq, C[3], Dq;
       int lastq;
-      composite_quadrant<BATCH, DEPTH>(S, q, rg, pair_items, rec, depth, tx0, ty0, uniform(Wf), uniform(half), qm, Tq, C, Dq, lastq);
+      composite_quadrant<BIN, BATCH, DEPTH>(S, q, rg, pair_items, rec, depth, tx0, ty0, uniform(Wf), uniform(half),
+                                            quadrant_masks<BIN>(qm, rg, q), Tq, C, Dq, lastq);
       const int64_t plane = (int64_t)W * H, pix = (int64_t)(y + 8 * (q >> 1)) * W + x + 8 * (q & 1);
       const int64_t gp = vt.pix_base[v] + pix;
       float* img = out_rgb + 3 * vt.pix_base[v];
@@ -1279,7 +1306,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 6
   __shared__ Stage4<BATCH> S;
   __shared__ __attribute__((aligned(16))) float ring[kRingEntries * kRingStride];
   if (forward_is_stale(sc)) return;  // uniform
-  const int nsplit = reverse_split(sc);
+  const int nsplit = reverse_split(sc), nfine = BIN == 32 ? reverse_fine(sc) : 0;
   __shared__ uint32_t s_claim;
   uint32_t round = 0, sel = 0;
   const int lane = threadIdx.x;
@@ -1288,10 +1315,12 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 6
   float* const out8 = ring + (lane >> 4) * kRingRow + 32 + (lane & 3);
   const FlushLane fl = flush_lane(ring, lane);
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
-  for (int g; (g = claim_task(sc, nsplit, round, &s_claim, sel)) >= 0;) {
+  for (int g; (g = claim_task(sc, nsplit, 0, nfine, round, &s_claim, sel)) >= 0;) {
     const int v = view_of_tile(vt, g);
     const int W = vt.W[v], H = vt.H[v];
     int tx0, ty0, pl;
+    const bool bits = BIN == 32 && (sel & 0x100u) != 0u;  // the part's masks are four runs of bits
+    sel &= 0xFFu;
     task_block<BIN>(vt, v, g, sel, tx0, ty0, pl);
     const int x = tx0 + (lane & 7), y = ty0 + (lane >> 3);
     const float px0 = (float)x + 0.5f, px1 = (float)(x + 8) + 0.5f;
@@ -1316,7 +1345,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 6
       for (int off = 32; off > 0; off >>= 1) x = max(x, __shfl_xor(x, off));
       return __builtin_amdgcn_readfirstlane(x);
     };
-    if (sel != 0xFu) {  // uniform: a quadrant of a split tile
+    if (BIN == 16 && sel != 0xFu) {  // uniform: a quadrant of a split tile
       const int q = __builtin_ctz(sel);
       const BwdPixel p = load_pixel(q);
       reverse_quadrant<BATCH>(S, ring, fl, p, q & 1 ? px1 : px0, q >> 1 ? py1 : py0, rg, wave_max(p.last), pair_items, rec,
@@ -1341,7 +1370,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 6
         uint32_t m = 0;
         if (e < cnt) {
           const uint32_t pos = rg.x + end - 1 - e;
-          m = qm[pos];
+          m = bits ? part_mask(qm, rg, end - 1 - e) : qm[pos];
           if (m != 0u) {  // records only of the entries the forward's pixels reached
             const uint32_t item = pair_items[pos];
             const Rec r = rec[item];

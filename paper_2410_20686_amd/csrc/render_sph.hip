@@ -567,7 +567,7 @@ __global__ __launch_bounds__(kWave) void render_sph_fwd4_kernel(
   uint32_t round = 0, sel = 0;
   const int lane = threadIdx.x;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
-  for (int g; (g = claim_task(sc, nsplit, round, &s_claim, sel)) >= 0;) {
+  for (int g; (g = claim_task(sc, nsplit, 0, 0, round, &s_claim, sel)) >= 0;) {
     const int v = view_of_tile(vt, g);
     const int W = vt.W[v], H = vt.H[v];
     const int ntx = W / TILE;
@@ -731,7 +731,7 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
   const float* const fsum = sums + kNV * fe + (fq < 3 ? 0 : (fq < 9 ? 3 : fq));
   for (int k = lane; k < kSphRing * kNV + 8; k += kWave) sums[k] = 0.0f;
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
-  for (int g; (g = claim_task(sc, nsplit, round, &s_claim, sel)) >= 0;) {
+  for (int g; (g = claim_task(sc, nsplit, 0, 0, round, &s_claim, sel)) >= 0;) {
     const int v = view_of_tile(vt, g);
     const int W = vt.W[v], H = vt.H[v];
     const int ntx = W / TILE;

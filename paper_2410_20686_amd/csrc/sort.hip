@@ -1160,6 +1160,14 @@ constexpr uint32_t kLongLen = 1024;
 constexpr uint32_t kLongShare = 4096;
 constexpr int kSplitAllTiles = 4096;
 constexpr int kSplitCapMin = 1024;
+// At 32x32 tiles, whose four parts are tasks of their own anyway, word 8: the lists of at least
+// 1 / kFineShare of all pairs and kLongLen pairs take their parts' quadrants as tasks in the forward.
+// 250k Gaussians on 4 views of 1920x960 (2.8M pairs, lists of up to 4,661), forward us: 434 with none,
+// 412, 351 and 345 from 1 / 1024, 1 / 2048 and 1 / 4096 of the pairs on (there the most a sixteenth, then an
+// eighth of the tiles); one of the views 371 -> 239.  The reverse, which puts such a part's masks together
+// from four runs of bits, goes 479 -> 498.
+constexpr uint32_t kFineShare = 4096;
+constexpr int kFineCapMin = 256;
 
 __device__ inline uint32_t cost_bucket(uint32_t len) {
   // 0 for an empty list, else 1 + 32 log2(len) (exponent and top five mantissa bits; <= 993)
@@ -1183,13 +1191,14 @@ __global__ __launch_bounds__(256) void queue_count_kernel(const uint2* __restric
   for (int b = threadIdx.x; b < kQueueBuckets; b += 256) bstart[(size_t)blockIdx.x * kQueueBuckets + b] = h[b];
 }
 
-// Header words 4 and 6 from the scan over buckets, whose threads each name their bucket and the number
+// Header words 4, 6 and 8 from the scan over buckets, whose threads each name their bucket and the number
 // of tiles in it or above.  Contains a barrier; cut: two words of LDS.
 __device__ inline void set_split(int bucket, uint32_t upto, uint32_t cap, bool split_all, uint32_t pairs, uint32_t* cut,
                                  uint32_t* __restrict__ header) {
   const uint32_t floor = split_all ? 1u : kSplitLen;
   if (bucket == (int)cost_bucket(max(split_all ? 1u : kLongLen, pairs / kLongShare))) header[4] = min(upto, cap);
   if (bucket == (int)cost_bucket(max(floor, pairs / kSplitShare))) cut[0] = upto;
+  if (bucket == (int)cost_bucket(max(kLongLen, pairs / kFineShare))) header[8] = upto;
   if (bucket == (int)cost_bucket(max(kLongLen, pairs / (2 * kSplitShare)))) cut[1] = min(upto, kSplitTop);
   __syncthreads();
   if (threadIdx.x == 0) header[6] = min(max(cut[0], cut[1]), cap);
@@ -1391,9 +1400,11 @@ TileSched make_sched(const odgs_plan* p, void* ws, int which) {
   s.split = q + 4;
   s.split_cap = 0;
   s.split_all = 0;
+  s.fine_cap = 0;
   return s;
 }
 
+int fine_tile_cap(int tiles) { return std::min(tiles, std::max(kFineCapMin, tiles / 8)); }
 int split_tile_cap(int tiles) { return tiles < kSplitCapMin ? tiles : std::max(kSplitCapMin, tiles / 8); }
 
 int sched_grid(const TileSched& s, int per_cu) {

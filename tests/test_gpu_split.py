@@ -85,3 +85,29 @@ def test_split_rule(n, scale, crowd, top):
     split, lengths = _check(sc, scenes.identity_cameras(2048, 1024), settings(tile=16), ("queue", "persistent"))
     assert 0 < split < len(lengths)
     assert (split == 128) == top
+
+
+@pytest.mark.parametrize("batch", [64, 128, 256])
+@pytest.mark.parametrize("n,opacity", [(1100, 0.02), (1301, 0.6)])
+def test_long_lists_of_32_pixel_tiles(n, opacity, batch):
+    """Forward in sixteen tasks per 32x32 tile from 1,024 pairs on, the reverse in four with the masks put
+    together: nothing but the order of the FP64 totals may differ from the launch without a queue.  Faint
+    footprints keep every pixel to the end of its list; others stop quadrants at different entries."""
+    sc = scenes.sphere_scene(n, 0, seed=n)
+    dist = np.linspace(1.0, 3.0, n)
+    sc.means[:] = np.stack([0.02 * dist, 0.1 * dist, -dist]) + 0.1 * np.random.default_rng(n).standard_normal((3, n))
+    sc.scales[:] = np.abs(sc.scales) * np.float32(3.0)
+    sc.opacities[:] = np.float32(opacity)
+    cams = scenes.identity_cameras(256, 128)
+    st = settings(tile=32, batch=batch, batch_bwd=batch)
+    dL = scenes.upstream_gradient(cams, seed=7)
+    base = _run(sc, cams, dict(st, schedule="tile_id"), dL)
+    assert base["header"][9] == 0
+    fine = int((_bucket(base["lengths"]) >= _bucket(1024)).sum())
+    assert 0 < fine < len(base["lengths"])
+    for s in ("queue", "persistent"):
+        res = _run(sc, cams, dict(st, schedule=s), dL)
+        assert res["header"][8] == fine and res["header"][9] == fine
+        for k in ("rgb", "T", "depth"):
+            np.testing.assert_array_equal(res[k], base[k])
+        G.assert_grads_close(res, base, names=("g2d",), rtol=1e-6, floor=1e-9)
