@@ -125,7 +125,7 @@ __device__ inline void quad_reduce9(float (&g)[9]) {
       "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n"
       "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n"
       "v_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n"
-      : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]), "+v"(g[8])
+      : "+&v"(g[0]), "+&v"(g[1]), "+&v"(g[2]), "+&v"(g[3]), "+&v"(g[8])
       : "v"(g[4]), "v"(g[5]), "v"(g[6]), "v"(g[7]));
 }
 

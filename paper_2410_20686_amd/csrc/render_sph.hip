@@ -332,7 +332,7 @@ __device__ inline void quad_reduce13(float (&g)[kNV]) {
       ODGS_FOLD(4, 4, "row_half_mirror", "0xf") ODGS_FOLD(6, 6, "row_half_mirror", "0xf")
       ODGS_FOLD(0, 1, "row_half_mirror", "0xa") ODGS_FOLD(2, 3, "row_half_mirror", "0xa")
       ODGS_FOLD(4, 5, "row_half_mirror", "0xa") ODGS_FOLD(6, 7, "row_half_mirror", "0xa")
-      : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]), "+v"(g[4]), "+v"(g[5]), "+v"(g[6]), "+v"(g[7])
+      : "+&v"(g[0]), "+&v"(g[1]), "+&v"(g[2]), "+&v"(g[3]), "+&v"(g[4]), "+&v"(g[5]), "+&v"(g[6]), "+&v"(g[7])
       : "v"(g[8]), "v"(g[9]), "v"(g[10]), "v"(g[11]), "v"(g[12]));
 #undef ODGS_FOLD
 }

@@ -41,7 +41,7 @@ __device__ inline int opaque(int x) {
 
 // Lane `lane` (uniform) of `x` takes the uniform word `value`.
 __device__ inline void set_lane(uint32_t& x, uint32_t value, int lane) {
-  asm("s_mov_b32 m0, %2\n\tv_writelane_b32 %0, %1, m0" : "+v"(x) : "s"(value), "s"(lane));
+  asm("s_mov_b32 m0, %2\n\tv_writelane_b32 %0, %1, m0" : "+v"(x) : "s"(value), "s"(lane) : "m0");
 }
 
 // Keeps a rarely taken uniform branch a branch: the value is not computed on the other path.
