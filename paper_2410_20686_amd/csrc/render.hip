@@ -884,25 +884,24 @@ __device__ inline double g2d_flush_value(const float (&acc)[NS][9][B], int q, in
       const double z11 = acc_total(acc, 2, t), z12 = acc_total(acc, 3, t), z22 = acc_total(acc, 4, t);
       return 2.0 * ((l1 * l1) * z11 + 2.0 * (l1 * l2) * z12 + (l2 * l2) * z22);
     }
-    case 5: return acc_total(acc, 5, t) / (double)b.z;
     default: return acc_total(acc, q, t);
   }
 }
 
 // One pixel's contribution of a Gaussian to the nine per-tile sums (added to gq when ADD, else
-// written; slots 0..4 in whitened coordinates as above; slot 5 the sum of dpow, which is the opacity
-// gradient times the opacity, since alpha = opacity G wherever alpha depends on the inputs), and the
-// pixel's recursion step.  `ok`: the Gaussian contributed to this pixel; t1 = l0 du + l1 dv,
-// t2 = l2 dv.  `clamp` (uniform): the opacity is above 0.99, so that alpha may be clamped (else
-// G <= 1 keeps it below); two branches past an instruction or two (the whole step compiled
-// for both cases copies the pixel state between them, which costs more than the branches).
+// written; slots 0..4 in whitened coordinates as above), and the pixel's recursion step.  `ok`: the
+// Gaussian contributed to this pixel; t1 = l0 du + l1 dv, t2 = l2 dv.  `clamp` (uniform): the opacity
+// is above 0.99, so that alpha may be clamped (else G <= 1 keeps it below); two branches past an
+// instruction or two (the whole step compiled for both cases copies the pixel state between them,
+// which costs more than the branches).  dL/dalpha is zeroed by a select of its own where the Gaussian
+// does not contribute: the product with alpha = 0 would pass on a NaN of the pixel's upstream gradient.
 template <bool ADD>
 __device__ inline void bwd_pixel_step(BwdPixel& P, bool ok, int clamp, float power, float t1, float t2, const float4& b,
                                       const float4& c, float (&gq)[9]) {
-  const float G = __expf(power);
+  const float G = ok ? __expf(power) : 0.0f;
   const float araw = b.z * G;
-  // alpha = 0 where the Gaussian does not contribute, so everything below is 0 without a select
-  float alpha = ok ? araw : 0.0f;
+  // alpha = 0 where the Gaussian does not contribute, so its weight below is 0 without a select
+  float alpha = araw;
   if (__builtin_expect(opaque(clamp) != 0, 0)) {
     alpha = fminf(alpha, kAlphaMax);
     keep_branch(alpha);
@@ -913,24 +912,20 @@ __device__ inline void bwd_pixel_step(BwdPixel& P, bool ok, int clamp, float pow
   P.T = P.T * inv_om;
   const float wk = alpha * P.T;
   const float dc = fmaf(P.dl0, c.x, fmaf(P.dl1, c.y, P.dl2 * c.z));  // dL/dC . colour
-  // dL/dalpha alpha = (dc T - DS / (1 - alpha)) alpha
-  float dpow = fmaf(-P.DS, alpha * inv_om, dc * wk);
+  float dla = ok ? fmaf(dc, P.T, -P.DS * inv_om) : 0.0f;  // dL/dalpha
   if (__builtin_expect(opaque(clamp) != 0, 0)) {
-    dpow = araw > kAlphaMax ? 0.0f : dpow;  // a clamped alpha does not depend on the inputs
-    keep_branch(dpow);
+    dla = araw > kAlphaMax ? 0.0f : dla;  // a clamped alpha does not depend on the inputs
+    keep_branch(dla);
   }
   P.DS = fmaf(dc, wk, P.DS);
+  const float dpow = dla * alpha;
   const float g0 = dpow * t1, g1 = dpow * t2;
   gq[0] = ADD ? gq[0] + g0 : g0;
   gq[1] = ADD ? gq[1] + g1 : g1;
-  gq[5] = ADD ? gq[5] + dpow : dpow;
-  // the other values are products x_q y_q (fused into the running sums when adding)
-  const float x[6] = {g0, g0, g1, wk, wk, wk}, y[6] = {t1, t2, t2, P.dl0, P.dl1, P.dl2};
+  // values 2..8 are products x_q y_q (fused into the running sums when adding)
+  const float x[7] = {g0, g0, g1, dla, wk, wk, wk}, y[7] = {t1, t2, t2, G, P.dl0, P.dl1, P.dl2};
 #pragma unroll
-  for (int q = 0; q < 6; ++q) {
-    const int k = q < 3 ? 2 + q : 3 + q;
-    gq[k] = ADD ? fmaf(x[q], y[q], gq[k]) : x[q] * y[q];
-  }
+  for (int q = 0; q < 7; ++q) gq[2 + q] = ADD ? fmaf(x[q], y[q], gq[2 + q]) : x[q] * y[q];
 }
 
 // g2d layout: [items][9] = d/du, d/dv, d/dS_uu, d/dS_uv, d/dS_vv, d/dopacity, d/dr, d/dg,
@@ -1089,7 +1084,7 @@ template <int BATCH>
 struct Stage4 {  // (one entry more for reverse_quadrant)
   float4 s0[BATCH + 1];  // u, v, l0, l1
   float4 s1[BATCH + 1];  // l2, p_min, opacity, unused
-  float4 s2[BATCH + 1];  // r, g, b, 1 / opacity
+  float4 s2[BATCH + 1];  // r, g, b, unused
   uint32_t sid[BATCH];
   uint16_t list[BATCH];  // entry index | quadrant mask << 8 | flags << 12
 };
@@ -1145,9 +1140,8 @@ __device__ inline void flush_group(const Stage4<BATCH>& S, const FlushLane& f, f
     const float l0 = a.z, l1 = a.w, l2 = S.s1[t].x;
     // value fq of the record, from the sums S0 .. S8:
     //   0: 2 (l0 S0)   1: 2 (l1 S0 + l2 S1)   2: 2 l0 (l0 S2)   3: 4 l0 (l1 S2 + l2 S3)
-    //   4: 2 l1 (l1 S2 + 2 l2 S3) + 2 l2 (l2 S4)   5: S5 / opacity   6, 7, 8: Sq
-    float x = fq == 5 ? S.s2[t].w : 1.0f, u = fq < 2 ? 2.0f : 1.0f;
-    x = fq < 5 ? l1 : x;
+    //   4: 2 l1 (l1 S2 + 2 l2 S3) + 2 l2 (l2 S4)   5 to 8: Sq
+    float x = fq < 5 ? l1 : 1.0f, u = fq < 2 ? 2.0f : 1.0f;
     x = fq == 0 || fq == 2 ? l0 : x;
     const float y = fq == 4 ? 2.0f * l2 : l2;
     u = fq == 2 ? 2.0f * l0 : u;
@@ -1197,7 +1191,7 @@ __device__ inline void reverse_quadrant(Stage4<BATCH>& S, float* ring, const Flu
       const float reach = fabsf(tcx - r0.x) + 9.0f;
       S.s1[lane] = make_float4(r1.x, r1.z, r1.y, 0.0f);
       S.sid[lane] = item;
-      S.s2[lane] = make_float4(r2.x, r2.y, r2.z, 1.0f / r1.y);
+      S.s2[lane] = make_float4(r2.x, r2.y, r2.z, 0.0f);
       w = 1u | (reach < half ? 0 : kEntryWrap << 4) | (r1.y > kAlphaMax ? kEntryClamp << 4 : 0);
     }
     const uint64_t bl = __builtin_amdgcn_ballot_w64(w != 0u);
@@ -1219,8 +1213,9 @@ __device__ inline void reverse_quadrant(Stage4<BATCH>& S, float* ring, const Flu
       const uint32_t words = lane < m ? S.list[i0 + lane] : NB;
       for (int i = 0; i < m; i += kQuadRunBwd) {
         vec4 a[kQuadRunBwd], b[kQuadRunBwd], c[kQuadRunBwd];
-        float du[kQuadRunBwd], t1[kQuadRunBwd], t2[kQuadRunBwd], araw[kQuadRunBwd], alpha[kQuadRunBwd];
-        float wk[kQuadRunBwd], dpow[kQuadRunBwd];
+        float du[kQuadRunBwd], t1[kQuadRunBwd], t2[kQuadRunBwd], G[kQuadRunBwd], alpha[kQuadRunBwd];
+        float wk[kQuadRunBwd], dla[kQuadRunBwd];
+        bool ok[kQuadRunBwd];
         int k[kQuadRunBwd];
         uint32_t flags = 0;
 #pragma unroll
@@ -1251,9 +1246,9 @@ __device__ inline void reverse_quadrant(Stage4<BATCH>& S, float* ring, const Flu
           t1[j] = fmaf(a[j].z, du[j], a[j].w * dv);
           t2[j] = b[j].x * dv;
           const float p = -fmaf(t1[j], t1[j], t2[j] * t2[j]);
-          const bool ok = end - 1 - k[j] < P.last && !(p < b[j].y);
-          araw[j] = b[j].z * __expf(p);
-          alpha[j] = ok ? araw[j] : 0.0f;
+          ok[j] = end - 1 - k[j] < P.last && !(p < b[j].y);
+          G[j] = ok[j] ? __expf(p) : 0.0f;
+          alpha[j] = b[j].z * G[j];
         }
         const int clamp = (int)(flags >> 12 & kEntryClamp);
         if (__builtin_expect(opaque(clamp) != 0, 0)) {  // uniform
@@ -1269,22 +1264,22 @@ __device__ inline void reverse_quadrant(Stage4<BATCH>& S, float* ring, const Flu
           P.T = P.T * inv_om;
           wk[j] = alpha[j] * P.T;
           const float dc = fmaf(P.dl0, c[j].x, fmaf(P.dl1, c[j].y, P.dl2 * c[j].z));
-          dpow[j] = fmaf(-P.DS, alpha[j] * inv_om, dc * wk[j]);
+          dla[j] = ok[j] ? fmaf(dc, P.T, -P.DS * inv_om) : 0.0f;
           P.DS = fmaf(dc, wk[j], P.DS);
         }
         if (__builtin_expect(opaque(clamp) != 0, 0)) {  // uniform
 #pragma unroll
           for (int j = 0; j < kQuadRunBwd; ++j) {
-            dpow[j] = araw[j] > kAlphaMax ? 0.0f : dpow[j];
-            keep_branch(dpow[j]);
+            dla[j] = b[j].z * G[j] > kAlphaMax ? 0.0f : dla[j];
+            keep_branch(dla[j]);
           }
         }
 #pragma unroll
         for (int j = 0; j < kQuadRunBwd; ++j) {
           if (j > 0 && i + j >= m) break;  // uniform (past an odd group)
-          const float g0 = dpow[j] * t1[j], g1 = dpow[j] * t2[j];
-          float g[9] = {g0,         g1,           g0 * t1[j],   g0 * t2[j],  g1 * t2[j],
-                        dpow[j],    wk[j] * P.dl0, wk[j] * P.dl1, wk[j] * P.dl2};
+          const float dpow = dla[j] * alpha[j], g0 = dpow * t1[j], g1 = dpow * t2[j];
+          float g[9] = {g0,            g1,            g0 * t1[j],    g0 * t2[j],   g1 * t2[j],
+                        dla[j] * G[j], wk[j] * P.dl0, wk[j] * P.dl1, wk[j] * P.dl2};
           quad_reduce9(g);
           out01[(i + j) * kRingStride] = g[0];
           out01[(i + j) * kRingStride + 16] = g[1];
@@ -1379,7 +1374,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 6
             m |= (reach < half ? 0 : kEntryWrap << 4) | (r.r1.y > kAlphaMax ? kEntryClamp << 4 : 0);
             S.s1[e] = make_float4(r.r1.x, r.r1.z, r.r1.y, 0.0f);
             S.sid[e] = item;
-            S.s2[e] = make_float4(r.r2.x, r.r2.y, r.r2.z, 1.0f / r.r1.y);
+            S.s2[e] = r.r2;
           }
         }
         const uint64_t bl = __builtin_amdgcn_ballot_w64(m != 0u);

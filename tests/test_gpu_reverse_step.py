@@ -1,0 +1,58 @@
+"""The reverse compositors' step at one pixel: the opacity gradient where every operation is exact, and a
+NaN of one pixel's upstream gradient, which belongs to the Gaussians that reach the pixel."""
+import numpy as np
+import pytest
+
+from paper_2410_20686_amd import scenes
+from tests import _gpu as G
+from tests._util import make_scene, settings
+
+pytestmark = pytest.mark.gpu
+
+W, H = 128, 64
+
+
+def _scene(u, v, opacity, scale, radius=2.0):
+    """Gaussians centred on the pixel positions (u, v) of the identity camera's W x H panorama."""
+    u, v = np.atleast_1d(u).astype(float), np.atleast_1d(v).astype(float)
+    phi, theta = (u - W / 2) * 2 * np.pi / W, (H / 2 - v) * np.pi / H
+    r = np.broadcast_to(radius, u.shape)
+    means = np.stack([np.cos(theta) * np.sin(phi), -np.sin(theta), np.cos(theta) * np.cos(phi)], 1) * r[:, None]
+    sh = np.random.default_rng(3).uniform(-1.0, 1.0, (3, len(u)))
+    return make_scene(means, scale * r[:, None] * np.ones(3), opac=np.broadcast_to(opacity, u.shape), sh=sh, dtype=np.float32)
+
+
+def _g2d(sc, st, dL):
+    res = G.run_gpu(sc, scenes.identity_cameras(W, H), st, dL=dL, return_rast=True, split_bwd=True)
+    return res["g2d"][0], res["rast"].records().cpu().numpy()
+
+
+@pytest.mark.parametrize("schedule", ["queue", "tile_id"])
+@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("opacity", [0.75, 0.875, 0.9375])
+def test_opacity_gradient_is_exact(tile, schedule, opacity):
+    """One Gaussian centred on a pixel, upstream gradient (1, 0, 0) there: G = 1, 1 - alpha and its
+    reciprocal are powers of two and T = 1, so dL/dopacity is the Gaussian's red, unrounded."""
+    dL = np.zeros((3, H, W), np.float32)
+    dL[0, 32, 64] = 1.0
+    g, rec = _g2d(_scene(64.5, 32.5, opacity, 0.02), settings(tile=tile, schedule=schedule), dL.ravel())
+    assert rec[0, 0] == 64.5 and rec[0, 1] == 32.5 and rec[0, 8] != 0.0
+    assert g[0, 5] == float(rec[0, 8])
+
+
+@pytest.mark.parametrize("schedule", ["queue", "tile_id"])
+@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("far", [0, 1])
+def test_nan_upstream_stays_with_its_pixel(tile, schedule, far):
+    """Two Gaussians in one 8x8 block of pixels, the upstream gradient NaN at the first one's centre, which
+    the second does not reach: its position, shape and opacity gradients are those of a zero there."""
+    sc = _scene([66.5, 70.5], [34.5, 38.5], 0.5, 0.02, radius=np.array([2.0, 2.5] if far else [2.5, 2.0]))
+    dL = np.random.default_rng(5).standard_normal((3, H, W)).astype(np.float32)
+    st = settings(tile=tile, schedule=schedule)
+    dL[:, 34, 66] = 0.0
+    want, _ = _g2d(sc, st, dL.ravel())
+    dL[:, 34, 66] = np.nan
+    got, _ = _g2d(sc, st, dL.ravel())
+    assert np.isnan(got[0, :6]).any()
+    np.testing.assert_array_equal(got[1, :6], want[1, :6])
+    assert (want[1, :6] != 0.0).all()
