@@ -873,29 +873,23 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
         if (fe < m) {
           const int t = S.list[i0 + fe] & 0xFF;
           const float4 a = S.s0[t], b = S.s1[t], c = S.s2[t];
-          // record value fq as x^T Y y, Y the symmetric matrix of the six sums from fsum on: a Sigma~
-          // entry (i, j) takes columns i and j of N; a mu^ component i its column and (1, 0, 0),
-          // with (S_y1, S_y2, S_y3) for Y's first row; the others (1, 0, 0) twice
+          // record value fq: a Sigma~ entry (i, j) is x^T Y y with columns i and j of N, Y the symmetric
+          // matrix of the six sums from fsum on; a mu^ component i its column times the three sums from
+          // fsum on; the others their sum.  What a value does not take is dropped by selects: the six words
+          // from fsum on may be another entry's, or an earlier group's, and need not be finite.
           const int ci = fq < 3 ? fq : (fq >= 6) + (fq >= 8), cj = fq == 3 ? 0 : (fq == 4 || fq == 6 ? 1 : 2);
           float x0, x1, x2, y0, y1, y2;
           sph_ncol(ci, a, b, c, x0, x1, x2);
           sph_ncol(cj, a, b, c, y0, y1, y2);
           const bool vec = fq < 3, plain = fq >= 9;
-          x0 = plain ? 1.0f : x0;
-          x1 = plain ? 0.0f : x1;
-          x2 = plain ? 0.0f : x2;
-          y0 = vec || plain ? 1.0f : y0;
-          y1 = vec || plain ? 0.0f : y1;
-          y2 = vec || plain ? 0.0f : y2;
-          float scale = fq == 3 || fq == 6 || fq == 8 || vec ? 2.0f : 4.0f;
-          scale = plain ? 1.0f : scale;
-          scale = fq == 9 ? S.s3[t].w : scale;
+          const float scale = fq == 3 || fq == 6 || fq == 8 || vec ? 2.0f : 4.0f;
           const double Y0 = fsum[0], Y1 = fsum[1], Y2 = fsum[2], Y3 = fsum[3], Y4 = fsum[4], Y5 = fsum[5];
           const double e0 = y0, e1 = y1, e2 = y2;
-          const double m0 = fma(Y0, e0, fma(Y1, e1, Y2 * e2));
-          const double m1 = fma(Y1, e0, fma(Y3, e1, Y4 * e2));
-          const double m2 = fma(Y2, e0, fma(Y4, e1, Y5 * e2));
-          const double v = (double)scale * fma((double)x0, m0, fma((double)x1, m1, (double)x2 * m2));
+          const double m0 = vec ? Y0 : fma(Y0, e0, fma(Y1, e1, Y2 * e2));
+          const double m1 = vec ? Y1 : fma(Y1, e0, fma(Y3, e1, Y4 * e2));
+          const double m2 = vec ? Y2 : fma(Y2, e0, fma(Y4, e1, Y5 * e2));
+          const double own = fq == 9 ? Y0 * (double)S.s3[t].w : Y0;
+          const double v = plain ? own : (double)scale * fma((double)x0, m0, fma((double)x1, m1, (double)x2 * m2));
           if (v != 0.0) unsafeAtomicAdd(&g2d[(int64_t)S.sid[t] * kNV + fq], v);
         }
         __syncthreads();

@@ -56,3 +56,23 @@ def test_nan_upstream_stays_with_its_pixel(tile, schedule, far):
     assert np.isnan(got[0, :6]).any()
     np.testing.assert_array_equal(got[1, :6], want[1, :6])
     assert (want[1, :6] != 0.0).all()
+
+
+@pytest.mark.parametrize("schedule", ["queue", "persistent", "tile_id"])
+@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("footprint", ["affine", "spherical"])
+def test_nan_upstream_stays_in_its_block(footprint, tile, schedule):
+    """Five Gaussians in two 8x8 blocks of a tile, in turn by depth, the upstream gradient NaN at a pixel
+    of the first block: every gradient of those in the second is that of a zero there."""
+    at = np.array([66.5, 74.5, 66.5, 74.5, 66.5])
+    sc = _scene(at, np.full(5, 34.5), 0.4, 0.02, radius=np.linspace(2.0, 3.0, 5))
+    dL = np.random.default_rng(6).standard_normal((3, H, W)).astype(np.float32)
+    st = settings(tile=tile, schedule=schedule, footprint=footprint)
+    dL[:, 34, 66] = 0.0
+    want, _ = _g2d(sc, st, dL.ravel())
+    dL[:, 34, 66] = np.nan
+    got, _ = _g2d(sc, st, dL.ravel())
+    second = at == 74.5
+    assert np.isnan(got[~second]).all()
+    np.testing.assert_array_equal(got[second], want[second])
+    assert (want[second] != 0.0).all()
