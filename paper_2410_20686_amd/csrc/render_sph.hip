@@ -785,7 +785,7 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
             S.s0[e] = r.s0;
             S.s1[e] = r.s1;
             S.s2[e] = r.s2;
-            S.s3[e] = make_float4(r.s3.x, r.s3.y, r.s3.z, 1.0f / r.s2.z);
+            S.s3[e] = r.s3;
             S.sid[e] = item;
             if (r.s2.z > kAlphaMax) m |= kEntryClamp << 4;
           }
@@ -813,13 +813,14 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
             if (!((mq >> q) & 1u) || jrel >= qmax[q]) continue;  // uniform
             float inv_D, t1, t2, h, D, qh;
             // evaluated on every lane (no short circuit): the gradient terms below are formed on
-            // all lanes and are zero where alpha is, which needs finite operands
+            // all lanes and zeroed by selects
             const bool hit = sph_eval(a, b, c, d[q], t1, t2, h, D, qh);
             const bool ok = jrel < last[q] && hit;
             if (__builtin_amdgcn_ballot_w64(ok) == 0ull) continue;  // uniform
-            const float araw = c.z * __expf(sph_power(qh, D, inv_D));
+            const float G = ok ? __expf(sph_power(qh, D, inv_D)) : 0.0f;
+            const float araw = c.z * G;
             // alpha = 0 where the Gaussian does not contribute, so its weight below is 0 without a select
-            float alpha = ok ? araw : 0.0f;
+            float alpha = araw;
             if (__builtin_expect(opaque((int)(mq & (kEntryClamp << 4))) != 0, 0)) {
               alpha = fminf(alpha, kAlphaMax);
               keep_branch(alpha);
@@ -828,13 +829,14 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
             T[q] = T[q] * inv_om;  // transmittance in front of this Gaussian (alpha = 0: times exactly 1)
             const float wk = alpha * T[q];
             const float dc = fmaf(dl0[q], col.x, fmaf(dl1[q], col.y, dl2[q] * col.z));  // dL/dC . colour
-            // dL/dalpha alpha = (dc T - DS / (1 - alpha)) alpha
-            float dpow = fmaf(-DS[q], alpha * inv_om, dc * wk);
+            // dL/dalpha (a select of its own: the pixel's upstream gradient may be NaN)
+            float dla = ok ? fmaf(dc, T[q], -DS[q] * inv_om) : 0.0f;
             if (__builtin_expect(opaque((int)(mq & (kEntryClamp << 4))) != 0, 0)) {
-              dpow = araw > kAlphaMax ? 0.0f : dpow;  // a clamped alpha does not depend on the inputs
-              keep_branch(dpow);
+              dla = araw > kAlphaMax ? 0.0f : dla;  // a clamped alpha does not depend on the inputs
+              keep_branch(dla);
             }
             DS[q] = fmaf(dc, wk, DS[q]);
+            const float dpow = dla * alpha;
             // whitened offset y = (h t1, h t2, qh) / D, zero on lanes that do not contribute
             const float s1 = ok ? inv_D : 0.0f, s1h = s1 * h;
             const float y1 = s1h * t1, y2 = s1h * t2, y3 = s1 * qh;
@@ -848,7 +850,7 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
             gv[6] = fmaf(gy, y2, gv[6]);
             gv[7] = fmaf(gy, y3, gv[7]);
             gv[8] = fmaf(gz, y3, gv[8]);
-            gv[9] += dpow;  // the opacity gradient times the opacity
+            gv[9] = fmaf(dla, G, gv[9]);
             gv[10] = fmaf(wk, dl0[q], gv[10]);
             gv[11] = fmaf(wk, dl1[q], gv[11]);
             gv[12] = fmaf(wk, dl2[q], gv[12]);
@@ -888,8 +890,7 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
           const double m0 = vec ? Y0 : fma(Y0, e0, fma(Y1, e1, Y2 * e2));
           const double m1 = vec ? Y1 : fma(Y1, e0, fma(Y3, e1, Y4 * e2));
           const double m2 = vec ? Y2 : fma(Y2, e0, fma(Y4, e1, Y5 * e2));
-          const double own = fq == 9 ? Y0 * (double)S.s3[t].w : Y0;
-          const double v = plain ? own : (double)scale * fma((double)x0, m0, fma((double)x1, m1, (double)x2 * m2));
+          const double v = plain ? Y0 : (double)scale * fma((double)x0, m0, fma((double)x1, m1, (double)x2 * m2));
           if (v != 0.0) unsafeAtomicAdd(&g2d[(int64_t)S.sid[t] * kNV + fq], v);
         }
         __syncthreads();

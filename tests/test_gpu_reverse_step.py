@@ -30,32 +30,35 @@ def _g2d(sc, st, dL):
 @pytest.mark.parametrize("schedule", ["queue", "tile_id"])
 @pytest.mark.parametrize("tile", [8, 16, 32])
 @pytest.mark.parametrize("opacity", [0.75, 0.875, 0.9375])
-def test_opacity_gradient_is_exact(tile, schedule, opacity):
+@pytest.mark.parametrize("footprint,slot", [("affine", 5), ("spherical", 9)])
+def test_opacity_gradient_is_exact(footprint, slot, tile, schedule, opacity):
     """One Gaussian centred on a pixel, upstream gradient (1, 0, 0) there: G = 1, 1 - alpha and its
     reciprocal are powers of two and T = 1, so dL/dopacity is the Gaussian's red, unrounded."""
     dL = np.zeros((3, H, W), np.float32)
     dL[0, 32, 64] = 1.0
-    g, rec = _g2d(_scene(64.5, 32.5, opacity, 0.02), settings(tile=tile, schedule=schedule), dL.ravel())
+    st = settings(tile=tile, schedule=schedule, footprint=footprint)
+    g, rec = _g2d(_scene(64.5, 32.5, opacity, 0.02), st, dL.ravel())
     assert rec[0, 0] == 64.5 and rec[0, 1] == 32.5 and rec[0, 8] != 0.0
-    assert g[0, 5] == float(rec[0, 8])
+    assert g[0, slot] == float(rec[0, 8])
 
 
 @pytest.mark.parametrize("schedule", ["queue", "tile_id"])
 @pytest.mark.parametrize("tile", [8, 16, 32])
 @pytest.mark.parametrize("far", [0, 1])
-def test_nan_upstream_stays_with_its_pixel(tile, schedule, far):
+@pytest.mark.parametrize("footprint,colour", [("affine", 6), ("spherical", 10)])
+def test_nan_upstream_stays_with_its_pixel(footprint, colour, tile, schedule, far):
     """Two Gaussians in one 8x8 block of pixels, the upstream gradient NaN at the first one's centre, which
     the second does not reach: its position, shape and opacity gradients are those of a zero there."""
     sc = _scene([66.5, 70.5], [34.5, 38.5], 0.5, 0.02, radius=np.array([2.0, 2.5] if far else [2.5, 2.0]))
     dL = np.random.default_rng(5).standard_normal((3, H, W)).astype(np.float32)
-    st = settings(tile=tile, schedule=schedule)
+    st = settings(tile=tile, schedule=schedule, footprint=footprint)
     dL[:, 34, 66] = 0.0
     want, _ = _g2d(sc, st, dL.ravel())
     dL[:, 34, 66] = np.nan
     got, _ = _g2d(sc, st, dL.ravel())
-    assert np.isnan(got[0, :6]).any()
-    np.testing.assert_array_equal(got[1, :6], want[1, :6])
-    assert (want[1, :6] != 0.0).all()
+    assert np.isnan(got[0, :colour]).any()
+    np.testing.assert_array_equal(got[1, :colour], want[1, :colour])
+    assert (want[1, :colour] != 0.0).all()
 
 
 @pytest.mark.parametrize("schedule", ["queue", "persistent", "tile_id"])
