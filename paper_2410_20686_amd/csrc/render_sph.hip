@@ -197,7 +197,10 @@ __device__ inline bool sph_eval(const float4& a, const float4& b, const float4& 
 // the hardware reciprocal and on the quotient with fused residuals.  The scaling that a general division
 // adds serves quotients near the ends of the float range; here qh <= -p_min D (below 6 D) with D
 // the square of a direction component, and a quotient small enough to lose bits has an exponential of 1.
+// D is clamped to the normal range, where the residuals are finite: it overflows for a Gaussian drawn out
+// along its own ray, whose exponent is zero there.  A ray that is not reached may get a NaN.
 __device__ inline float sph_power(float qh, float D, float& inv_D) {
+  D = __builtin_amdgcn_fmed3f(D, __FLT_MIN__, __FLT_MAX__);
   float r = __builtin_amdgcn_rcpf(D);
   r = fmaf(fmaf(-D, r, 1.0f), r, r);
   float q = qh * r;
@@ -478,16 +481,15 @@ __global__ __launch_bounds__(TILE* TILE) void render_sph_bwd_kernel(
         const float4 a = S.s0[k], b = S.s1[k], c = S.s2[k];
         float inv_D, t1, t2, h, D, qh;
         // evaluated on every lane (no short circuit): the gradient terms below are formed on all
-        // lanes and zeroed by selects, which needs finite operands
+        // lanes and zeroed by selects
         const bool hit = sph_eval(a, b, c, d, t1, t2, h, D, qh);
         const bool ok = jrel < last && hit;
         if (__builtin_amdgcn_ballot_w64(ok) == 0ull) continue;  // uniform
-        const float power = sph_power(qh, D, inv_D);
-        const float G = __expf(power);
+        const float G = ok ? __expf(sph_power(qh, D, inv_D)) : 0.0f;
         const float araw = c.z * G;
         const bool live = ok && !(araw > kAlphaMax);  // contributes and unclamped
         // alpha = 0 where the Gaussian does not contribute, so its weight below is 0 without a select
-        const float alpha = ok ? fminf(araw, kAlphaMax) : 0.0f;
+        const float alpha = fminf(araw, kAlphaMax);
         const float inv_om = __builtin_amdgcn_rcpf(1.0f - alpha);
         T = T * inv_om;  // transmittance in front of this Gaussian (alpha = 0: times exactly 1)
         const float wk = alpha * T;

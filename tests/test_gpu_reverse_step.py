@@ -79,3 +79,23 @@ def test_nan_upstream_stays_in_its_block(footprint, tile, schedule):
     assert np.isnan(got[~second]).all()
     np.testing.assert_array_equal(got[second], want[second])
     assert (want[second] != 0.0).all()
+
+
+@pytest.mark.parametrize("tile", [8, 16, 32])
+def test_spherical_denominator_past_the_float_range(tile):
+    """A Gaussian drawn out along its own viewing ray until the exponent's denominator D overflows: the
+    exponent's limit is zero, as dividing by infinity gives, so its opacity covers its hemisphere."""
+    from oracle import oracle as O
+    sc = make_scene([[0.0, 0.0, 2.0], [0.3, 0.1, 3.0]], [[0.02, 0.02, 1e19], [0.1, 0.1, 0.1]], opac=[0.5, 0.6],
+                    sh=np.random.default_rng(8).uniform(-1.0, 1.0, (3, 2)), dtype=np.float32)
+    cams, st = scenes.identity_cameras(W, H), settings(tile=tile, footprint="spherical")
+    fwd = O.render(sc, cams, st, mode=32)
+    dL = np.random.default_rng(9).standard_normal((3, H, W)).astype(np.float32)
+    res = G.run_gpu(sc, cams, st, dL=dL.ravel(), split_bwd=True)
+    T = res["T"].reshape(H, W)
+    assert T[2, 64] == 0.5 and T[32, 34] == 0.5 and T[32, 0] == 1.0
+    np.testing.assert_allclose(res["T"], fwd["T"], rtol=0, atol=G.RGB_ATOL)
+    np.testing.assert_allclose(res["rgb"], fwd["rgb"], rtol=0, atol=G.RGB_ATOL)
+    assert np.isfinite(res["g2d"]).all()
+    ref = O.backward(sc, cams, st, dL.ravel(), mode=32, want_g2d=True)["g2d_kernel"]
+    G.assert_grads_close({"opacity": res["g2d"][..., 9]}, {"opacity": ref[..., 9]}, names=("opacity",))
