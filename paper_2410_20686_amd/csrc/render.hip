@@ -615,7 +615,6 @@ __device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, 
           hit |= bit_if(__builtin_amdgcn_ballot_w64(ok[j]), j);
         }
         if (hit == 0) continue;  // uniform
-        used |= (uint64_t)(uint32_t)hit << i0;
         if (__builtin_expect(opaque((int)(flags >> 12 & kEntryClamp)), 0)) {  // uniform
 #pragma unroll
           for (int j = 0; j < kQuadRun; ++j) {
@@ -628,15 +627,19 @@ __device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, 
         for (int j = 0; j < kQuadRun; ++j) t[j + 1] = t[j] * (1.0f - alpha[j]);
         // T never rises, so a pixel stops within the run only if its last product is below the threshold
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(t[kQuadRun] < kTStop) != 0ull, 0)) {
-          // entry by entry: a pixel stops at the entry that would take T below 1e-4, without it
+          // entry by entry: a pixel stops at the entry that would take T below 1e-4, without it.  An entry
+          // at which all the pixels it reaches stop is none of the backward's, which evaluates runs whole.
+          hit = 0;
 #pragma unroll
           for (int j = 0; j < kQuadRun; ++j) {
             qstop = t[j] * (1.0f - alpha[j]) < kTStop ? __builtin_nanf("") : qstop;
             ok[j] = ok[j] && qstop == 0.0f;
+            hit |= bit_if(__builtin_amdgcn_ballot_w64(ok[j]), j);
             alpha[j] = ok[j] ? alpha[j] : 0.0f;
             t[j + 1] = t[j] * (1.0f - alpha[j]);
           }
         }
+        used |= (uint64_t)(uint32_t)hit << i0;
         T = t[kQuadRun];
         float c[kQuadRun][3], d[kQuadRun];
 #pragma unroll
@@ -659,7 +662,7 @@ __device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, 
       }
       if (lane < n) S.used[words & 0xFFu] = (uint8_t)((used >> lane & 1u) << q);
       __syncthreads();
-      // the backward's masks for this batch: whether some pixel reached each entry
+      // the backward's masks for this batch: whether each entry contributed to some pixel
       if constexpr (BIN == 32) {
         const uint64_t reached = __builtin_amdgcn_ballot_w64(lane < cnt && S.used[lane] != 0);
         if (8 * lane < cnt) qm[((base - rg.x) >> 3) + lane] = (uint8_t)(reached >> (8 * lane));

@@ -111,3 +111,20 @@ def test_long_lists_of_32_pixel_tiles(n, opacity, batch):
         for k in ("rgb", "T", "depth"):
             np.testing.assert_array_equal(res[k], base[k])
         G.assert_grads_close(res, base, names=("g2d",), rtol=1e-6, floor=1e-9)
+
+
+@pytest.mark.parametrize("schedule", ["queue", "tile_id"])
+def test_entry_that_only_stops_pixels_gets_no_gradient(schedule):
+    """The third of three footprints on one pixel reaches only that pixel, which stops at it; a fourth lies
+    behind.  The upstream gradient is NaN elsewhere in the 8x8 block: none of it may reach the third, which
+    contributes to no pixel."""
+    from tests.test_gpu_reverse_step import H, W, _g2d, _scene
+    sc = _scene([66.5, 66.5, 66.5, 70.5], [34.5, 34.5, 34.5, 36.5], [0.999, 0.98997, 0.008, 0.5], 1e-3,
+                radius=np.array([2.0, 2.2, 2.4, 2.6]))
+    dL = np.random.default_rng(4).standard_normal((3, H, W)).astype(np.float32)
+    dL[:, 38, 65] = np.nan
+    T = G.run_gpu(sc, scenes.identity_cameras(W, H), settings(tile=16, schedule=schedule))["T"].reshape(H, W)
+    assert 1e-4 <= T[34, 66] < 1.008e-4 and T[38, 65] == 1.0
+    g, _ = _g2d(sc, settings(tile=16, schedule=schedule), dL.ravel())
+    assert (g[2] == 0.0).all()
+    assert (g[[0, 1, 3]][:, 5] != 0.0).all()
