@@ -500,6 +500,13 @@ __device__ inline int bit_if(uint64_t mask, int j) {
   return x;
 }
 
+// Zero, formed where it is used: no register holds it before.
+__device__ inline float zero_here() {
+  float x;
+  asm volatile("v_mov_b32 %0, 0" : "=v"(x));
+  return x;
+}
+
 __device__ inline vec4 as_vec4(const float4& f) { return vec4{f.x, f.y, f.z, f.w}; }
 
 // One quadrant of a split tile, one pixel per lane.  A split tile's list is long against the launch, so
@@ -564,7 +571,8 @@ __device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, 
         const Rec r{make_float4(r0.x, r0.y, r0.z, r0.w), make_float4(r1.x, r1.y, r1.z, r1.w),
                     make_float4(r2.x, r2.y, r2.z, r2.w)};
         m = quadrant_mask<8>(r, tx0 + 8 * (q & 1), ty0 + 8 * (q >> 1), Wf, half);
-        if (m != 0u) m |= (reach < half ? 0 : kEntryWrap << 4) | (r1.y > kAlphaMax ? kEntryClamp << 4 : 0);
+        const bool rare = r1.y > kAlphaMax || fmaxf(fmaxf(r2.x, r2.y), r2.z) == __builtin_inff();
+        if (m != 0u) m |= (reach < half ? 0 : kEntryWrap << 4) | (rare ? kEntryClamp << 4 : 0);
       }
       const uint64_t bl = __builtin_amdgcn_ballot_w64(m != 0u);
       if (m != 0u) S.list[bits_below(bl)] = (uint16_t)(lane | (m << 8));
@@ -616,10 +624,13 @@ __device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, 
         }
         if (hit == 0) continue;  // uniform
         if (__builtin_expect(opaque((int)(flags >> 12 & kEntryClamp)), 0)) {  // uniform
+          const float zero = zero_here();
 #pragma unroll
           for (int j = 0; j < kQuadRun; ++j) {
             alpha[j] = fminf(alpha[j], kAlphaMax);
             keep_branch(alpha[j]);
+            // an entry that reaches no pixel: its colour, times a weight of zero, may be infinite
+            if ((hit >> j & 1) == 0) S.s2[at[j]].x = S.s2[at[j]].y = S.s2[at[j]].z = zero;
           }
         }
         t[0] = T;

@@ -30,7 +30,7 @@ __device__ inline float sum_rows(float x) {
 
 // Flags of a staged entry in the one-wavefront compositors (above the quadrant mask).
 constexpr int kEntryWrap = 1;   // some pixel centre of the tile may need the seam wrap
-constexpr int kEntryClamp = 2;  // opacity above 0.99: alpha may be clamped
+constexpr int kEntryClamp = 2;  // opacity above 0.99: alpha may be clamped (in composite_quadrant also: infinite colour)
 
 // A uniform word the compiler cannot relate to its other uses, so that a test of it stays a scalar
 // test beside its branch.

@@ -128,3 +128,27 @@ def test_entry_that_only_stops_pixels_gets_no_gradient(schedule):
     g, _ = _g2d(sc, settings(tile=16, schedule=schedule), dL.ravel())
     assert (g[2] == 0.0).all()
     assert (g[[0, 1, 3]][:, 5] != 0.0).all()
+
+
+@pytest.mark.parametrize("schedule", ["queue", "tile_id"])
+def test_infinite_colour_that_reaches_no_pixel(schedule):
+    """Faint footprints between the pixel centres of an 8x8 block, among others that cover it: they are in
+    its list but reach no pixel, so the image is that of the others, whatever their colours (here past the
+    float range)."""
+    n, m = 6, 32
+    u, v = np.r_[np.full(n, 67.3), np.full(m, 68.0)], np.r_[np.full(n, 35.6), np.full(m, 36.0)]
+    from tests.test_gpu_reverse_step import H, W, _scene
+    sc = _scene(u, v, np.r_[np.full(n, 0.3), np.full(m, 0.0045)], np.r_[np.full(n, 0.2), np.full(m, 1e-3)][:, None],
+                radius=np.r_[np.linspace(2.0, 3.0, n), np.linspace(1.9, 3.1, m)])
+    rng = np.random.default_rng(12)
+    sh = 0.3 * rng.standard_normal((48, n + m)).astype(np.float32)
+    sh[:, n:] = np.float32(3e38) * rng.choice([-1.0, 1.0], (48, m))
+    sc = scenes.Scene(sc.means, sc.scales, sc.quats, sc.opacities, sh, 3)
+    cams, st = scenes.identity_cameras(W, H), settings(tile=16, schedule=schedule)
+    res = G.run_gpu(sc, cams, st, return_rast=True)
+    colour = res["rast"].records()[n:, 8:11].cpu().numpy()
+    assert np.isinf(colour).any()
+    only = G.run_gpu(sc.subset(np.arange(n)), cams, st)
+    np.testing.assert_array_equal(res["rgb"], only["rgb"])
+    np.testing.assert_array_equal(res["T"], only["T"])
+    assert only["T"].reshape(H, W)[36, 68] < 0.9
