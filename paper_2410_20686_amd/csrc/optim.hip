@@ -81,6 +81,7 @@ struct AdamArray {
 };
 constexpr int kAdamArrays = 5;
 constexpr int kAdamThreads = 256;
+constexpr int kAdamBlock = 4 * kAdamThreads;  // elements
 struct AdamTable {
   AdamArray a[kAdamArrays];
 };
@@ -105,6 +106,7 @@ __device__ inline void adam_element(float& raw, float& act, float grad, float& m
   act = ACT == kExp ? expf(p) : (ACT == kSigmoid ? 1.0f / (1.0f + expf(-p)) : p);
 }
 
+// Four elements of an array: neighbours from i on with VEC, else i and every kAdamThreads-th after it.
 template <int ACT, bool VEC>
 __device__ inline void adam_block(const AdamArray& q, int64_t i, const AdamRates& rates, const AdamArgs& a) {
   if (VEC && i + 4 <= q.count) {
@@ -122,8 +124,7 @@ __device__ inline void adam_block(const AdamArray& q, int64_t i, const AdamRates
     *reinterpret_cast<float4*>(q.act + i) = act;
     return;
   }
-  const int64_t end = VEC ? min(i + 4, q.count) : min(i + 1, q.count);
-  for (; i < end; ++i) {
+  for (int e = 0; e < 4 && i < q.count; ++e, i += VEC ? 1 : kAdamThreads) {
     float raw = q.raw[i], act = ACT != kIdentity ? q.act[i] : 0.0f, m = q.m[i], v = q.v[i];
     adam_element<ACT>(raw, act, q.grad[i], m, v, i < q.split ? rates.r0 : rates.r1, rates.root2, a);
     q.raw[i] = raw;
@@ -139,9 +140,10 @@ __device__ inline void adam_block(const AdamArray& q, int64_t i, const AdamRates
 // value rewritten for the next forward pass.  The step count is read on the device.
 //
 // Bound by HBM: 32 bytes per element.  One launch over the five arrays; one thread per block raises the
-// betas to the step's power, and with VEC (arrays 16-byte aligned) a thread takes four elements: 72 us for
-// 14.75M elements (250k Gaussians at SH degree 3), 130 us in five launches of one element per thread, each
-// raising the betas for itself.
+// betas to the step's power, and a thread takes four elements, in words of 16 bytes with VEC (arrays so
+// aligned): 72 us for 14.75M elements (250k Gaussians at SH degree 3), 130 us in five launches of one element
+// per thread, each raising the betas for itself.  (One element per thread in one launch would also pass the
+// 2^32 threads of a launch from 73M Gaussians on, which five launches took.)
 template <bool VEC>
 __global__ __launch_bounds__(kAdamThreads) void adam_kernel(AdamTable table, const float* __restrict__ lr,
                                                             const int32_t* __restrict__ step, AdamArgs a) {
@@ -156,7 +158,7 @@ __global__ __launch_bounds__(kAdamThreads) void adam_kernel(AdamTable table, con
     rates = AdamRates{lr[q.g0] / bc1, lr[q.g1] / bc1, sqrtf(bc2)};
   }
   __syncthreads();
-  const int64_t i = ((int64_t)(blockIdx.x - q.block0) * kAdamThreads + threadIdx.x) * (VEC ? 4 : 1);
+  const int64_t i = (int64_t)(blockIdx.x - q.block0) * kAdamBlock + threadIdx.x * (VEC ? 4 : 1);
   if (q.kind == kExp)
     adam_block<kExp, VEC>(q, i, rates, a);
   else if (q.kind == kSigmoid)
@@ -241,11 +243,10 @@ hipError_t launch_adam_step(int64_t n, int32_t sh_degree, const odgs_param_ptrs&
     low |= reinterpret_cast<uintptr_t>(q.raw) | reinterpret_cast<uintptr_t>(q.act) | reinterpret_cast<uintptr_t>(q.grad) |
            reinterpret_cast<uintptr_t>(q.m) | reinterpret_cast<uintptr_t>(q.v);
   const bool vec = (low & 15) == 0;
-  const int64_t per_block = kAdamThreads * (vec ? 4 : 1);
   int64_t blocks = 0;
   for (AdamArray& q : t.a) {
     q.block0 = (uint32_t)blocks;
-    blocks += (q.count + per_block - 1) / per_block;
+    blocks += (q.count + kAdamBlock - 1) / kAdamBlock;
   }
   if (blocks > 0) {
     if (vec)
