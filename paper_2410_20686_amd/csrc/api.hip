@@ -100,7 +100,7 @@ int odgs_plan_init(odgs_plan* plan, int64_t n, int32_t sh_degree, int32_t n_view
     plan->pix_base[v] = pixels;
     tiles += (int64_t)(W / st.tile) * (H / st.tile);
     pixels += (int64_t)W * H;
-    // up to four compositing tasks per tile must fit a launch grid
+    // four compositing tasks per tile must fit an int (fine_tile_cap bounds the tiles that take more)
     if (tiles >= (int64_t(1) << 29) || pixels >= (int64_t(1) << 40)) return ODGS_EINVAL;
   }
   plan->tile_base[n_views] = (int32_t)tiles;

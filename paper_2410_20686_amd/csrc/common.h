@@ -100,7 +100,8 @@ struct TileSched {
   int32_t fine_cap;       // with split_all: most tiles in sixteen tasks
 };
 
-// Upper bound of the task count of a launch (its grid without a persistent launch).
+// Upper bound of the task count of a launch (its grid without a persistent launch); at most 4 tiles, or
+// below 2^26 (fine_tile_cap), and so an int for every plan.
 inline int sched_tasks(const TileSched& s) { return s.tiles + 3 * s.split_cap + 12 * s.fine_cap; }
 
 // Next task of this workgroup (uniform): returns its tile and sets `sel` to the part it covers

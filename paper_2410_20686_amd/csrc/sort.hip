@@ -1404,7 +1404,12 @@ TileSched make_sched(const odgs_plan* p, void* ws, int which) {
   return s;
 }
 
-int fine_tile_cap(int tiles) { return std::min(tiles, std::max(kFineCapMin, tiles / 8)); }
+// A launch holds fewer than 2^32 threads, so fewer than 2^26 tasks of a wavefront each: with four per tile
+// counted, what is left of them bounds the tiles that may take twelve more (from 12.2M tiles on).
+int fine_tile_cap(int tiles) {
+  const int64_t room = ((int64_t(1) << 26) - 1 - 4 * (int64_t)tiles) / 12;
+  return (int)std::min<int64_t>(std::min(tiles, std::max(kFineCapMin, tiles / 8)), std::max<int64_t>(room, 0));
+}
 int split_tile_cap(int tiles) { return tiles < kSplitCapMin ? tiles : std::max(kSplitCapMin, tiles / 8); }
 
 int sched_grid(const TileSched& s, int per_cu) {
