@@ -152,3 +152,26 @@ def test_infinite_colour_that_reaches_no_pixel(schedule):
     np.testing.assert_array_equal(res["rgb"], only["rgb"])
     np.testing.assert_array_equal(res["T"], only["T"])
     assert only["T"].reshape(H, W)[36, 68] < 0.9
+
+
+@pytest.mark.parametrize("batch,batch_bwd", [(64, 64), (64, 128), (256, 64)])
+@pytest.mark.parametrize("opacity", [0.02, 0.6])
+def test_more_long_lists_than_sixteen_task_tiles(opacity, batch, batch_bwd):
+    """Four views of 512x256 at 32x32 tiles whose 512 lists are nearly all long: the first 256 of the queue
+    take sixteen tasks each, the others four, forward and reverse staging batches of their own."""
+    sc = scenes.sphere_scene(1301, 0, seed=21)
+    sc.scales[:] = np.float32(2.0) * np.linalg.norm(sc.means, axis=0)[None] * np.linspace(0.2, 2.0, 1301)
+    sc.opacities[:] = np.float32(opacity)
+    cams = scenes.yaw_cameras(4, 512, 256, seed=21)
+    st = settings(tile=32, batch=batch, batch_bwd=batch_bwd)
+    dL = scenes.upstream_gradient(cams, seed=7)
+    base = _run(sc, cams, dict(st, schedule="tile_id"), dL)
+    assert len(base["lengths"]) == 512 and base["header"][9] == 0
+    fine = int((_bucket(base["lengths"]) >= _bucket(1024)).sum())
+    assert 256 < fine
+    for s in ("queue", "persistent"):
+        res = _run(sc, cams, dict(st, schedule=s), dL)
+        assert res["header"][8] == fine and res["header"][9] == 256
+        for k in ("rgb", "T", "depth"):
+            np.testing.assert_array_equal(res[k], base[k])
+        G.assert_grads_close(res, base, names=("g2d",), rtol=1e-6, floor=1e-9)
