@@ -146,7 +146,7 @@ typedef struct odgs_plan {
   int64_t items;           /* n * n_views (Gaussian, view) items, item id = view * n + gaussian */
   int64_t pair_capacity;   /* maximum Gaussian-tile pairs the workspace holds */
   int32_t tile_bits;       /* significant bits of a global tile id */
-  int32_t item_blocks;     /* sort / scan blocks over items */
+  int32_t item_blocks;     /* blocks of 4096 items (the sort counts its blocks view by view) */
   int32_t pair_blocks;     /* sort blocks over pair_capacity */
   int32_t g2d_stride;      /* per-item gradient values of the reverse compositor: 9, or 13 (spherical) */
   /* workspace layout, byte offsets */

@@ -92,8 +92,8 @@ struct TileSched {
   const uint32_t* order;  // tile ids by descending list length, or nullptr
   uint32_t* ctr;          // persistent: {next task, finished workgroups}; nullptr: one task each
   odgs_status* status;
-  uint32_t* split;        // counts by binning and of those the last forward's: long lists, tiles to split, and
-                          // 32x32 tiles to take in sixteen tasks
+  uint32_t* split;        // counts by binning and of those the last forward's: long lists (kept for inspection,
+                          // no kernel reads the two), tiles to split, 32x32 tiles to take in sixteen tasks
   int32_t tiles;
   int32_t split_cap;      // 0: whole tiles only
   int32_t split_all;      // every tile in four parts (split_cap == tiles)

@@ -32,34 +32,14 @@ namespace {
 constexpr float kAlphaMax = 0.99f;
 constexpr float kTStop = 1e-4f;
 
-template <int CTRL, int ROW_MASK>
-__device__ inline float dpp_shift_add(float v) {
-  const int s = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xF, false);
-  return v + __int_as_float(s);
-}
-
-// Wavefront sum by DPP; the total lands in lane 63.
-__device__ inline float wave_sum_to_lane63(float v) {
-  v = dpp_shift_add<0xB1, 0xF>(v);   // quad_perm [1,0,3,2]: pairs
-  v = dpp_shift_add<0x4E, 0xF>(v);   // quad_perm [2,3,0,1]: quads
-  v = dpp_shift_add<0x141, 0xF>(v);  // row_half_mirror: 8 lanes
-  v = dpp_shift_add<0x140, 0xF>(v);  // row_mirror: 16-lane rows
-  v = dpp_shift_add<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
-  v = dpp_shift_add<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
-  return v;
-}
-
-__device__ inline float lane63(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63)); }
-
-
-// Sums nine per-lane values over each 16-lane row in four DPP exchange steps (pairs (i, 15-i),
+// Nine per-lane values can be summed over each 16-lane row in four DPP exchange steps (pairs (i, 15-i),
 // (i, 7-i), (i, 3-i), (i, i^1) inside the row).  Values 0..7 are transposed (each step halves the
 // slots a lane holds: value index = lane bits 3,2,1 read as 4*b3 + 2*b2 + b1 on even lanes); value
 // 8 is summed in place through the first three steps and takes the odd lanes in the last one.
 // Lane i ends with the row sum of value kRowSlot[i % 16] (none where the table says 15; value 8,
-// held by all eight odd lanes, is assigned to lane 1 only).
+// held by all eight odd lanes, is assigned to lane 1 only).  The kernels take the first two steps
+// (quad_reduce9) and leave the last two to LDS; the table of all four is modelled by a host test.
 constexpr uint64_t kRowSlot = 0xF7F6F5F4F3F2F180ull;  // nibble i = value index held by row lane i
-
 
 // Sum of a value over the eight lanes of an aligned 8-lane group (every lane gets the sum).
 __device__ inline float group8_sum(float x) {
@@ -102,7 +82,7 @@ __device__ inline float red_finish(const float4& r0, const float4& r1) {
   return group8_sum(((r0.x + r0.y) + (r0.z + r0.w)) + ((r1.x + r1.y) + (r1.z + r1.w)));
 }
 
-// The first two steps (quad_reduce9) fold pairs of values with DPP adds whose bank masks write one
+// The first two of the exchange steps above (quad_reduce9) fold pairs of values with DPP adds whose bank masks write one
 // value's sum into half of the lanes and the other value's into the other half: two 4-cycle adds
 // per pair, where a select per side and an add took about eleven (measured on the VALU: DPP add 4.1
 // cycles per wavefront, select 2.8 to 4.2, plain add 2.5).  They sit in one block in an order that
@@ -128,14 +108,6 @@ __device__ inline void quad_reduce9(float (&g)[9]) {
       : "+&v"(g[0]), "+&v"(g[1]), "+&v"(g[2]), "+&v"(g[3]), "+&v"(g[8])
       : "v"(g[4]), "v"(g[5]), "v"(g[6]), "v"(g[7]));
 }
-
-__device__ inline float row_reduce9(float (&g)[9], bool b1, bool b0) {
-  quad_reduce9(g);
-  const float d = bfly<0x1B>(g[0], g[1], b1);  // quad_perm [3,2,1,0]
-  const float s8 = g[8] + dpp_read<0x1B>(g[8]);
-  return bfly<0xB1>(d, s8, b0);  // quad_perm [1,0,3,2]
-}
-
 
 // Minimum over the rectangle [x0, x1] x [y0, y1] of f(x, y) = a x^2 + 2 b x y + c y^2 (positive
 // definite), with nba = -b/a and nbc = -b/c precomputed.  f is convex with its minimum at the origin,
@@ -956,13 +928,11 @@ __global__ __launch_bounds__(TILE* TILE) void render_bwd_kernel(ViewTable vt, co
   static_assert(TILE == 8, "tiles of 16 and 32 take the four-pixel kernel");
   using St = Stage<TILE, BATCH>;
   constexpr int N = St::N;
-  // One wavefront per 8x8 tile, owning a slot per (value, entry) (the slot-set logic is written
-  // for up to four wavefronts, whose sets are summed at the flush, so no LDS atomics).
-  constexpr bool kSlots = St::NW <= 4;
-  constexpr int NS = kSlots ? St::NW : 1;
+  // One wavefront per 8x8 tile, owning a slot per (value, entry).
+  constexpr int NS = St::NW;
   __shared__ St S;
   __shared__ float acc[NS][9][BATCH + 1];  // padded rows: the nine slot writes hit nine banks
-  __shared__ float red[kSlots ? St::NW : 1][8][kRedStride];  // per-wavefront reduction scratch
+  __shared__ float red[NS][8][kRedStride];  // reduction scratch
   __shared__ int smax;
   if (forward_is_stale(sc)) return;  // uniform
   __shared__ uint32_t s_claim;
@@ -978,7 +948,6 @@ __global__ __launch_bounds__(TILE* TILE) void render_bwd_kernel(ViewTable vt, co
     const int x = tx0 + lx, y = ty0 + ly;
     const int lane = threadIdx.x & (kWave - 1);
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int slot = (int)((kRowSlot >> (4 * (lane & 15))) & 0xF);
     const float px = (float)x + 0.5f, py = (float)y + 0.5f;
     const float Wf = (float)W, half = wrap_half(vt, v);  // no seam in pinhole views
     const uint2 rg = ranges[g];
@@ -1037,26 +1006,21 @@ __global__ __launch_bounds__(TILE* TILE) void render_bwd_kernel(ViewTable vt, co
         const bool ok = jrel < P.last && !(power > 0.0f || power < b.y);
         if (__builtin_amdgcn_ballot_w64(ok) == 0ull) continue;  // uniform
         float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f), r1 = r0;
-        if (kSlots && pend) red_read(red[wq], lane, r0, r1);  // previous accepted entry's values
+        if (pend) red_read(red[wq], lane, r0, r1);  // previous accepted entry's values
         const float4 c = S.s2[k];
         float gq[9];
         bwd_pixel_step<false>(P, ok, 1, power, t1, t2, b, c, gq);
-        if constexpr (kSlots) {
-          if (pend) {
-            const float sj = red_finish(r0, r1);
-            if ((lane & 7) == 0) acc[wq][lane >> 3][pk] = sj;
-          }
-          red_write(red[wq], gq, lane);
-          const float s8 = wave_sum(gq[8]);
-          if (lane == 1) acc[wq][8][k] = s8;
-          pend = true;
-          pk = k;
-        } else {
-          const float rs = row_reduce9(gq, lane & 2, lane & 1);
-          if (slot < 9) atomicAdd(&acc[0][slot][k], rs);  // 9 lanes per row, 4 rows: one LDS atomic
+        if (pend) {
+          const float sj = red_finish(r0, r1);
+          if ((lane & 7) == 0) acc[wq][lane >> 3][pk] = sj;
         }
+        red_write(red[wq], gq, lane);
+        const float s8 = wave_sum(gq[8]);
+        if (lane == 1) acc[wq][8][k] = s8;
+        pend = true;
+        pk = k;
       }
-      if (kSlots && pend) {
+      if (pend) {
         float4 r0, r1;
         red_read(red[wq], lane, r0, r1);
         const float sj = red_finish(r0, r1);

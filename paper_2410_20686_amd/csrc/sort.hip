@@ -1192,7 +1192,8 @@ __global__ __launch_bounds__(256) void queue_count_kernel(const uint2* __restric
 }
 
 // Header words 4, 6 and 8 from the scan over buckets, whose threads each name their bucket and the number
-// of tiles in it or above.  Contains a barrier; cut: two words of LDS.
+// of tiles in it or above.  (Word 4, the lists of 1 / kLongShare of the pairs and, from kSplitAllTiles tiles
+// on, kLongLen, is for inspection: no kernel reads it.)  Contains a barrier; cut: two words of LDS.
 __device__ inline void set_split(int bucket, uint32_t upto, uint32_t cap, bool split_all, uint32_t pairs, uint32_t* cut,
                                  uint32_t* __restrict__ header) {
   const uint32_t floor = split_all ? 1u : kSplitLen;
