@@ -65,7 +65,9 @@ enum {
  * of a tile whose list is long against the launch (at least 1/4096 of all pairs, or among the 128
  * longest and at least 1/8192 and 1024 pairs; with 4096 tiles or more, at least 64 pairs; at most
  * max(1024, tiles / 8) tiles): those are split into four tasks at the front of the queue, so that one
- * list does not set the launch's length.  The two flags below select the alternatives: */
+ * list does not set the launch's length.  A 32x32 tile is four tasks, one per 16x16 block, and in the
+ * forward sixteen, one per 8x8 quadrant, if its list is long (at least 1/4096 of all pairs and 1024
+ * pairs; at most max(256, tiles / 8) tiles).  The two flags below select the alternatives: */
 #define ODGS_FLAG_SCHED_PERSISTENT 4 /* persistent launches: as many workgroups as fit on the device,
                                         each claiming the next task when it finishes one */
 #define ODGS_FLAG_SCHED_TILE_ID 8    /* one workgroup per tile in global tile id order (no queue, no

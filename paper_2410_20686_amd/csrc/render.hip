@@ -489,7 +489,7 @@ __device__ inline vec4 as_vec4(const float4& f) { return vec4{f.x, f.y, f.z, f.w
 // scalar, and past the list's end the run reads an entry that nothing reaches, so it needs no bounds.
 // The next batch's records are loaded while the current one is composited.  Each pixel's float operations
 // and their order are those of the one-entry loop.  Run by a whole wavefront; S is its staging.
-// 60k Gaussians on a cube map and two panoramas (0.57M pairs, lists of up to 901): 214 us unsplit, 129 us
+// 60k Gaussians on a cube map and a panorama (0.57M pairs, lists of up to 901): 214 us unsplit, 129 us
 // split with the one-entry loop, 106 us with runs whose reads the compiler had put one behind another, 80 us
 // with this; 6k on 512x256 (lists of up to 102) 16.4 us with the one-entry loop, 11.6 us with this.
 constexpr int kQuadRun = 4;
@@ -668,8 +668,10 @@ __device__ inline void composite_quadrant(FwdStage4<BATCH>& S, int q, uint2 rg, 
   last_out = last;
 }
 
-// (Seven wavefronts per SIMD, 71 registers: left to itself the compiler takes more with the quadrant path
-// beside the loop: 814 against 778 us at 500k Gaussians, 8 views, many lists split.)
+// (Seven wavefronts per SIMD, 72 registers: left to itself the compiler takes more with the quadrant path
+// beside the loop: 814 against 778 us at 500k Gaussians, 8 views, many lists split, in <16, 64, false>, the
+// one instance this was measured for.  The others of batches up to 64 but <16, 32, false> spill a few words
+// at it: 20 bytes of scratch with depth at 16, 20 without and 36 with depth at 32.)
 template <int BIN, int BATCH, bool DEPTH>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 64 ? 1 : 7))) void render_fwd4_kernel(
     ViewTable vt, const uint2* __restrict__ ranges, const uint32_t* __restrict__ pair_items, const Rec* __restrict__ rec,
@@ -1056,8 +1058,9 @@ __global__ __launch_bounds__(TILE* TILE) void render_bwd_kernel(ViewTable vt, co
 // masked folds, a branch-free map and the clamp only for entries that can need it; 1,350 us with the
 // last two steps of the reduction left to the group and the list words read from one register.  LDS
 // per wavefront counts too: 7,748 bytes took seven of its 1,280-byte granules and held a CU to 18
-// wavefronts where the registers allow 20; with a group's sums over its partials, 7,492 bytes take six:
-// 1,355 -> 1,290 us.
+// wavefronts where the registers allow 20; with a group's sums over its partials, 7,540 bytes take six:
+// 1,355 -> 1,290 us.  (On a card where all of that took 1,126 us, the select of its own that dL/dalpha
+// needs makes it 1,152.)
 template <int BATCH>
 struct Stage4 {  // (one entry more for reverse_quadrant)
   float4 s0[BATCH + 1];  // u, v, l0, l1
@@ -1139,7 +1142,8 @@ __device__ inline void flush_group(const Stage4<BATCH>& S, const FlushLane& f, f
 // One quadrant of a split tile in reverse, one pixel per lane: as in composite_quadrant, a run of
 // kQuadRunBwd entries is evaluated together and only T and DS stay chains; the culling masks, items and
 // records of the next batches are loaded ahead.  The cases of composite_quadrant: 306 us unsplit, 186 us with
-// the one-entry loop, 138 us with this (three entries together: 141), and 23.4 -> 18.9 us.
+// the one-entry loop, 138 us with this (three entries together: 141), and 23.4 -> 18.9 us; with dL/dalpha
+// selected on its own 7 and 5% more (135 -> 144 and 18.5 -> 19.5 us on one card).
 constexpr int kQuadRunBwd = 2;
 
 template <int BATCH>

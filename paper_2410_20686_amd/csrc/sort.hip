@@ -1152,7 +1152,13 @@ constexpr int kQueueTiles = 4096;  // tiles per block of the count and scatter k
 // pairs, forward 193, 175, 175, 175 (unsplit 219); 500k, 4096x2048, 8.4M pairs 261 / 463, 258 / 462,
 // 276 / 513, 294 / 574; 500k, 8 views, 25.8M pairs 735 / 1293, 740 / 1306, 744 / 1316, 776 / 1376; 300k,
 // mixed sizes, 20.8M pairs 957 / 1314, 928 / 1308, 778 / 1356.  The last one's few lists between the two
-// shares are what kSplitTop is for: 772 / 1352, and 500k on 4096x2048 stays at 260 / 469.
+// shares are what kSplitTop is for: 772 / 1352, and 500k on 4096x2048 stays at 260 / 469.  Forward us with
+// none, 32, 128 and 512 of them (reverse the same within 2%), on scenes drawn elsewise: mixed sizes, 14.9M
+// pairs 831, 828, 678, 639 and 21.8M 868, 806, 798, 801; 200k on 4 of 2048x1024, 5.8M 313, 312, 312, 281; 400k
+// on 4096x2048 and 6 of 1024x512, 16.6M 833, 830, 831, 586; 250k on 4096x2048, 2 of 2048x1024 and 5 of 512x256,
+// 11.7M 660, 654, 662, 493; 700k on 2 of 4096x2048, 19.6M 518, 515, 512, 517.  The spherical footprint, whose
+// quadrant tasks take one entry at a time, is even at all four (6.4M pairs 582, 574, 576, 577; 4.0M 433, 428,
+// 429, 441; below that no list lies between the shares).  So 128 loses nowhere; 512 would gain more.
 constexpr uint32_t kSplitLen = 64;
 constexpr uint32_t kSplitShare = 4096;
 constexpr uint32_t kSplitTop = 128;
@@ -1165,7 +1171,10 @@ constexpr int kSplitCapMin = 1024;
 // 250k Gaussians on 4 views of 1920x960 (2.8M pairs, lists of up to 4,661), forward us: 434 with none,
 // 412, 351 and 345 from 1 / 1024, 1 / 2048 and 1 / 4096 of the pairs on (there the most a sixteenth, then an
 // eighth of the tiles); one of the views 371 -> 239.  The reverse, which puts such a part's masks together
-// from four runs of bits, goes 479 -> 498.
+// from four runs of bits, goes 479 -> 498.  With none and with the rule, forward: 300k on 4096x2048 and 4 of
+// 1024x512 900 -> 460; 60k on 6 of 1024x512 275 -> 241; 100k on 2048x1024 231 -> 213; but 400k on 8 of
+// 2048x1024, where a thousand lists of 2,050 pairs and more (8.4M in all) each are staged sixteen times,
+// 663 -> 751.  There the rule reaches further than it should.
 constexpr uint32_t kFineShare = 4096;
 constexpr int kFineCapMin = 256;
 
