@@ -27,6 +27,11 @@ def _g2d(sc, st, dL):
     return res["g2d"][0], res["rast"].records().cpu().numpy()
 
 
+def _same(got, want):
+    """Equal but for the order in which the tasks' sums reach the FP64 totals (as two runs of one launch)."""
+    G.assert_grads_close({"g2d": got}, {"g2d": want}, names=("g2d",), rtol=1e-6, floor=1e-9)
+
+
 @pytest.mark.parametrize("schedule", ["queue", "tile_id"])
 @pytest.mark.parametrize("tile", [8, 16, 32])
 @pytest.mark.parametrize("opacity", [0.75, 0.875, 0.9375])
@@ -57,7 +62,7 @@ def test_nan_upstream_stays_with_its_pixel(footprint, colour, tile, schedule, fa
     dL[:, 34, 66] = np.nan
     got, _ = _g2d(sc, st, dL.ravel())
     assert np.isnan(got[0, :colour]).any()
-    np.testing.assert_array_equal(got[1, :colour], want[1, :colour])
+    _same(got[1, :colour], want[1, :colour])
     assert (want[1, :colour] != 0.0).all()
 
 
@@ -77,7 +82,7 @@ def test_nan_upstream_stays_in_its_block(footprint, tile, schedule):
     got, _ = _g2d(sc, st, dL.ravel())
     second = at == 74.5
     assert np.isnan(got[~second]).all()
-    np.testing.assert_array_equal(got[second], want[second])
+    _same(got[second], want[second])
     assert (want[second] != 0.0).all()
 
 
