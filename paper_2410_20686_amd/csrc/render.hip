@@ -841,6 +841,9 @@ struct BwdPixel {
   int last;
 };
 
+// Whether products of the pixel's gradients may leave the float range (kLarge).
+__device__ inline bool pixel_is_large(const BwdPixel& P) { return is_large(magnitude(P.dl0, P.dl1, P.dl2) + fabsf(P.DS)); }
+
 // The position and shape sums are taken in the footprint's whitened coordinates t = L d
 // (t1 = l0 du + l1 dv, t2 = l2 dv, L = [[l0, l1], [0, l2]] the record's factor of Sigma^-1 / 2, so
 // power = -|t|^2): per pixel dpow * t and dpow * t t^T, whose entries are all of the same order for
@@ -878,19 +881,20 @@ __device__ inline double g2d_flush_value(const float (&acc)[NS][9][B], int q, in
 
 // One pixel's contribution of a Gaussian to the nine per-tile sums (added to gq when ADD, else
 // written; slots 0..4 in whitened coordinates as above), and the pixel's recursion step.  `ok`: the
-// Gaussian contributed to this pixel; t1 = l0 du + l1 dv, t2 = l2 dv.  `clamp` (uniform): the opacity
-// is above 0.99, so that alpha may be clamped (else G <= 1 keeps it below); two branches past an
-// instruction or two (the whole step compiled for both cases copies the pixel state between them,
-// which costs more than the branches).  dL/dalpha is zeroed by a select of its own where the Gaussian
-// does not contribute: the product with alpha = 0 would pass on a NaN of the pixel's upstream gradient.
+// Gaussian contributed to this pixel; t1 = l0 du + l1 dv, t2 = l2 dv.  `rare` (uniform): the opacity
+// is above 0.99, so that alpha may be clamped (else G <= 1 keeps it below), or an upstream gradient or
+// a colour is large or not finite, so that dL/dalpha needs a select of its own where the Gaussian does not
+// contribute (else its products with alpha = 0 and G = 0 are zero); two branches past an instruction or
+// two (the whole step compiled for both cases copies the pixel state between them, which costs more than
+// the branches, and the select in every step 2%: 1,126 -> 1,152 us at 500k Gaussians, 8 views).
 template <bool ADD>
-__device__ inline void bwd_pixel_step(BwdPixel& P, bool ok, int clamp, float power, float t1, float t2, const float4& b,
+__device__ inline void bwd_pixel_step(BwdPixel& P, bool ok, int rare, float power, float t1, float t2, const float4& b,
                                       const float4& c, float (&gq)[9]) {
   const float G = ok ? __expf(power) : 0.0f;
   const float araw = b.z * G;
   // alpha = 0 where the Gaussian does not contribute, so its weight below is 0 without a select
   float alpha = araw;
-  if (__builtin_expect(opaque(clamp) != 0, 0)) {
+  if (__builtin_expect(opaque(rare) != 0, 0)) {
     alpha = fminf(alpha, kAlphaMax);
     keep_branch(alpha);
   }
@@ -900,9 +904,9 @@ __device__ inline void bwd_pixel_step(BwdPixel& P, bool ok, int clamp, float pow
   P.T = P.T * inv_om;
   const float wk = alpha * P.T;
   const float dc = fmaf(P.dl0, c.x, fmaf(P.dl1, c.y, P.dl2 * c.z));  // dL/dC . colour
-  float dla = ok ? fmaf(dc, P.T, -P.DS * inv_om) : 0.0f;  // dL/dalpha
-  if (__builtin_expect(opaque(clamp) != 0, 0)) {
-    dla = araw > kAlphaMax ? 0.0f : dla;  // a clamped alpha does not depend on the inputs
+  float dla = fmaf(dc, P.T, -P.DS * inv_om);  // dL/dalpha
+  if (__builtin_expect(opaque(rare) != 0, 0)) {
+    dla = !ok || araw > kAlphaMax ? 0.0f : dla;  // a clamped alpha does not depend on the inputs
     keep_branch(dla);
   }
   P.DS = fmaf(dc, wk, P.DS);
@@ -1059,8 +1063,7 @@ __global__ __launch_bounds__(TILE* TILE) void render_bwd_kernel(ViewTable vt, co
 // last two steps of the reduction left to the group and the list words read from one register.  LDS
 // per wavefront counts too: 7,748 bytes took seven of its 1,280-byte granules and held a CU to 18
 // wavefronts where the registers allow 20; with a group's sums over its partials, 7,540 bytes take six:
-// 1,355 -> 1,290 us.  (On a card where all of that took 1,126 us, the select of its own that dL/dalpha
-// needs makes it 1,152.)
+// 1,355 -> 1,290 us.
 template <int BATCH>
 struct Stage4 {  // (one entry more for reverse_quadrant)
   float4 s0[BATCH + 1];  // u, v, l0, l1
@@ -1142,8 +1145,7 @@ __device__ inline void flush_group(const Stage4<BATCH>& S, const FlushLane& f, f
 // One quadrant of a split tile in reverse, one pixel per lane: as in composite_quadrant, a run of
 // kQuadRunBwd entries is evaluated together and only T and DS stay chains; the culling masks, items and
 // records of the next batches are loaded ahead.  The cases of composite_quadrant: 306 us unsplit, 186 us with
-// the one-entry loop, 138 us with this (three entries together: 141), and 23.4 -> 18.9 us; with dL/dalpha
-// selected on its own 7 and 5% more (135 -> 144 and 18.5 -> 19.5 us on one card).
+// the one-entry loop, 138 us with this (three entries together: 141), and 23.4 -> 18.9 us.
 constexpr int kQuadRunBwd = 2;
 
 template <int BATCH>
@@ -1246,7 +1248,7 @@ __device__ inline void reverse_quadrant(Stage4<BATCH>& S, float* ring, const Flu
           P.T = P.T * inv_om;
           wk[j] = alpha[j] * P.T;
           const float dc = fmaf(P.dl0, c[j].x, fmaf(P.dl1, c[j].y, P.dl2 * c[j].z));
-          dla[j] = ok[j] ? fmaf(dc, P.T, -P.DS * inv_om) : 0.0f;
+          dla[j] = ok[j] ? fmaf(dc, P.T, -P.DS * inv_om) : 0.0f;  // (a select each costs less here than a flag)
           P.DS = fmaf(dc, wk[j], P.DS);
         }
         if (__builtin_expect(opaque(clamp) != 0, 0)) {  // uniform
@@ -1331,11 +1333,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 6
     }
     BwdPixel P[4];  // quadrant q = 2 * qy + qx
     int wmax = 0;
+    bool some_large = false;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       P[q] = load_pixel(q);
       wmax = max(wmax, P[q].last);
+      some_large = some_large || pixel_is_large(P[q]);
     }
+    const uint32_t large = __builtin_amdgcn_ballot_w64(some_large) != 0ull ? kEntryClamp << 4 : 0;
     wmax = wave_max(wmax);
     for (int end = wmax; end > 0; end -= BATCH) {
       const int cnt = min(BATCH, end);
@@ -1353,7 +1358,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 6
             const Rec r = rec[item];
             S.s0[e] = r.r0;
             const float reach = fabsf((float)tx0 + 0.5f * (float)TILE - r.r0.x) + 0.5f * (float)TILE + 1.0f;
-            m |= (reach < half ? 0 : kEntryWrap << 4) | (r.r1.y > kAlphaMax ? kEntryClamp << 4 : 0);
+            m |= reach < half ? 0 : kEntryWrap << 4;
+            if (r.r1.y > kAlphaMax || is_large(magnitude(r.r2.x, r.r2.y, r.r2.z))) m |= kEntryClamp << 4;
             S.s1[e] = make_float4(r.r1.x, r.r1.z, r.r1.y, 0.0f);
             S.sid[e] = item;
             S.s2[e] = r.r2;
@@ -1373,7 +1379,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(BATCH > 6
           const int jrel = end - 1 - k;
           const float4 a = S.s0[k];
           const float4 b = S.s1[k];
-          const uint32_t mq = km >> 8;
+          const uint32_t mq = km >> 8 | large;
           float du0 = px0 - a.x, du1 = px1 - a.x;
           const float4 c = S.s2[k];
           float gq[9];

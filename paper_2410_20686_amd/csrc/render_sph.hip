@@ -748,6 +748,7 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
     float dl0[4], dl1[4], dl2[4], T[4], DS[4];
     int last[4], qmax[4];  // qmax: the quadrant's last contributor over its pixels (uniform)
     int wmax = 0;
+    bool some_large = false;  // see kLarge
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       if (!((sel >> q) & 1u)) {
@@ -764,12 +765,14 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
       last[q] = ws_last[gp];
       // dL/dC . (colour of everything behind, incl. background), one scalar for the three channels
       DS[q] = T[q] * fmaf(dl0[q], bg0, fmaf(dl1[q], bg1, dl2[q] * bg2));
+      some_large = some_large || is_large(magnitude(dl0[q], dl1[q], dl2[q]) + fabsf(DS[q]));
       int m = last[q];
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
       qmax[q] = __builtin_amdgcn_readfirstlane(m);
       wmax = max(wmax, qmax[q]);
     }
+    const uint32_t large = __builtin_amdgcn_ballot_w64(some_large) != 0ull ? kEntryClamp << 4 : 0;
     const uint8_t* qm = qmask + (sel == 0xFu ? 0 : (int64_t)__builtin_ctz(sel) * qplane);
     for (int end = wmax; end > 0; end -= BATCH) {
       const int cnt = min(BATCH, end);
@@ -790,7 +793,7 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
             S.s2[e] = r.s2;
             S.s3[e] = r.s3;
             S.sid[e] = item;
-            if (r.s2.z > kAlphaMax) m |= kEntryClamp << 4;
+            if (r.s2.z > kAlphaMax || is_large(magnitude(r.s3.x, r.s3.y, r.s3.z))) m |= kEntryClamp << 4;
           }
         }
         const uint64_t bl = __builtin_amdgcn_ballot_w64(m != 0u);
@@ -805,7 +808,7 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
           const uint32_t km = __builtin_amdgcn_readlane(words, i);
           const int k = (int)(km & 0xFFu);
           const int jrel = end - 1 - k;
-          const uint32_t mq = km >> 8;
+          const uint32_t mq = km >> 8 | large;
           const float4 a = S.s0[k], b = S.s1[k], c = S.s2[k];
           const float4 col = S.s3[k];
           float gv[kNV];
@@ -832,10 +835,9 @@ __global__ __launch_bounds__(kWave) void render_sph_bwd4_kernel(
             T[q] = T[q] * inv_om;  // transmittance in front of this Gaussian (alpha = 0: times exactly 1)
             const float wk = alpha * T[q];
             const float dc = fmaf(dl0[q], col.x, fmaf(dl1[q], col.y, dl2[q] * col.z));  // dL/dC . colour
-            // dL/dalpha (a select of its own: the pixel's upstream gradient may be NaN)
-            float dla = ok ? fmaf(dc, T[q], -DS[q] * inv_om) : 0.0f;
+            float dla = fmaf(dc, T[q], -DS[q] * inv_om);  // dL/dalpha
             if (__builtin_expect(opaque((int)(mq & (kEntryClamp << 4))) != 0, 0)) {
-              dla = araw > kAlphaMax ? 0.0f : dla;  // a clamped alpha does not depend on the inputs
+              dla = !ok || araw > kAlphaMax ? 0.0f : dla;  // a clamped alpha does not depend on the inputs
               keep_branch(dla);
             }
             DS[q] = fmaf(dc, wk, DS[q]);

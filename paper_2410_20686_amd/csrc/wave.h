@@ -30,7 +30,8 @@ __device__ inline float sum_rows(float x) {
 
 // Flags of a staged entry in the one-wavefront compositors (above the quadrant mask).
 constexpr int kEntryWrap = 1;   // some pixel centre of the tile may need the seam wrap
-constexpr int kEntryClamp = 2;  // opacity above 0.99: alpha may be clamped (in composite_quadrant also: infinite colour)
+constexpr int kEntryClamp = 2;  // opacity above 0.99: alpha may be clamped (forward quadrant tasks: or the colour is
+                                // infinite; reverse: or the colour is kLarge and more, see is_large)
 
 // A uniform word the compiler cannot relate to its other uses, so that a test of it stays a scalar
 // test beside its branch.
@@ -43,6 +44,15 @@ __device__ inline int opaque(int x) {
 __device__ inline void set_lane(uint32_t& x, uint32_t value, int lane) {
   asm("s_mov_b32 m0, %2\n\tv_writelane_b32 %0, %1, m0" : "+v"(x) : "s"(value), "s"(lane) : "m0");
 }
+
+// Upstream gradients and colours below kLarge give the reverse steps finite values throughout: with both
+// below 2^50 (and dL/dC . background below it), dL/dC . colour stays below 2^102, and so does the sum of such
+// products times weights that add up to one; over 1 - alpha >= 0.01 below 2^109.  A value that is not finite
+// counts as large.  Only where something is large does a step zero dL/dalpha by a select of its own for
+// pixels that the Gaussian does not reach; elsewhere its product with alpha = 0 is zero.
+constexpr float kLarge = 0x1p50f;
+__device__ inline bool is_large(float sum_of_magnitudes) { return !(sum_of_magnitudes < kLarge); }
+__device__ inline float magnitude(float a, float b, float c) { return fabsf(a) + fabsf(b) + fabsf(c); }
 
 // Keeps a rarely taken uniform branch a branch: the value is not computed on the other path.
 __device__ inline void keep_branch(float& x) { asm volatile("" : "+v"(x)); }

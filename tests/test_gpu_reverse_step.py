@@ -51,17 +51,19 @@ def test_opacity_gradient_is_exact(footprint, slot, tile, schedule, opacity):
 @pytest.mark.parametrize("tile", [8, 16, 32])
 @pytest.mark.parametrize("far", [0, 1])
 @pytest.mark.parametrize("footprint,colour", [("affine", 6), ("spherical", 10)])
-def test_nan_upstream_stays_with_its_pixel(footprint, colour, tile, schedule, far):
-    """Two Gaussians in one 8x8 block of pixels, the upstream gradient NaN at the first one's centre, which
-    the second does not reach: its position, shape and opacity gradients are those of a zero there."""
+@pytest.mark.parametrize("value", [np.nan, np.inf, 3e38])
+def test_upstream_stays_with_its_pixel(value, footprint, colour, tile, schedule, far):
+    """Two Gaussians in one 8x8 block of pixels, the upstream gradient not finite, or so large that its
+    products are not, at the first one's centre, which the second does not reach: its position, shape and
+    opacity gradients are those of a zero there."""
     sc = _scene([66.5, 70.5], [34.5, 38.5], 0.5, 0.02, radius=np.array([2.0, 2.5] if far else [2.5, 2.0]))
     dL = np.random.default_rng(5).standard_normal((3, H, W)).astype(np.float32)
     st = settings(tile=tile, schedule=schedule, footprint=footprint)
     dL[:, 34, 66] = 0.0
     want, _ = _g2d(sc, st, dL.ravel())
-    dL[:, 34, 66] = np.nan
+    dL[:, 34, 66] = value
     got, _ = _g2d(sc, st, dL.ravel())
-    assert np.isnan(got[0, :colour]).any()
+    assert not np.array_equal(got[0, :colour], want[0, :colour])
     _same(got[1, :colour], want[1, :colour])
     assert (want[1, :colour] != 0.0).all()
 
@@ -104,3 +106,23 @@ def test_spherical_denominator_past_the_float_range(tile):
     assert np.isfinite(res["g2d"]).all()
     ref = O.backward(sc, cams, st, dL.ravel(), mode=32, want_g2d=True)["g2d_kernel"]
     G.assert_grads_close({"opacity": res["g2d"][..., 9]}, {"opacity": ref[..., 9]}, names=("opacity",))
+
+
+@pytest.mark.parametrize("schedule", ["queue", "tile_id"])
+@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("footprint,colour", [("affine", 6), ("spherical", 10)])
+def test_large_colour_stays_with_its_pixels(footprint, colour, tile, schedule):
+    """A colour of 8e37 whose product with the upstream gradient overflows at a pixel that the Gaussian does
+    not reach, in an 8x8 block that it does: its position, shape and opacity gradients are those of a zero
+    there."""
+    sc = _scene(66.5, 34.5, 0.5, 0.02)
+    sc.sh[:, 0] = np.float32(3e38), 0.0, 0.1
+    dL = np.zeros((3, H, W), np.float32)
+    dL[:, 33:37, 65:69] = 1e-3 * np.random.default_rng(7).uniform(0.5, 1.0, (3, 4, 4))
+    st = settings(tile=tile, schedule=schedule, footprint=footprint)
+    want, rec = _g2d(sc, st, dL.ravel())
+    assert 8e37 < rec[0, 8] < np.inf and np.isfinite(want).all()
+    dL[0, 38, 70] = 100.0
+    got, _ = _g2d(sc, st, dL.ravel())
+    _same(got[0, :colour], want[0, :colour])
+    assert (want[0, :colour] != 0.0).all()
